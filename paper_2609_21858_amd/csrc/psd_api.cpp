@@ -117,8 +117,6 @@ psd_status check_block(const psd_params* p, const psd_block* b) {
     return PSD_OK;
 }
 
-bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
-
 psd::RaceArgs base_args(const psd_params* p, const psd_block* b) {
     psd::RaceArgs a;
     memset(&a, 0, sizeof a);
@@ -214,11 +212,6 @@ psd::MpfrArgs mpfr_args(const psd_params* p, const psd_block* b, int32_t s_begin
     return m;
 }
 
-bool mpfr_vec(const psd_params* p, const void* draft_logits) {
-    const size_t es = p->dtype == PSD_BF16 ? 2 : 4;
-    return ((size_t)p->vocab * es) % 16 == 0 && aligned16(draft_logits);
-}
-
 // A depth's launch has one workgroup per (sequence, path), each streaming its row.
 // When those cannot fill the device (B K < 1024), every draft row of the call is
 // streamed first in one launch (group maxima, maxima, LSE) and the depths only sample
@@ -236,7 +229,7 @@ psd_status mpfr_prepare(const psd_params* p, const psd_block* b, psd::MpfrArgs& 
     m.row_max = (uint64_t*)((unsigned char*)b->workspace + M.rmax);
     m.row_seed = (uint64_t*)((unsigned char*)b->workspace + M.seed);
     bool fits = false;
-    hipError_t e = psd::mpfr_all_depths_fit(m, p->dtype == PSD_BF16, mpfr_vec(p, m.logits), p->clocks, &fits);
+    hipError_t e = psd::mpfr_all_depths_fit(m, p->dtype == PSD_BF16, p->clocks, &fits);
     if (e != hipSuccess) return hip_fail(e, "MPFR occupancy query");
     m.tok_slot = fits ? (uint64_t*)((unsigned char*)b->workspace + M.slot) : nullptr;
     m.stream_records_epoch = fits ? 0 : 1;
@@ -244,13 +237,13 @@ psd_status mpfr_prepare(const psd_params* p, const psd_block* b, psd::MpfrArgs& 
 }
 
 psd_status mpfr_stream_rows(const psd_params* p, psd::MpfrArgs& m, hipStream_t stream) {
-    hipError_t e = psd::launch_mpfr_stream(m, p->dtype == PSD_BF16, mpfr_vec(p, m.logits), stream);
+    hipError_t e = psd::launch_mpfr_stream(m, p->dtype == PSD_BF16, stream);
     if (e != hipSuccess) return hip_fail(e, "MPFR stream kernel launch");
     return PSD_OK;
 }
 
 psd_status mpfr_sample_depths(const psd_params* p, psd::MpfrArgs& m, hipStream_t stream) {
-    hipError_t e = psd::launch_mpfr_depths(m, p->dtype == PSD_BF16, mpfr_vec(p, m.logits), p->clocks, stream);
+    hipError_t e = psd::launch_mpfr_depths(m, p->dtype == PSD_BF16, p->clocks, stream);
     if (e != hipSuccess) return hip_fail(e, "MPFR draft kernel launch");
     return PSD_OK;
 }
@@ -342,11 +335,7 @@ psd_status run_topk(const psd_params* p, const psd_block* b, int32_t s_begin, in
 }
 
 psd_status run_race(const psd_params* p, psd::RaceArgs& a, hipStream_t stream) {
-    const size_t es = p->dtype == PSD_BF16 ? 2 : 4;
-    bool vec = ((size_t)p->vocab * es) % 16 == 0;
-    if (a.draft_logits) vec = vec && aligned16(a.draft_logits);
-    if (a.target_logits) vec = vec && aligned16(a.target_logits);
-    hipError_t e = psd::launch_race(a, p->dtype == PSD_BF16, vec, p->clocks, stream);
+    hipError_t e = psd::launch_race(a, p->dtype == PSD_BF16, p->clocks, stream);
     if (e != hipSuccess) return hip_fail(e, "race kernel launch");
     return PSD_OK;
 }

@@ -209,16 +209,16 @@ hipError_t launch_topk_race(const TopkRaceArgs& a, int layout, hipStream_t strea
 // [B][gamma+1] and the drafts, then the call's error bits (with *a.status_in).
 hipError_t launch_walk(const TopkRaceArgs& a, hipStream_t stream);
 
-hipError_t launch_race(const RaceArgs& a, bool bf16, bool vec, int layout, hipStream_t stream);
+hipError_t launch_race(const RaceArgs& a, bool bf16, int layout, hipStream_t stream);
 // The sampling of depths [s_begin, s_begin + s_count): one launch that runs every
 // depth when the drafts can be handed over in tagged slots (tok_slot set, more than
 // one depth) and every workgroup of it can be resident at once, else one launch per
 // depth.
-hipError_t launch_mpfr_depths(MpfrArgs a, bool bf16, bool vec, int layout, hipStream_t stream);
+hipError_t launch_mpfr_depths(MpfrArgs a, bool bf16, int layout, hipStream_t stream);
 // Whether one sampling launch can run every depth of a: more than one depth, and all
 // B K workgroups resident together.  *fits is set; a HIP error of the query is returned.
-hipError_t mpfr_all_depths_fit(const MpfrArgs& a, bool bf16, bool vec, int layout, bool* fits);
-hipError_t launch_mpfr_stream(const MpfrArgs& a, bool bf16, bool vec, hipStream_t stream);
+hipError_t mpfr_all_depths_fit(const MpfrArgs& a, bool bf16, int layout, bool* fits);
+hipError_t launch_mpfr_stream(const MpfrArgs& a, bool bf16, hipStream_t stream);
 hipError_t launch_finish_status(uint32_t* ctrl, uint32_t* status, hipStream_t stream);
 hipError_t launch_detect(const DetectArgs& a, int layout, hipStream_t stream);
 hipError_t launch_pvalue(int n, const double* score, const int32_t* count, double* out_log_p,

@@ -87,66 +87,71 @@ __device__ __forceinline__ float mload(const unsigned char* row, bool bf16, int 
     return bf16 ? __uint_as_float((uint32_t)((const uint16_t*)row)[v] << 16) : ((const float*)row)[v];
 }
 
+// 16 bytes at any element boundary in one load (rows of an odd vocabulary start off
+// the 16-byte grid).
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4_f32 __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t u32x4_b16 __attribute__((ext_vector_type(4), aligned(2)));
+template <bool BF16>
+__device__ __forceinline__ uint4 mld16(const void* p) {
+    u32x4 v;
+    if constexpr (BF16)
+        v = *(const u32x4_b16*)p;
+    else
+        v = *(const u32x4_f32*)p;
+    return make_uint4(v.x, v.y, v.z, v.w);
+}
+
+// Raw words of 8 logits for a load issued ahead of its use (one or two 16-byte loads,
+// the address clamped into the row).
+template <bool BF16>
+struct MRaw {
+    uint4 w[BF16 ? 1 : 2];
+};
+template <bool BF16>
+__device__ __forceinline__ void mraw_values(const MRaw<BF16>& r, float (&x)[8]) {
+    if constexpr (BF16) {
+        const uint4 u = r.w[0];
+        x[0] = bf16_lo(u.x); x[1] = bf16_hi(u.x); x[2] = bf16_lo(u.y); x[3] = bf16_hi(u.y);
+        x[4] = bf16_lo(u.z); x[5] = bf16_hi(u.z); x[6] = bf16_lo(u.w); x[7] = bf16_hi(u.w);
+    } else {
+        x[0] = __uint_as_float(r.w[0].x); x[1] = __uint_as_float(r.w[0].y);
+        x[2] = __uint_as_float(r.w[0].z); x[3] = __uint_as_float(r.w[0].w);
+        x[4] = __uint_as_float(r.w[1].x); x[5] = __uint_as_float(r.w[1].y);
+        x[6] = __uint_as_float(r.w[1].z); x[7] = __uint_as_float(r.w[1].w);
+    }
+}
+
 // 8 logits from `base` (-inf past V).
-template <bool BF16, bool VEC>
+template <bool BF16>
 __device__ __forceinline__ void mload8(const unsigned char* row, int V, int base, float (&x)[8]) {
-    if constexpr (VEC) {
-        if constexpr (BF16) {
-            uint4 u = make_uint4(0xFF80FF80u, 0xFF80FF80u, 0xFF80FF80u, 0xFF80FF80u);
-            if (base < V) u = *(const uint4*)((const uint16_t*)row + base);
-            x[0] = bf16_lo(u.x); x[1] = bf16_hi(u.x); x[2] = bf16_lo(u.y); x[3] = bf16_hi(u.y);
-            x[4] = bf16_lo(u.z); x[5] = bf16_hi(u.z); x[6] = bf16_lo(u.w); x[7] = bf16_hi(u.w);
-        } else {
-            float4 f0 = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY), f1 = f0;
-            if (base < V) f0 = *(const float4*)((const float*)row + base);
-            if (base + 4 < V) f1 = *(const float4*)((const float*)row + base + 4);
-            x[0] = f0.x; x[1] = f0.y; x[2] = f0.z; x[3] = f0.w;
-            x[4] = f1.x; x[5] = f1.y; x[6] = f1.z; x[7] = f1.w;
-        }
+    if (base + 8 <= V) {
+        MRaw<BF16> r;
+        r.w[0] = mld16<BF16>(row + (size_t)base * (BF16 ? 2 : 4));
+        if constexpr (!BF16) r.w[1] = mld16<BF16>(row + ((size_t)base + 4) * 4);
+        mraw_values<BF16>(r, x);
     } else {
 #pragma unroll
         for (int i = 0; i < 8; ++i) x[i] = base + i < V ? mload(row, BF16, base + i) : -INFINITY;
     }
 }
 
-// Raw words of 8 logits for a load issued ahead of its use (vector path: one or two
-// 16-byte loads, the address clamped into the row; scalar path: nothing loaded ahead).
-template <bool BF16, bool VEC>
-struct MRaw {
-    uint4 w[BF16 ? 1 : 2];
-};
-template <bool BF16, bool VEC>
-__device__ __forceinline__ void mraw_load(const unsigned char* row, int V, int base, MRaw<BF16, VEC>& r) {
-    if constexpr (VEC) {
-        if constexpr (BF16) {
-            r.w[0] = *(const uint4*)((const uint16_t*)row + min(base, V - 8));
-        } else {
-            r.w[0] = *(const uint4*)((const float*)row + min(base, V - 4));
-            r.w[1] = *(const uint4*)((const float*)row + min(base + 4, V - 4));
-        }
+template <bool BF16>
+__device__ __forceinline__ void mraw_load(const unsigned char* row, int V, int base, MRaw<BF16>& r) {
+    if constexpr (BF16) {
+        r.w[0] = mld16<true>((const uint16_t*)row + min(base, V - 8));
+    } else {
+        r.w[0] = mld16<false>((const float*)row + min(base, V - 4));
+        r.w[1] = mld16<false>((const float*)row + min(base + 4, V - 4));
     }
 }
-// The 8 logits from `base` (-inf past V) out of the raw words (scalar path: loaded here).
-template <bool BF16, bool VEC>
-__device__ __forceinline__ void mraw_unpack(const unsigned char* row, int V, int base, const MRaw<BF16, VEC>& r,
+// The 8 logits from `base` (-inf past V) out of the raw words; the row's last tokens
+// are loaded here when the unit reaches past the row.
+template <bool BF16>
+__device__ __forceinline__ void mraw_unpack(const unsigned char* row, int V, int base, const MRaw<BF16>& r,
                                             float (&x)[8]) {
-    if constexpr (VEC) {
-        if constexpr (BF16) {
-            const uint4 u = r.w[0];
-            x[0] = bf16_lo(u.x); x[1] = bf16_hi(u.x); x[2] = bf16_lo(u.y); x[3] = bf16_hi(u.y);
-            x[4] = bf16_lo(u.z); x[5] = bf16_hi(u.z); x[6] = bf16_lo(u.w); x[7] = bf16_hi(u.w);
-        } else {
-            x[0] = __uint_as_float(r.w[0].x); x[1] = __uint_as_float(r.w[0].y);
-            x[2] = __uint_as_float(r.w[0].z); x[3] = __uint_as_float(r.w[0].w);
-            x[4] = __uint_as_float(r.w[1].x); x[5] = __uint_as_float(r.w[1].y);
-            x[6] = __uint_as_float(r.w[1].z); x[7] = __uint_as_float(r.w[1].w);
-        }
-#pragma unroll
-        for (int i = 0; i < 8; ++i)
-            if (base + i >= V) x[i] = -INFINITY;
-    } else {
-        mload8<BF16, VEC>(row, V, base, x);
-    }
+    mraw_values<BF16>(r, x);
+    if (base + 8 > V) mload8<BF16>(row, V, base, x);
 }
 
 template <int LAYOUT>
@@ -215,7 +220,7 @@ __device__ __forceinline__ void eval_chunk(MShared& sm, const MpfrArgs& a, const
 // Stream one row: log-sum-exp at T (to *lse_out when non-null), the maximum of every
 // 128-token group (to gm, in LDS or global memory) and the row maximum (returned to
 // every thread).  red_* are LDS scratch of kMBlock / 64 entries.
-template <bool BF16, bool VEC>
+template <bool BF16>
 __device__ __forceinline__ float mstream_row(const unsigned char* row, int V, float invT, float* gm, float* lse_out,
                                              float* red_m, float* red_s, float* red_x, float* rowmax) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -225,16 +230,18 @@ __device__ __forceinline__ float mstream_row(const unsigned char* row, int V, fl
     const int nstep = (V + 2047) / 2048;
     // software-pipelined: the next four units' raw words are loaded before the current
     // four are reduced (words past the row are never used)
-    MRaw<BF16, VEC> wn[4];
+    // a row of fewer than 8 tokens: nothing is loaded ahead
+    MRaw<BF16> wn[4];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) mraw_load<BF16, VEC>(row, V, q * 2048 + 8 * tid, wn[q]);
+    for (int q = 0; q < 4; ++q)
+        if (V >= 8) mraw_load<BF16>(row, V, q * 2048 + 8 * tid, wn[q]);
     for (int st0 = 0; st0 < nstep; st0 += 4) {
         float x[4][8];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) mraw_unpack<BF16, VEC>(row, V, (st0 + q) * 2048 + 8 * tid, wn[q], x[q]);
+        for (int q = 0; q < 4; ++q) mraw_unpack<BF16>(row, V, (st0 + q) * 2048 + 8 * tid, wn[q], x[q]);
         if (st0 + 4 < nstep) {
 #pragma unroll
-            for (int q = 0; q < 4; ++q) mraw_load<BF16, VEC>(row, V, (st0 + 4 + q) * 2048 + 8 * tid, wn[q]);
+            for (int q = 0; q < 4; ++q) mraw_load<BF16>(row, V, (st0 + 4 + q) * 2048 + 8 * tid, wn[q]);
         }
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
@@ -319,7 +326,7 @@ __device__ __forceinline__ void seed_groups(const float* gm, int ng, int* seed_g
 
 // Each seed group's largest token (its lowest index holding the maximum), 16 lanes per
 // group (after a barrier that published seed_g).  Every thread calls it.
-template <bool BF16, bool VEC>
+template <bool BF16>
 __device__ __forceinline__ void seed_tokens(const unsigned char* row, int V, const float* gm, const int* seed_g,
                                             int* seed_tok) {
     const int tid = threadIdx.x;
@@ -329,7 +336,7 @@ __device__ __forceinline__ void seed_tokens(const unsigned char* row, int V, con
         if (g >= 0) {
             float x[8];
             const int base = g * 128 + sub * 8;
-            mload8<BF16, VEC>(row, V, base, x);
+            mload8<BF16>(row, V, base, x);
 #pragma unroll
             for (int t = 7; t >= 0; --t)
                 if (base + t < V && x[t] == gm[g]) tk = base + t;
@@ -373,7 +380,7 @@ __device__ __forceinline__ void record_epoch(const MpfrArgs& a, uint32_t ep) {
 // s_count), depth-major (the first depth's rows are handed out first), one row per
 // workgroup or (stream_grid) several, writing each row's group maxima, maximum and
 // seed tokens as tagged words and its LSE.  It never waits.
-template <bool BF16, bool VEC>
+template <bool BF16>
 __global__ __launch_bounds__(kMBlock) void mpfr_stream_kernel(MpfrArgs a) {
     __shared__ float red_m[kMBlock / 64], red_s[kMBlock / 64], red_x[kMBlock / 64], rowmax;
     __shared__ float gm[kMaxGroups];
@@ -391,7 +398,7 @@ __global__ __launch_bounds__(kMBlock) void mpfr_stream_kernel(MpfrArgs a) {
         const unsigned char* row = (const unsigned char*)a.logits +
                                    (((size_t)b * a.K + k) * a.s_count + (size_t)(s - a.s_begin)) * (size_t)a.V * esize;
         const size_t rid = ((size_t)b * a.K + k) * a.gamma + s;
-        const float xm = mstream_row<BF16, VEC>(row, a.V, a.invT, gm, a.draft_lse ? a.draft_lse + rid : nullptr,
+        const float xm = mstream_row<BF16>(row, a.V, a.invT, gm, a.draft_lse ? a.draft_lse + rid : nullptr,
                                                 red_m, red_s, red_x, &rowmax);
         // (mstream_row ends with a barrier: the group maxima and the epoch are in LDS)
         const uint64_t tag = (uint64_t)ep_s << 32;
@@ -400,7 +407,7 @@ __global__ __launch_bounds__(kMBlock) void mpfr_stream_kernel(MpfrArgs a) {
         // the row's seed tokens, for every context this row may serve
         seed_groups(gm, ng, seed_g);
         __syncthreads();
-        seed_tokens<BF16, VEC>(row, a.V, gm, seed_g, seed_tok);
+        seed_tokens<BF16>(row, a.V, gm, seed_g, seed_tok);
         __syncthreads();
         if (threadIdx.x < kSeeds)
             mst_dev(a.row_seed + rid * kSeeds + threadIdx.x, tag | (uint32_t)seed_tok[threadIdx.x]);
@@ -443,7 +450,7 @@ __device__ __forceinline__ uint32_t row_word(const MpfrArgs& a, const uint64_t* 
 
 // Depth s of path k of sequence b (every thread of the workgroup calls it; its early
 // returns are uniform).  ep: the launch's epoch when it runs every depth.
-template <bool BF16, bool VEC, int LAYOUT>
+template <bool BF16, int LAYOUT>
 __device__ __forceinline__ void mpfr_depth(const MpfrArgs& a, MShared& sm, float* gm, int b, int k, int s, uint32_t ep) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint32_t V = (uint32_t)a.V;
@@ -501,7 +508,7 @@ __device__ __forceinline__ void mpfr_depth(const MpfrArgs& a, MShared& sm, float
     } else {
         // ---- stream the row: log-sum-exp, group maxima, row maximum
         __syncthreads();
-        mstream_row<BF16, VEC>(row, a.V, a.invT, gm,
+        mstream_row<BF16>(row, a.V, a.invT, gm,
                                a.draft_lse ? a.draft_lse + ((size_t)b * a.K + k) * a.gamma + s : nullptr, sm.red_m,
                                sm.red_s, sm.red_x, &sm.rowmax);
     }
@@ -538,7 +545,7 @@ __device__ __forceinline__ void mpfr_depth(const MpfrArgs& a, MShared& sm, float
             for (int i = 16 * t; i < min(n3, 16 * t + 16); ++i) mx = fmaxf(mx, sm.m3[i]);
             sm.m4[t] = mx;
         }
-        if (!a.row_seed) seed_tokens<BF16, VEC>(row, a.V, gm, sm.seed_g, sm.seed_tok);
+        if (!a.row_seed) seed_tokens<BF16>(row, a.V, gm, sm.seed_g, sm.seed_tok);
         __syncthreads();
         const uint32_t k0 = sm.kappa0, k1 = sm.kappa1;
         // seed arrivals in float32: E_j for every (seed, j < nu), the cumulative sums in
@@ -654,7 +661,7 @@ __device__ __forceinline__ void mpfr_depth(const MpfrArgs& a, MShared& sm, float
                             const MNode gn = sm.lg[gi];
                             const uint32_t chunk = gn.i * 16u + (uint32_t)(tid & 15);
                             float x[8];
-                            mload8<BF16, VEC>(row, a.V, (int)(chunk * 8u), x);
+                            mload8<BF16>(row, a.V, (int)(chunk * 8u), x);
                             eval_chunk<0>(sm, a, x, chunk, gn.m, gn.p, shift, k0, k1);
                         }
                     }
@@ -666,7 +673,7 @@ __device__ __forceinline__ void mpfr_depth(const MpfrArgs& a, MShared& sm, float
                     if (g < ng && kLnClockFloor - (gm[g] - shift) * a.invT <= sm.theta) {
                         const uint32_t chunk = (uint32_t)g * 16u + (uint32_t)(tid & 15);
                         float x[8];
-                        mload8<BF16, VEC>(row, a.V, (int)(chunk * 8u), x);
+                        mload8<BF16>(row, a.V, (int)(chunk * 8u), x);
                         eval_chunk<1>(sm, a, x, chunk, 0.f, 0u, shift, k0, k1);
                     }
                 }
@@ -868,20 +875,20 @@ __device__ __forceinline__ void mpfr_depth(const MpfrArgs& a, MShared& sm, float
 // earlier depths as they land; waits are only for workgroups of the same launch, so
 // the launcher uses this form only when all of them can be resident together.  The
 // last workgroup to leave resets the exit count and records the launch's epoch.
-template <bool BF16, bool VEC, int LAYOUT>
+template <bool BF16, int LAYOUT>
 __global__ __launch_bounds__(kMBlock, 3) void mpfr_draft_kernel(MpfrArgs a) {
     __shared__ MShared sm;
     extern __shared__ __align__(16) float gm[];  // the row's group maxima (dynamic: one per group)
     const int b = (int)blockIdx.x / a.K, k = (int)blockIdx.x % a.K;
     if (!a.tok_slot) {
-        mpfr_depth<BF16, VEC, LAYOUT>(a, sm, gm, b, k, a.s, 0u);
+        mpfr_depth<BF16, LAYOUT>(a, sm, gm, b, k, a.s, 0u);
         return;
     }
     if (threadIdx.x == 0) sm.epoch = next_epoch(a);
     __syncthreads();
     const uint32_t ep = sm.epoch;
     for (int s = a.s_begin; s < a.s_begin + a.s_count; ++s) {
-        mpfr_depth<BF16, VEC, LAYOUT>(a, sm, gm, b, k, s, ep);
+        mpfr_depth<BF16, LAYOUT>(a, sm, gm, b, k, s, ep);
         __syncthreads();
     }
     if (threadIdx.x == 0) record_epoch(a, ep);
@@ -902,13 +909,13 @@ namespace {
 // Dynamic LDS of a sampling launch: the row's group maxima.
 size_t mpfr_draft_smem(const MpfrArgs& a) { return (size_t)(((a.V + 127) / 128 + 3) & ~3) * sizeof(float); }
 
-template <bool BF16, bool VEC, int LAYOUT>
+template <bool BF16, int LAYOUT>
 hipError_t mpfr_fit(const MpfrArgs& a, bool* fits) {
     *fits = false;
     if (!a.row_gm || a.s_count < 2) return hipSuccess;
     int per_cu = 0, dev = 0, cus = 0;
     hipError_t e;
-    if ((e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, mpfr_draft_kernel<BF16, VEC, LAYOUT>, kMBlock,
+    if ((e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, mpfr_draft_kernel<BF16, LAYOUT>, kMBlock,
                                                           mpfr_draft_smem(a))) != hipSuccess)
         return e;
     if ((e = hipGetDevice(&dev)) != hipSuccess) return e;
@@ -919,9 +926,9 @@ hipError_t mpfr_fit(const MpfrArgs& a, bool* fits) {
 
 // tok_slot set (the caller checked mpfr_all_depths_fit): one launch for every depth;
 // otherwise one launch per depth.
-template <bool BF16, bool VEC, int LAYOUT>
+template <bool BF16, int LAYOUT>
 hipError_t mpfr_depths(MpfrArgs a, hipStream_t stream) {
-    auto fn = mpfr_draft_kernel<BF16, VEC, LAYOUT>;
+    auto fn = mpfr_draft_kernel<BF16, LAYOUT>;
     const dim3 grid((unsigned)(a.B * a.K)), block(kMBlock);
     const size_t smem = mpfr_draft_smem(a);
     hipError_t e;
@@ -939,34 +946,23 @@ hipError_t mpfr_depths(MpfrArgs a, hipStream_t stream) {
 
 }  // namespace
 
-hipError_t mpfr_all_depths_fit(const MpfrArgs& a, bool bf16, bool vec, int layout, bool* fits) {
-    if (bf16) {
-        if (vec) return layout == 0 ? mpfr_fit<true, true, 0>(a, fits) : mpfr_fit<true, true, 1>(a, fits);
-        return layout == 0 ? mpfr_fit<true, false, 0>(a, fits) : mpfr_fit<true, false, 1>(a, fits);
-    }
-    if (vec) return layout == 0 ? mpfr_fit<false, true, 0>(a, fits) : mpfr_fit<false, true, 1>(a, fits);
-    return layout == 0 ? mpfr_fit<false, false, 0>(a, fits) : mpfr_fit<false, false, 1>(a, fits);
+hipError_t mpfr_all_depths_fit(const MpfrArgs& a, bool bf16, int layout, bool* fits) {
+    if (bf16) return layout == 0 ? mpfr_fit<true, 0>(a, fits) : mpfr_fit<true, 1>(a, fits);
+    return layout == 0 ? mpfr_fit<false, 0>(a, fits) : mpfr_fit<false, 1>(a, fits);
 }
 
-hipError_t launch_mpfr_depths(MpfrArgs a, bool bf16, bool vec, int layout, hipStream_t stream) {
-    if (bf16) {
-        if (vec) return layout == 0 ? mpfr_depths<true, true, 0>(a, stream) : mpfr_depths<true, true, 1>(a, stream);
-        return layout == 0 ? mpfr_depths<true, false, 0>(a, stream) : mpfr_depths<true, false, 1>(a, stream);
-    }
-    if (vec) return layout == 0 ? mpfr_depths<false, true, 0>(a, stream) : mpfr_depths<false, true, 1>(a, stream);
-    return layout == 0 ? mpfr_depths<false, false, 0>(a, stream) : mpfr_depths<false, false, 1>(a, stream);
+hipError_t launch_mpfr_depths(MpfrArgs a, bool bf16, int layout, hipStream_t stream) {
+    if (bf16) return layout == 0 ? mpfr_depths<true, 0>(a, stream) : mpfr_depths<true, 1>(a, stream);
+    return layout == 0 ? mpfr_depths<false, 0>(a, stream) : mpfr_depths<false, 1>(a, stream);
 }
 
-hipError_t launch_mpfr_stream(const MpfrArgs& a, bool bf16, bool vec, hipStream_t stream) {
+hipError_t launch_mpfr_stream(const MpfrArgs& a, bool bf16, hipStream_t stream) {
     const int rows = a.B * a.K * a.s_count;
     const dim3 grid((unsigned)(a.stream_grid > 0 && a.stream_grid < rows ? a.stream_grid : rows)), block(kMBlock);
-    if (bf16) {
-        if (vec) hipLaunchKernelGGL((mpfr_stream_kernel<true, true>), grid, block, 0, stream, a);
-        else hipLaunchKernelGGL((mpfr_stream_kernel<true, false>), grid, block, 0, stream, a);
-    } else {
-        if (vec) hipLaunchKernelGGL((mpfr_stream_kernel<false, true>), grid, block, 0, stream, a);
-        else hipLaunchKernelGGL((mpfr_stream_kernel<false, false>), grid, block, 0, stream, a);
-    }
+    if (bf16)
+        hipLaunchKernelGGL(mpfr_stream_kernel<true>, grid, block, 0, stream, a);
+    else
+        hipLaunchKernelGGL(mpfr_stream_kernel<false>, grid, block, 0, stream, a);
     return hipGetLastError();
 }
 

@@ -222,78 +222,32 @@ __device__ __forceinline__ float load_logit(const unsigned char* row, int v) {
         return ((const float*)row)[v];
 }
 
-// 8 consecutive logits starting at `base` (-inf past V).
-template <bool BF16, bool VEC>
-__device__ __forceinline__ void load8(const unsigned char* row, int V, int base, float (&x)[8]) {
-    if constexpr (VEC) {
-        if constexpr (BF16) {
-            uint4 u = make_uint4(0xFF80FF80u, 0xFF80FF80u, 0xFF80FF80u, 0xFF80FF80u);
-            if (base < V) u = *(const uint4*)((const uint16_t*)row + base);
-            x[0] = bf16_lo(u.x); x[1] = bf16_hi(u.x); x[2] = bf16_lo(u.y); x[3] = bf16_hi(u.y);
-            x[4] = bf16_lo(u.z); x[5] = bf16_hi(u.z); x[6] = bf16_lo(u.w); x[7] = bf16_hi(u.w);
-        } else {
-            float4 f0 = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY), f1 = f0;
-            if (base < V) f0 = *(const float4*)((const float*)row + base);
-            if (base + 4 < V) f1 = *(const float4*)((const float*)row + base + 4);
-            x[0] = f0.x; x[1] = f0.y; x[2] = f0.z; x[3] = f0.w;
-            x[4] = f1.x; x[5] = f1.y; x[6] = f1.z; x[7] = f1.w;
-        }
-    } else {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) x[i] = (base + i < V) ? load_logit<BF16>(row, base + i) : -INFINITY;
-    }
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+// 16 bytes at any element boundary: rows of an odd vocabulary start off the 16-byte
+// grid.  gfx950 serves such a load with one instruction (global_load_dwordx4), at the
+// price of one more cache line per wave: a whole call at V = 50257, K = 3, gamma = 4,
+// B = 24, bf16 takes 105 us against 148 us with element-by-element loads of such rows.
+typedef uint32_t u32x4_f32 __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t u32x4_b16 __attribute__((ext_vector_type(4), aligned(2)));
+
+template <bool BF16, bool NT>
+__device__ __forceinline__ uint4 ld16(const void* p) {
+    u32x4 v;
+    if constexpr (BF16)
+        v = NT ? (u32x4)__builtin_nontemporal_load((const u32x4_b16*)p) : (u32x4)*(const u32x4_b16*)p;
+    else
+        v = NT ? (u32x4)__builtin_nontemporal_load((const u32x4_f32*)p) : (u32x4)*(const u32x4_f32*)p;
+    return make_uint4(v.x, v.y, v.z, v.w);
 }
 
-// Raw 16-byte words of one 8-token unit (bf16: one word, float32: two); -inf past V.
-template <bool BF16, bool VEC>
+// Raw 16-byte words of one 8-token unit (bf16: one word, float32: two).
+template <bool BF16>
 struct Unit {
     uint4 w[BF16 ? 1 : 2];
 };
 
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-
-template <bool NT>
-__device__ __forceinline__ uint4 ld16(const void* p) {
-    if constexpr (NT) {
-        const u32x4 v = __builtin_nontemporal_load((const u32x4*)p);
-        return make_uint4(v.x, v.y, v.z, v.w);
-    } else {
-        return *(const uint4*)p;
-    }
-}
-
-// Vector path: the address is clamped into the row (V * element size is a multiple
-// of 16 bytes there), so every load is unconditional and the compiler can wait for
-// them one by one; words past V are left for the caller to mask.  NT: streaming
-// (non-temporal) loads for the single pass over the logits; re-reads of a few
-// groups use ordinary loads.
-template <bool BF16, bool VEC, bool NT = true>
-__device__ __forceinline__ void load_unit(const unsigned char* row, int V, int base, Unit<BF16, VEC>& u) {
-    if constexpr (VEC) {
-        if constexpr (BF16) {
-            u.w[0] = ld16<NT>((const uint16_t*)row + min(base, V - 8));
-        } else {
-            u.w[0] = ld16<NT>((const float*)row + min(base, V - 4));
-            u.w[1] = ld16<NT>((const float*)row + min(base + 4, V - 4));
-        }
-    } else {
-        float x[8];
-        load8<BF16, false>(row, V, base, x);
-        if constexpr (BF16) {
-            uint32_t p[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                p[i] = (__float_as_uint(x[2 * i]) >> 16) | (__float_as_uint(x[2 * i + 1]) & 0xFFFF0000u);
-            u.w[0] = make_uint4(p[0], p[1], p[2], p[3]);
-        } else {
-            u.w[0] = make_uint4(__float_as_uint(x[0]), __float_as_uint(x[1]), __float_as_uint(x[2]), __float_as_uint(x[3]));
-            u.w[1] = make_uint4(__float_as_uint(x[4]), __float_as_uint(x[5]), __float_as_uint(x[6]), __float_as_uint(x[7]));
-        }
-    }
-}
-
-template <bool BF16, bool VEC>
-__device__ __forceinline__ void unpack_unit(const Unit<BF16, VEC>& u, float (&x)[8]) {
+template <bool BF16>
+__device__ __forceinline__ void unpack_unit(const Unit<BF16>& u, float (&x)[8]) {
     if constexpr (BF16) {
         x[0] = bf16_lo(u.w[0].x); x[1] = bf16_hi(u.w[0].x); x[2] = bf16_lo(u.w[0].y); x[3] = bf16_hi(u.w[0].y);
         x[4] = bf16_lo(u.w[0].z); x[5] = bf16_hi(u.w[0].z); x[6] = bf16_lo(u.w[0].w); x[7] = bf16_hi(u.w[0].w);
@@ -302,6 +256,47 @@ __device__ __forceinline__ void unpack_unit(const Unit<BF16, VEC>& u, float (&x)
         x[2] = __uint_as_float(u.w[0].z); x[3] = __uint_as_float(u.w[0].w);
         x[4] = __uint_as_float(u.w[1].x); x[5] = __uint_as_float(u.w[1].y);
         x[6] = __uint_as_float(u.w[1].z); x[7] = __uint_as_float(u.w[1].w);
+    }
+}
+
+// The words of 8 consecutive logits starting at `base` (-inf past V): vector loads
+// where all eight lie inside the row, else element by element.
+template <bool BF16>
+__device__ __forceinline__ void load_words(const unsigned char* row, int V, int base, Unit<BF16>& u) {
+    if (base + 8 <= V) {
+        u.w[0] = ld16<BF16, false>(row + (size_t)base * (BF16 ? 2 : 4));
+        if constexpr (!BF16) u.w[1] = ld16<BF16, false>(row + ((size_t)base + 4) * 4);
+        return;
+    }
+    uint32_t b[8];  // float bits
+#pragma unroll
+    for (int i = 0; i < 8; ++i) b[i] = __float_as_uint(base + i < V ? load_logit<BF16>(row, base + i) : -INFINITY);
+    if constexpr (BF16) {
+        u.w[0] = make_uint4((b[0] >> 16) | b[1], (b[2] >> 16) | b[3], (b[4] >> 16) | b[5], (b[6] >> 16) | b[7]);
+    } else {
+        u.w[0] = make_uint4(b[0], b[1], b[2], b[3]);
+        u.w[1] = make_uint4(b[4], b[5], b[6], b[7]);
+    }
+}
+
+template <bool BF16>
+__device__ __forceinline__ void load8(const unsigned char* row, int V, int base, float (&x)[8]) {
+    Unit<BF16> u;
+    load_words<BF16>(row, V, base, u);
+    unpack_unit<BF16>(u, x);
+}
+
+// The streaming pass's loads: the address is clamped into the row, so every load is
+// unconditional (non-temporal: the pass reads the logits once) and the compiler can
+// wait for them one by one.  A unit that reaches past the row holds other tokens'
+// words; its reader replaces them.  V >= 8.
+template <bool BF16>
+__device__ __forceinline__ void load_unit(const unsigned char* row, int V, int base, Unit<BF16>& u) {
+    if constexpr (BF16) {
+        u.w[0] = ld16<true, true>((const uint16_t*)row + min(base, V - 8));
+    } else {
+        u.w[0] = ld16<false, true>((const float*)row + min(base, V - 4));
+        u.w[1] = ld16<false, true>((const float*)row + min(base + 4, V - 4));
     }
 }
 
@@ -335,20 +330,23 @@ constexpr int units_per_segment() {
 }
 
 // Issue the loads of one segment (one 8-token unit per thread and unit).
-template <bool BF16, bool VEC>
+template <bool BF16>
 __device__ __forceinline__ void issue_segment(const RaceArgs& a, const Row& r, int seg,
-                                              Unit<BF16, VEC> (&u)[units_per_segment<BF16>()]) {
+                                              Unit<BF16> (&u)[units_per_segment<BF16>()]) {
     constexpr int NU = units_per_segment<BF16>();
     const int seg0 = seg * (BF16 ? kSegTokensBf16 : kSegTokensF32);
+    // a row of fewer than 8 tokens: read (and ignored) from the workspace's control words
+    const unsigned char* row = a.V < 8 ? a.ws : r.ptr;
+    const int n = max(a.V, 8);
 #pragma unroll
-    for (int q = 0; q < NU; ++q) load_unit<BF16, VEC>(r.ptr, a.V, seg0 + q * kBlock * 8 + 8 * threadIdx.x, u[q]);
+    for (int q = 0; q < NU; ++q) load_unit<BF16>(row, n, seg0 + q * kBlock * 8 + 8 * threadIdx.x, u[q]);
 }
 
 // Consume a loaded segment: per-wave LSE partials and the maximum of every
 // 128-token group, staged in LDS (parity p) for publish_segment.
-template <bool BF16, bool VEC>
+template <bool BF16>
 __device__ __forceinline__ void consume_segment(const RaceArgs& a, const Row& r, int seg, Shared& sm, int p,
-                                                const Unit<BF16, VEC> (&u)[units_per_segment<BF16>()]) {
+                                                const Unit<BF16> (&u)[units_per_segment<BF16>()]) {
     constexpr int NU = units_per_segment<BF16>();
     constexpr int UT = kBlock * 8;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -359,13 +357,16 @@ __device__ __forceinline__ void consume_segment(const RaceArgs& a, const Row& r,
 #pragma unroll
     for (int q = 0; q < NU; ++q) {
         float x[8];
-        unpack_unit<BF16, VEC>(u[q], x);
+        unpack_unit<BF16>(u[q], x);
         const int ub = seg0 + q * UT;
         if (ub + UT > V) {  // uniform: this unit reaches past the row
             const int base = ub + 8 * tid;
+            if (base < V && base + 8 > V) {
+                load8<BF16>(r.ptr, V, base, x);  // the row's last tokens (V not a multiple of 8)
+            } else if (base >= V) {
 #pragma unroll
-            for (int i = 0; i < 8; ++i)
-                if (base + i >= V) x[i] = -INFINITY;
+                for (int i = 0; i < 8; ++i) x[i] = -INFINITY;
+            }
         }
         const float um = fmaxf(fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])), fmaxf(fmaxf(x[4], x[5]), fmaxf(x[6], x[7])));
         const float g = row16_max(um);
@@ -529,16 +530,16 @@ __device__ __forceinline__ void list_near(Shared& sm, const RaceArgs& a, uint32_
 // calls).  Halves beyond the list's capacity are done by their chunk's lane.
 // Raw logits of this lane's chunk of the entries of the pass starting at `first`
 // (list end `end`; nothing is loaded past it).  Words past V are never used.
-template <bool BF16, bool VEC>
+template <bool BF16>
 __device__ __forceinline__ void load_pass(const RaceArgs& a, const Row& r, const Shared& sm, int first, int end,
-                                          Unit<BF16, VEC> (&ux)[kRowEntries]) {
+                                          Unit<BF16> (&ux)[kRowEntries]) {
     const int c = threadIdx.x & 15, row = threadIdx.x >> 4;
 #pragma unroll
     for (int q = 0; q < kRowEntries; ++q) {
         const int e = first + row * kRowEntries + q;
         if (e < end) {
             const uint32_t g = sm.l2[e].id & 0xFFFFFu;
-            load_unit<BF16, VEC, false>(r.ptr, a.V, (int)(g * kGroupTokens + (uint32_t)c * 8u), ux[q]);
+            load_words<BF16>(r.ptr, a.V, (int)(g * kGroupTokens + (uint32_t)c * 8u), ux[q]);
         }
     }
 }
@@ -551,10 +552,10 @@ struct HalfOut {
     bool valid;
 };
 
-template <bool BF16, bool VEC, int LAYOUT>
+template <bool BF16, int LAYOUT>
 __device__ __forceinline__ void eval_groups(const RaceArgs& a, const Row& r, Shared& sm, const float* gm, int first,
                                             int n, int end, int par, uint32_t k0, uint32_t k1, HalfOut& ho,
-                                            uint32_t& ovf, Unit<BF16, VEC> (&ux)[kRowEntries]) {
+                                            uint32_t& ovf, Unit<BF16> (&ux)[kRowEntries]) {
     const int tid = threadIdx.x, lane = tid & 63;
     const int c = tid & 15;
     const int row = tid >> 4;  // 16 rows of 16 lanes
@@ -569,7 +570,7 @@ __device__ __forceinline__ void eval_groups(const RaceArgs& a, const Row& r, Sha
         const int e = first + row * kRowEntries + q;
         act[q] = e < first + n;
         nd[q] = act[q] ? sm.l2[e] : Node{0u, 0.f, 0u};
-        unpack_unit<BF16, VEC>(ux[q], x[q]);
+        unpack_unit<BF16>(ux[q], x[q]);
     }
     // What each chunk needs: its own draw (unless it holds the group minimum) and
     // the words of each half with a token that can still win.
@@ -636,7 +637,7 @@ __device__ __forceinline__ void eval_groups(const RaceArgs& a, const Row& r, Sha
         }
     }
     // the next pass's logits, in flight while this pass draws and scores
-    load_pass<BF16, VEC>(a, r, sm, first + kPassGroups, end, ux);
+    load_pass<BF16>(a, r, sm, first + kPassGroups, end, ux);
     __syncthreads();
     // the other parity's counts were read in the previous pass: clear them for the next
     if (tid == 0) sm.n_ev[par ^ 1] = 0u;
@@ -797,15 +798,15 @@ __device__ __forceinline__ int order_groups(const Row& r, Shared& sm, const floa
 
 // Evaluate and empty the group list.  Callers read the list count after a barrier
 // and before any push of the current pass.
-template <bool BF16, bool VEC, int LAYOUT>
+template <bool BF16, int LAYOUT>
 __device__ __forceinline__ void flush_groups(const RaceArgs& a, const Row& r, Shared& sm, const float* gm, uint32_t k0,
                                              uint32_t k1) {
     int n = min(sm.n_l2, kL2Cap);
     const bool ordered = n > kPassGroups;
     if (ordered) n = order_groups<LAYOUT>(r, sm, gm, n);
     int par = 0;
-    Unit<BF16, VEC> ux[kRowEntries];
-    load_pass<BF16, VEC>(a, r, sm, 0, n, ux);
+    Unit<BF16> ux[kRowEntries];
+    load_pass<BF16>(a, r, sm, 0, n, ux);
     for (int first = 0; first < n; first += kPassGroups, par ^= 1) {
         // every later entry's bound is at least its bucket's smallest (the threshold
         // and the buckets are read after the previous pass's last barrier)
@@ -813,7 +814,7 @@ __device__ __forceinline__ void flush_groups(const RaceArgs& a, const Row& r, Sh
             break;
         HalfOut ho;
         uint32_t ovf;
-        eval_groups<BF16, VEC, LAYOUT>(a, r, sm, gm, first, min(n - first, kPassGroups), n, par, k0, k1, ho, ovf, ux);
+        eval_groups<BF16, LAYOUT>(a, r, sm, gm, first, min(n - first, kPassGroups), n, par, k0, k1, ho, ovf, ux);
         __syncthreads();
         // every half of the pass has lowered the best: list the near-ties
         if (ho.valid) list_near(sm, a, ho.base4, ho.slot, ho.sc, sm.half[threadIdx.x].x);
@@ -835,7 +836,7 @@ __device__ __forceinline__ void flush_groups(const RaceArgs& a, const Row& r, Sh
 // list, so that the draws run on full wavefronts.  One loop with a single
 // evaluation call site: it refills the work list when it is used up, evaluates the
 // group list when it may overflow or at the end, and draws kBlock items per step.
-template <bool BF16, bool VEC>
+template <bool BF16>
 __device__ __forceinline__ void flush_l3(const RaceArgs& a, const Row& r, Shared& sm, const float* gm, uint32_t k0, uint32_t k1) {
     const int tid = threadIdx.x;
     const int n = min(sm.n_l3, kL3Cap) * 16;
@@ -863,7 +864,7 @@ __device__ __forceinline__ void flush_l3(const RaceArgs& a, const Row& r, Shared
         // The count is read by every thread before any thread of this step pushes.
         const bool flush = done ? sm.n_l2 > 0 : sm.n_l2 > kL2Cap - kBlock;
         __syncthreads();
-        if (flush) flush_groups<BF16, VEC, 0>(a, r, sm, gm, k0, k1);
+        if (flush) flush_groups<BF16, 0>(a, r, sm, gm, k0, k1);
         if (done) break;
         const int i = wb + tid;
         if (i < nw) {
@@ -910,7 +911,7 @@ __device__ __forceinline__ uint32_t pick_word(uint32_t a0, uint32_t a1, uint32_t
     return i == 0 ? a0 : i == 1 ? a1 : i == 2 ? a2 : a3;
 }
 
-template <bool BF16, bool VEC, int LAYOUT>
+template <bool BF16, int LAYOUT>
 __device__ __forceinline__ void race(const RaceArgs& a, const Row& r, Shared& sm, const float* gm, uint32_t k0, uint32_t k1) {
     // (lists, candidates and the best score were reset by the caller)
     const int tid = threadIdx.x;
@@ -1020,7 +1021,7 @@ __device__ __forceinline__ void race(const RaceArgs& a, const Row& r, Shared& sm
             const bool done = base >= nB;  // one call site of flush_l3 (see flush_l3)
             const bool flush = done || sm.n_l3 > kL3Cap - kBlock;
             __syncthreads();
-            if (flush) flush_l3<BF16, VEC>(a, r, sm, gm, k0, k1);
+            if (flush) flush_l3<BF16>(a, r, sm, gm, k0, k1);
             if (done) break;
             const int e = base + tid;
             if (e < nB) {
@@ -1046,7 +1047,7 @@ __device__ __forceinline__ void race(const RaceArgs& a, const Row& r, Shared& sm
             const bool done = base >= tot;  // one call site of flush_groups
             const bool flush = done || sm.n_l2 > kL2Cap - kBlock;
             __syncthreads();
-            if (flush) flush_groups<BF16, VEC, 1>(a, r, sm, gm, k0, k1);
+            if (flush) flush_groups<BF16, 1>(a, r, sm, gm, k0, k1);
             if (done) break;
             const int e = base + tid;
             if (e < tot) {
@@ -1237,7 +1238,7 @@ __device__ __forceinline__ bool key_consumer(const RaceArgs& a, const Row& r) {
     return r.s + 1 < a.s_begin + a.s_count || (a.target_rows > 1 && r.s + 1 <= a.gamma);
 }
 
-template <bool BF16, bool VEC, int LAYOUT>
+template <bool BF16, int LAYOUT>
 __device__ __forceinline__ void finish_row(const RaceArgs& a, const Row& r, Shared& sm, float* gm) {
     // The race is a latency chain (the next depth of this path waits for it) while
     // the other waves on the same SIMDs stream: raise this wave's issue priority,
@@ -1355,7 +1356,7 @@ __device__ __forceinline__ void finish_row(const RaceArgs& a, const Row& r, Shar
         if (g >= 0) {
             float x[8];
             const int base = g * kGroupTokens + sub * 8;
-            load8<BF16, VEC>(r.ptr, a.V, base, x);
+            load8<BF16>(r.ptr, a.V, base, x);
             const float gmax = gm[g];
 #pragma unroll
             for (int t = 7; t >= 0; --t)
@@ -1450,7 +1451,7 @@ __device__ __forceinline__ void finish_row(const RaceArgs& a, const Row& r, Shar
     } else {
         Row rs = r;
         rs.shift = sm.rowmax;
-        race<BF16, VEC, LAYOUT>(a, rs, sm, gm, k0, k1);
+        race<BF16, LAYOUT>(a, rs, sm, gm, k0, k1);
     }
     if (tid == 0) {
         const int y = sm.win_token;
@@ -1541,7 +1542,7 @@ __device__ __forceinline__ void decode_item(const RaceArgs& a, const Shared& sm,
 // both): streaming never waits, and a finishing workgroup waits only for segments
 // (streamed without waiting) and for races of rows earlier in the order (taken
 // earlier by running finishing workgroups), so every wait ends.
-template <bool BF16, bool VEC, int LAYOUT>
+template <bool BF16, int LAYOUT>
 __global__ __launch_bounds__(kBlock, 4) void race_kernel(RaceArgs a) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     Shared& sm = *reinterpret_cast<Shared*>(smem_raw);
@@ -1580,9 +1581,9 @@ __global__ __launch_bounds__(kBlock, 4) void race_kernel(RaceArgs a) {
                 Row rs;
                 int ss;
                 decode_item<BF16>(a, sm, item, rs, ss);
-                Unit<BF16, VEC> u[units_per_segment<BF16>()];
-                issue_segment<BF16, VEC>(a, rs, ss, u);
-                consume_segment<BF16, VEC>(a, rs, ss, sm, p, u);
+                Unit<BF16> u[units_per_segment<BF16>()];
+                issue_segment<BF16>(a, rs, ss, u);
+                consume_segment<BF16>(a, rs, ss, sm, p, u);
                 __syncthreads();
                 publish_segment<BF16>(a, rs.row_id, ss, sm, p);
                 if (item >= last) break;
@@ -1592,7 +1593,7 @@ __global__ __launch_bounds__(kBlock, 4) void race_kernel(RaceArgs a) {
             Row r;
             int seg;
             decode_item<BF16>(a, sm, R * a.L.nseg + a.L.nseg - 1, r, seg);
-            finish_row<BF16, VEC, LAYOUT>(a, r, sm, gm);
+            finish_row<BF16, LAYOUT>(a, r, sm, gm);
             if (tid == 0) sm.tick[0] = take_row(a, q, nq);
             __syncthreads();
             R = sm.tick[0];
@@ -1600,22 +1601,22 @@ __global__ __launch_bounds__(kBlock, 4) void race_kernel(RaceArgs a) {
     } else {
         // Software-pipelined: the next segment's loads are issued before the current
         // one is published.
-        Unit<BF16, VEC> u[units_per_segment<BF16>()];
+        Unit<BF16> u[units_per_segment<BF16>()];
         int item = sm.tick[0], seg = 0;
         Row r;
         if (item < a.n_items) {
             decode_item<BF16>(a, sm, item, r, seg);
-            issue_segment<BF16, VEC>(a, r, seg, u);
+            issue_segment<BF16>(a, r, seg, u);
         }
         for (int parity = 0; item < a.n_items; parity ^= 1) {
             if (tid == 0) sm.tick[parity ^ 1] = take_item(a, q, nq);
-            consume_segment<BF16, VEC>(a, r, seg, sm, parity, u);
+            consume_segment<BF16>(a, r, seg, sm, parity, u);
             __syncthreads();
             const int pub_row = r.row_id, pub_seg = seg;
             item = sm.tick[parity ^ 1];
             if (item < a.n_items) {
                 decode_item<BF16>(a, sm, item, r, seg);
-                issue_segment<BF16, VEC>(a, r, seg, u);
+                issue_segment<BF16>(a, r, seg, u);
             }
             publish_segment<BF16>(a, pub_row, pub_seg, sm, parity);
         }
@@ -1649,10 +1650,10 @@ size_t shared_bytes(int ng, int K) {
            (size_t)K * (size_t)((ng + 255) / 256) * sizeof(Node);
 }
 
-template <bool BF16, bool VEC, int LAYOUT>
+template <bool BF16, int LAYOUT>
 hipError_t launch_one(const RaceArgs& a, hipStream_t stream) {
     const size_t smem = shared_bytes(a.L.ng, a.K);
-    auto fn = race_kernel<BF16, VEC, LAYOUT>;
+    auto fn = race_kernel<BF16, LAYOUT>;
     int per_cu = 0;
     hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, kBlock, smem);
     if (e != hipSuccess) return e;
@@ -1670,15 +1671,10 @@ hipError_t launch_one(const RaceArgs& a, hipStream_t stream) {
 
 }  // namespace
 
-hipError_t launch_race(const RaceArgs& a, bool bf16, bool vec, int layout, hipStream_t stream) {
-    if (bf16) {
-        if (vec) return layout == 0 ? launch_one<true, true, 0>(a, stream) : launch_one<true, true, 1>(a, stream);
-        return layout == 0 ? launch_one<true, false, 0>(a, stream) : launch_one<true, false, 1>(a, stream);
-    }
-    if (vec) return layout == 0 ? launch_one<false, true, 0>(a, stream) : launch_one<false, true, 1>(a, stream);
-    return layout == 0 ? launch_one<false, false, 0>(a, stream) : launch_one<false, false, 1>(a, stream);
+hipError_t launch_race(const RaceArgs& a, bool bf16, int layout, hipStream_t stream) {
+    if (bf16) return layout == 0 ? launch_one<true, 0>(a, stream) : launch_one<true, 1>(a, stream);
+    return layout == 0 ? launch_one<false, 0>(a, stream) : launch_one<false, 1>(a, stream);
 }
-
 
 // ---------------------------------------------------------------- static scratch
 

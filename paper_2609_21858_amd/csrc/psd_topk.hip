@@ -40,6 +40,9 @@ namespace {
 constexpr int kTBlock = 256;
 constexpr int kUnroll = 4;  // 16-byte loads in flight per thread
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+// 16 bytes at any element boundary in one load (rows of an odd vocabulary start off
+// the 16-byte grid).
+typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(2)));
 
 // ---------------------------------------------------------------- keys
 
@@ -206,15 +209,14 @@ __device__ __forceinline__ void stream_group_max(SelShared& sm, const unsigned c
     constexpr int EPT = BF16 ? 8 : 4, WCH = 64 * EPT, STEP = kWaves * kUnroll, LPG = kGroupTokens / EPT;
     constexpr size_t ES = BF16 ? 2 : 4;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const bool vec = ((uintptr_t)row & 15u) == 0;
     const int nch = (V + WCH - 1) / WCH, ng = (V + kGroupTokens - 1) / kGroupTokens;
     for (int c0 = w; c0 < nch; c0 += STEP) {
         uint32_t wv[kUnroll][4];
 #pragma unroll
         for (int u = 0; u < kUnroll; ++u) {
             const int base = (c0 + u * kWaves) * WCH + lane * EPT;
-            if (vec && base + EPT <= V) {
-                const u32x4 q = __builtin_nontemporal_load((const u32x4*)(row + (size_t)base * ES));
+            if (base + EPT <= V) {
+                const u32x4 q = __builtin_nontemporal_load((const u32x4_any*)(row + (size_t)base * ES));
                 wv[u][0] = q.x;
                 wv[u][1] = q.y;
                 wv[u][2] = q.z;
@@ -320,7 +322,6 @@ __device__ __forceinline__ bool select_candidates(SelShared& sm, const unsigned 
     // wave w reads groups w*GPW .. of every step of kWaves*GPW list entries
     uint32_t* bk = sm.u.wb.key[w];
     int32_t* bi = sm.u.wb.idx[w];
-    const bool vec = ((uintptr_t)row & 15u) == 0;
     int cnt = 0;
     bool over = false;
     for (int e0 = w * GPW; e0 < n_cg; e0 += kWaves * GPW * kUnroll) {
@@ -334,8 +335,8 @@ __device__ __forceinline__ bool select_candidates(SelShared& sm, const unsigned 
             for (int i = 0; i < 4; ++i) wv[u][i] = BF16 ? 0xFF80FF80u : 0xFF800000u;  // -inf
             if (e < n_cg && e < e0 + u * kWaves * GPW + GPW) {
                 base[u] = sm.cgl[e] * kGroupTokens + (lane % LPG) * EPT;
-                if (vec && base[u] + EPT <= V) {
-                    const uint4 q = *(const uint4*)(row + (size_t)base[u] * ES);
+                if (base[u] + EPT <= V) {
+                    const u32x4 q = *(const u32x4_any*)(row + (size_t)base[u] * ES);
                     wv[u][0] = q.x;
                     wv[u][1] = q.y;
                     wv[u][2] = q.z;
