@@ -16,7 +16,7 @@
 // (waiting only for the newest context token), runs the keyed race, publishes the
 // winner and -- for the last row of a sequence -- walks the block.
 //
-// The race (TREE clocks): the argmax tokens of four top groups give achievable
+// The race (TREE clocks): the largest tokens of the row's eighths give achievable
 // scores; a level-by-level descent then expands only nodes whose lower bound
 // ln(min clock of the node) - max logit / T can still beat the best score; a
 // child's minimum is never below its parent's, so the parent's minimum bounds a
@@ -47,16 +47,18 @@ namespace psd {
 
 namespace {
 
-constexpr int kInit = 8;                   // seed tokens of a race (segment top tokens)
+constexpr int kInit = 8;                   // seed tokens of a race (largest token of each eighth of the row)
 constexpr int kL3Cap = 512;
 constexpr int kL2Cap = 512;
 constexpr int kRowEntries = 2;             // group entries per 16-lane row and evaluation pass
 constexpr int kCandCap = 256;
-constexpr int kWorkCap = 2048;             // (level-3 node, group) items per prefilter round
-constexpr int kRolePeriod = 11;            // workgroup roles: of every kRolePeriod blocks,
-constexpr int kRoleFinish = 4;             // kRoleFinish finish rows and the others stream
+constexpr int kWorkCap = 2048;             // compacted (level-3 node, group) items
+constexpr int kRolePeriod = 9;             // workgroup roles: of every kRolePeriod blocks,
+constexpr int kRoleFinish = 3;             // kRoleFinish finish rows and the others stream
 constexpr int kHalfCap = 256;              // 4-token halves listed by one evaluation pass
 constexpr int kPassGroups = 16 * kRowEntries;  // group entries of one evaluation pass
+constexpr int kEvalGroups = 128;           // group entries of one evaluation pass (tree clocks; 64: 100 vs 96 us at
+                                           // V = 32000, K = 4, 1383 vs 1395 at V = 151936, K = 8)
 constexpr int kBuckets = 32;               // bound buckets of the group list's evaluation order
 constexpr float kMargin = 1e-3f;           // float32 pruning / candidate margin (score units)
 constexpr float kCutSlack = 1e-3f;         // slack of the per-token logit cut (score units)
@@ -82,9 +84,9 @@ struct Shared {
     float m4[16];
     int init_v[kInit];     // seed groups of the race (-1: none)
     int seed_tok[kInit];   // seed tokens of the race (-1: none)
-    int stop[64];          // top group of every segment (-1: none)
     float part[64];        // LSE partial sum of every segment
     Node l3[kL3Cap];
+    uint16_t l3_mask[kL3Cap];  // groups of a listed level-3 node that can still win (bit i: its i-th)
     Node l2[kL2Cap];
     int cand_v[kCandCap];
     int cand_j[kCandCap];
@@ -95,7 +97,8 @@ struct Shared {
     int red_j[kBlock / 64];
     float red_a[2][kBlock / 64];  // per-wave LSE partials of the streamed segment (by parity)
     float red_b[2][kBlock / 64];
-    int n_l4, n_l3, n_l2, n_cand;
+    int n_l2, n_cand;
+    uint32_t n_l3;         // listed level-3 nodes | their set group bits << 16
     int best_key;
     int tick[4];
     int ph_first[kMaxPhases], ph_depth[kMaxPhases], ph_nd[kMaxPhases];  // work-order phases
@@ -105,11 +108,16 @@ struct Shared {
     float rowmax;
     uint32_t kappa0, kappa1;
     uint32_t next0, next1;  // partial context key of the path's next depth
+    int newest;             // winner of the race one depth up the path (it came with the key)
+    // where the race's winner goes, ready before the race: the next depth's key words
+    // (null: no race of the call reads them), the row's token slot, the caller's outputs
+    uint64_t* pub_key;
+    uint64_t* pub_tok;
+    int32_t* pub_out;
     int win[32];            // context tokens (own window, next depth's window)
     int key_min, key_max;   // (token, slot) range of the candidates near the best
     uint32_t err_local;       // error bits this workgroup recorded (it then publishes them with a release)
     uint16_t work[kWorkCap];  // compacted work items (level-3 list index * 16 + group)
-    int n_work;
     uint32_t n_ev[2];                 // listed halves, per pass parity
     Half half[kHalfCap];
     // evaluation order of the group list (order_groups)
@@ -120,11 +128,11 @@ struct Shared {
 };
 static_assert(sizeof(Half) * kHalfCap >= sizeof(Node) * kL2Cap, "the reordering stages the group list in half[]");
 
-// Dynamic LDS after Shared: the group maxima gm (ng floats, rounded up to 4), then
-// the level-4 node list of a race (K slots x level-4 nodes; sized at launch).
-__device__ __forceinline__ Node* level4_list(const float* gm, int ng) {
-    return (Node*)(gm + ((ng + 3) & ~3));
-}
+// Dynamic LDS after Shared: the group maxima gm (ng floats, padded with -inf to whole
+// level-3 nodes), then the level-4 node list of a race (K slots x level-4 nodes; sized
+// at launch).
+__host__ __device__ constexpr int padded_groups(int ng) { return (ng + 15) & ~15; }
+__device__ __forceinline__ Node* level4_list(const float* gm, int ng) { return (Node*)(gm + padded_groups(ng)); }
 
 struct Row {
     int kind;  // 0 draft, 1 target
@@ -180,6 +188,28 @@ __device__ __forceinline__ uint64_t wait_slot(const RaceArgs& a, const uint64_t*
         v = ld_dev(p);
     }
     return v;
+}
+
+// Bounded wait of a wave for what the race of row `prod` publishes, one word per lane in
+// one load: the two words of the next depth's key (lanes 0 and 1) and, when asked, its
+// winner (lane 2).  (Polls served by the XCD's own L2, with a path's rows handed out to
+// one XCD, measured the same.)  Returns the lane's word.
+__device__ __forceinline__ uint32_t wait_key(const RaceArgs& a, int prod, uint32_t epoch, bool winner) {
+    const int lane = threadIdx.x & 63;
+    const int n = winner ? 3 : 2;
+    const uint64_t* p = lane < 2 ? (const uint64_t*)(a.ws + a.L.keys) + 2 * (size_t)prod + lane
+                                 : (const uint64_t*)(a.ws + a.L.tok) + prod;
+    uint64_t w = 0;
+    for (uint32_t i = 0;; ++i) {
+        if (lane < n) w = ld_dev(p);
+        if (__ballot(lane < n && (uint32_t)(w >> 32) != epoch) == 0u) break;
+        if (i >= a.spin_limit) {
+            if (lane == 0) set_error(a, kErrSpin);
+            break;
+        }
+        __builtin_amdgcn_s_sleep(2);
+    }
+    return (uint32_t)w;
 }
 
 __device__ __forceinline__ int target_row_id(const RaceArgs& a, int b, int k, int s) {
@@ -387,12 +417,11 @@ __device__ __forceinline__ void consume_segment(const RaceArgs& a, const Row& r,
 }
 
 // Publish a consumed segment (after a barrier): one 64-bit slot per group and per
-// 2048-token block, written by consecutive lanes, the segment's top group and its
-// LSE partial.
+// 2048-token block, written by consecutive lanes, and the segment's LSE partial.
 template <bool BF16>
 __device__ __forceinline__ void publish_segment(const RaceArgs& a, int row_id, int seg, Shared& sm, int p) {
     constexpr int NU = units_per_segment<BF16>();
-    const int tid = threadIdx.x, lane = tid & 63;
+    const int tid = threadIdx.x;
     const int seg0 = seg * (BF16 ? kSegTokensBf16 : kSegTokensF32);
     const uint64_t ep = (uint64_t)sm.epoch << 32;
     const int g0 = seg0 >> 7;
@@ -406,28 +435,6 @@ __device__ __forceinline__ void publish_segment(const RaceArgs& a, int row_id, i
         for (int i = 1; i < 16; ++i) mx = fmaxf(mx, sm.gst[p][16 * q + i]);
         uint64_t* m3slot = (uint64_t*)(a.ws + a.L.m3) + (size_t)row_id * a.L.n3;
         st_dev(m3slot + (seg0 >> 11) + q, ep | __float_as_uint(mx));
-    }
-    if (tid < 64) {
-        // the segment's top group: its largest group, lowest index on ties
-        float bv = lane < NU * 16 ? sm.gst[p][lane] : -INFINITY;
-        int bi = lane;
-        if (lane + 64 < NU * 16 && sm.gst[p][lane + 64] > bv) {
-            bv = sm.gst[p][lane + 64];
-            bi = lane + 64;
-        }
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-            const float ov = __shfl_xor(bv, off);
-            const int oi = __shfl_xor(bi, off);
-            if (ov > bv || (ov == bv && oi < bi)) {
-                bv = ov;
-                bi = oi;
-            }
-        }
-        if (lane == 0) {
-            uint64_t* stop = (uint64_t*)(a.ws + a.L.stop) + (size_t)row_id * a.L.nseg;
-            st_dev(stop + seg, ep | (uint32_t)(bv == -INFINITY ? -1 : g0 + bi));
-        }
     }
     if (tid == 0) {
         float m = sm.red_a[p][0], s = sm.red_b[p][0];
@@ -519,15 +526,14 @@ __device__ __forceinline__ void list_near(Shared& sm, const RaceArgs& a, uint32_
         if (sc[t] <= thr) push_candidate(sm, a, (int)(base4 + (uint32_t)t), (int)slot, sc[t], x[t]);
 }
 
+// ---- flat clocks: evaluation of the listed groups.
+//
 // Evaluate listed group entries [first, first + n): 16 lanes hold the 16 chunks of
 // one entry (8 tokens each); each row takes kRowEntries entries, whose loads are
-// issued together.  Only a few chunks of a surviving group hold a token that can
-// still win against the group minimum (chunk and token minima are never below
-// it), so the work is listed rather than done by each chunk's lane (a wave runs
-// every branch any of its lanes takes): the 4-token halves that need token words
-// go to an LDS list and are scored one per thread, each drawing its chunk's
-// minimum too when the chunk does not hold the group's (two independent Philox
-// calls).  Halves beyond the list's capacity are done by their chunk's lane.
+// issued together.  The 4-token halves with a token that can still win against the
+// clock floor go to an LDS list and are scored one per thread (a wave runs every
+// branch any of its lanes takes, so the work is listed rather than done by each
+// chunk's lane).  Halves beyond the list's capacity are done by their chunk's lane.
 // Raw logits of this lane's chunk of the entries of the pass starting at `first`
 // (list end `end`; nothing is loaded past it).  Words past V are never used.
 template <bool BF16>
@@ -552,7 +558,7 @@ struct HalfOut {
     bool valid;
 };
 
-template <bool BF16, int LAYOUT>
+template <bool BF16>
 __device__ __forceinline__ void eval_groups(const RaceArgs& a, const Row& r, Shared& sm, const float* gm, int first,
                                             int n, int end, int par, uint32_t k0, uint32_t k1, HalfOut& ho,
                                             uint32_t& ovf, Unit<BF16> (&ux)[kRowEntries]) {
@@ -560,7 +566,6 @@ __device__ __forceinline__ void eval_groups(const RaceArgs& a, const Row& r, Sha
     const int c = tid & 15;
     const int row = tid >> 4;  // 16 rows of 16 lanes
     const uint32_t V = (uint32_t)a.V;
-    constexpr uint32_t kDomain = LAYOUT == 0 ? kDomainTree : kDomainFlat;
     // this pass's logits were loaded into ux by the caller or the previous pass
     float x[kRowEntries][8];
     Node nd[kRowEntries];
@@ -572,19 +577,16 @@ __device__ __forceinline__ void eval_groups(const RaceArgs& a, const Row& r, Sha
         nd[q] = act[q] ? sm.l2[e] : Node{0u, 0.f, 0u};
         unpack_unit<BF16>(ux[q], x[q]);
     }
-    // What each chunk needs: its own draw (unless it holds the group minimum) and
-    // the words of each half with a token that can still win.
+    // What each chunk needs: the words of each half with a token that can still win.
     const float thr0 = current_threshold(sm);
     uint32_t hm[kRowEntries][2];
-    bool cj[kRowEntries];
     int nh = 0;
 #pragma unroll
     for (int q = 0; q < kRowEntries; ++q) {
         const uint32_t g = nd[q].id & 0xFFFFFu;
         const uint32_t base = g * kGroupTokens + (uint32_t)c * 8u;
-        const float lnm = LAYOUT == 0 ? ln_f32(nd[q].m) : kLnClockFloor;
+        const float lnm = kLnClockFloor;
         hm[q][0] = hm[q][1] = 0u;
-        cj[q] = false;
         if (act[q] && lnm - scaled(r, gm[g]) <= thr0) {
             // a token can reach thr0 only if lnm - (x - shift) / T <= thr0, i.e.
             // x - shift >= (lnm - thr0) T; the cut is lowered by kCutSlack, far more
@@ -598,10 +600,6 @@ __device__ __forceinline__ void eval_groups(const RaceArgs& a, const Row& r, Sha
             if (nv < 8) m8 &= nv > 0 ? (1u << nv) - 1u : 0u;
             hm[q][0] = m8 & 15u;
             hm[q][1] = m8 >> 4;
-            if (LAYOUT == 0 && m8) {
-                const uint32_t ce = node_end(kShift1, g * 16u + (uint32_t)c, V);
-                cj[q] = !(nd[q].p >= base && nd[q].p < ce);
-            }
         }
         nh += (int)(hm[q][0] != 0u) + (int)(hm[q][1] != 0u);
     }
@@ -617,14 +615,12 @@ __device__ __forceinline__ void eval_groups(const RaceArgs& a, const Row& r, Sha
 #pragma unroll
     for (int q = 0; q < kRowEntries; ++q) {
         const int le = row * kRowEntries + q;
-        const int cref = cj[q] ? 0 : -1;
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             if (hm[q][h]) {
                 if (jh < kHalfCap) {
                     Half& hf = sm.half[jh];
                     hf.desc = ((uint32_t)le << 9) | ((uint32_t)c << 5) | ((uint32_t)h << 4) | hm[q][h];
-                    hf.cref = cref;
                     hf.x[0] = x[q][4 * h];
                     hf.x[1] = x[q][4 * h + 1];
                     hf.x[2] = x[q][4 * h + 2];
@@ -658,19 +654,8 @@ __device__ __forceinline__ void eval_groups(const RaceArgs& a, const Row& r, Sha
             const uint32_t g = pn.id & 0xFFFFFu;
             const uint32_t chunk = g * 16u + ((hf.desc >> 5) & 15u), h = (hf.desc >> 4) & 1u;
             ho.base4 = chunk * 8u + 4u * h;
-            float mc = pn.m;
-            uint32_t pc = pn.p;
-            if (LAYOUT == 0 && hf.cref >= 0) {
-                // the chunk's own minimum (its draw is independent of the half's words,
-                // so the two Philox calls overlap)
-                const uint32_t ce = node_end(kShift1, chunk, V);
-                const Words wc = philox(chunk, ho.slot, 1u, kDomainTree, k0, k1);
-                mc = pn.m + div_n(exp1_f32(wc.w0), ce - chunk * 8u);
-                pc = chunk * 8u + uniform_position(wc.w1, wc.w2, ce - chunk * 8u);
-            }
-            const Words w = LAYOUT == 0 ? philox(chunk, ho.slot, 8u + h, kDomainTree, k0, k1)
-                                        : philox(ho.base4 >> 2, ho.slot, 0u, kDomainFlat, k0, k1);
-            half_scores<LAYOUT>(r, ho.base4, hf.desc & 15u, hf.x, mc, pc, w, thr, ho.sc);
+            const Words w = philox(ho.base4 >> 2, ho.slot, 0u, kDomainFlat, k0, k1);
+            half_scores<1>(r, ho.base4, hf.desc & 15u, hf.x, 0.f, 0u, w, thr, ho.sc);
             offer_best(sm, ho.sc);
         }
     }
@@ -679,7 +664,7 @@ __device__ __forceinline__ void eval_groups(const RaceArgs& a, const Row& r, Sha
 // Halves an evaluation pass could not list (more than kHalfCap): each is scored by
 // its chunk's lane (logits read again), one (entry, half) combination at a time,
 // with the same offer / barrier / list steps.  Called by every thread.
-template <bool BF16, int LAYOUT>
+template <bool BF16>
 __device__ __forceinline__ void eval_overflow(const RaceArgs& a, const Row& r, Shared& sm, int first, uint32_t ovf,
                                               uint32_t k0, uint32_t k1) {
     const int tid = threadIdx.x, c = tid & 15, row = tid >> 4;
@@ -698,20 +683,11 @@ __device__ __forceinline__ void eval_overflow(const RaceArgs& a, const Row& r, S
                 const uint32_t g = pn.id & 0xFFFFFu;
                 const uint32_t chunk = g * 16u + (uint32_t)c;
                 base4 = chunk * 8u + 4u * (uint32_t)h;
-                float mc = pn.m;
-                uint32_t pc = pn.p;
-                const uint32_t ce = node_end(kShift1, chunk, V);
-                if (LAYOUT == 0 && !(pn.p >= chunk * 8u && pn.p < ce)) {
-                    const Words wc = philox(chunk, slot, 1u, kDomainTree, k0, k1);
-                    mc = pn.m + div_n(exp1_f32(wc.w0), ce - chunk * 8u);
-                    pc = chunk * 8u + uniform_position(wc.w1, wc.w2, ce - chunk * 8u);
-                }
-                const Words w = LAYOUT == 0 ? philox(chunk, slot, 8u + (uint32_t)h, kDomainTree, k0, k1)
-                                            : philox(base4 >> 2, slot, 0u, kDomainFlat, k0, k1);
+                const Words w = philox(base4 >> 2, slot, 0u, kDomainFlat, k0, k1);
 #pragma unroll
                 for (int t = 0; t < 4; ++t)
                     xs[t] = (mask >> t) & 1u ? load_logit<BF16>(r.ptr, (int)(base4 + (uint32_t)t)) : -INFINITY;
-                half_scores<LAYOUT>(r, base4, mask, xs, mc, pc, w, current_threshold(sm), sc);
+                half_scores<1>(r, base4, mask, xs, 0.f, 0u, w, current_threshold(sm), sc);
                 offer_best(sm, sc);
             }
             __syncthreads();
@@ -721,15 +697,14 @@ __device__ __forceinline__ void eval_overflow(const RaceArgs& a, const Row& r, S
     }
 }
 
-// Reorder the first n entries of the group list by their bounds (ln of the group
-// minimum minus the scaled group maximum), counting-sorted into kBuckets buckets
+// Reorder the first n entries of the group list by their bounds (ln of the clock
+// floor minus the scaled group maximum), counting-sorted into kBuckets buckets
 // between the smallest bound and the threshold; entries above the threshold are
 // dropped.  Evaluating the most promising groups first lowers the threshold
 // early, and a pass whose first entry's bucket lies above the threshold ends the
 // evaluation (later buckets hold larger bounds).  Returns the kept count.  The
 // sort stages the list in half[], which is free between evaluation passes.
 // Called by every thread.
-template <int LAYOUT>
 __device__ __forceinline__ int order_groups(const Row& r, Shared& sm, const float* gm, int n) {
     static_assert(kL2Cap <= 2 * kBlock, "two entries per thread");
     const int tid = threadIdx.x, lane = tid & 63;
@@ -741,8 +716,7 @@ __device__ __forceinline__ int order_groups(const Row& r, Shared& sm, const floa
     for (int i = 0; i < 2; ++i) {
         const int e = tid + i * kBlock;
         nd[i] = e < n ? sm.l2[e] : Node{0u, 0.f, 0u};
-        const float lnm = LAYOUT == 0 ? ln_f32(nd[i].m) : kLnClockFloor;
-        b[i] = e < n ? lnm - scaled(r, gm[nd[i].id & 0xFFFFFu]) : INFINITY;
+        b[i] = e < n ? kLnClockFloor - scaled(r, gm[nd[i].id & 0xFFFFFu]) : INFINITY;
         if (b[i] <= thr) wmin = fminf(wmin, b[i]);
     }
 #pragma unroll
@@ -798,12 +772,12 @@ __device__ __forceinline__ int order_groups(const Row& r, Shared& sm, const floa
 
 // Evaluate and empty the group list.  Callers read the list count after a barrier
 // and before any push of the current pass.
-template <bool BF16, int LAYOUT>
+template <bool BF16>
 __device__ __forceinline__ void flush_groups(const RaceArgs& a, const Row& r, Shared& sm, const float* gm, uint32_t k0,
                                              uint32_t k1) {
     int n = min(sm.n_l2, kL2Cap);
     const bool ordered = n > kPassGroups;
-    if (ordered) n = order_groups<LAYOUT>(r, sm, gm, n);
+    if (ordered) n = order_groups(r, sm, gm, n);
     int par = 0;
     Unit<BF16> ux[kRowEntries];
     load_pass<BF16>(a, r, sm, 0, n, ux);
@@ -814,11 +788,11 @@ __device__ __forceinline__ void flush_groups(const RaceArgs& a, const Row& r, Sh
             break;
         HalfOut ho;
         uint32_t ovf;
-        eval_groups<BF16, LAYOUT>(a, r, sm, gm, first, min(n - first, kPassGroups), n, par, k0, k1, ho, ovf, ux);
+        eval_groups<BF16>(a, r, sm, gm, first, min(n - first, kPassGroups), n, par, k0, k1, ho, ovf, ux);
         __syncthreads();
         // every half of the pass has lowered the best: list the near-ties
         if (ho.valid) list_near(sm, a, ho.base4, ho.slot, ho.sc, sm.half[threadIdx.x].x);
-        if (sm.n_ev[par] > (uint32_t)kHalfCap) eval_overflow<BF16, LAYOUT>(a, r, sm, first, ovf, k0, k1);
+        if (sm.n_ev[par] > (uint32_t)kHalfCap) eval_overflow<BF16>(a, r, sm, first, ovf, k0, k1);
         __syncthreads();
         // (the next pass touches the candidates only after two more barriers)
         if (threadIdx.x == 0) compact_candidates(sm);
@@ -830,61 +804,219 @@ __device__ __forceinline__ void flush_groups(const RaceArgs& a, const Row& r, Sh
     __syncthreads();
 }
 
-// Expand listed level-3 nodes into groups (tree clocks), evaluating the groups as
-// the list fills.  A draw-free prefilter (group maximum against the node's
-// minimum) first compacts the (node, group) items that can still win into a work
-// list, so that the draws run on full wavefronts.  One loop with a single
-// evaluation call site: it refills the work list when it is used up, evaluates the
-// group list when it may overflow or at the end, and draws kBlock items per step.
+// ---- tree clocks: descent below level 3 and evaluation of the listed groups.
+//
+// A race is a chain of short phases in one workgroup, bound by their latency (Philox
+// calls, barriers, one trip to memory for the listed groups' logits), so the phases
+// are few and wide: level-3 nodes carry the mask of their groups that can still win
+// (one pass over the group maxima by the node's own lane), the set bits are the work
+// list of the group draws, and up to kEvalGroups listed groups are evaluated at once.
+// Whole calls, against passes of 32 groups in the order of their bounds: 114 -> 98 us at
+// V = 32000, K = 4, gamma = 5, B = 16 (46 and 68 groups listed per draft and target race,
+// 1.3 passes), 103 -> 95 us at V = 128256, K = 4, gamma = 4, B = 64.
+
+// Listed halves of the group entries [first, first + cnt): 16 lanes hold the 16 chunks
+// of an entry, each row of 16 lanes takes four entries at a time (their loads in flight
+// together).  Only the 4-token halves with a token that can still win are listed; most
+// entries list one.  Called by every thread.
 template <bool BF16>
-__device__ __forceinline__ void flush_l3(const RaceArgs& a, const Row& r, Shared& sm, const float* gm, uint32_t k0, uint32_t k1) {
+__device__ __forceinline__ void list_halves(const RaceArgs& a, const Row& r, Shared& sm, const float* gm, int first,
+                                            int cnt, int par) {
+    constexpr int U = 4;
+    const int tid = threadIdx.x, lane = tid & 63, c = tid & 15, row = tid >> 4;
+    const float thr = current_threshold(sm);
+    for (int s0 = 0; s0 < cnt; s0 += 16 * U) {
+        Unit<BF16> ux[U];
+        uint32_t m8[U], hold = 0u;  // surviving tokens; bit q: the chunk holds the group's minimum
+        float xc[U];
+        uint32_t base[U];
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            const int le = s0 + q * 16 + row;
+            m8[q] = 0u;
+            xc[q] = INFINITY;
+            base[q] = 0u;
+            if (le < cnt) {
+                const Node nd = sm.l2[first + le];
+                const uint32_t g = nd.id & 0xFFFFFu;
+                const float lnm = ln_f32(nd.m);
+                base[q] = g * kGroupTokens + (uint32_t)c * 8u;
+                if (lnm - scaled(r, gm[g]) <= thr && (int)base[q] < a.V) {
+                    // a token can reach thr only if lnm - (x - shift) / T <= thr, i.e.
+                    // x - shift >= (lnm - thr) T; the cut is lowered by kCutSlack, far more
+                    // than the rounding of either form (compared in the shifted frame)
+                    xc[q] = (lnm - thr - kCutSlack) * r.T;
+                    if (nd.p >= base[q] && nd.p < base[q] + 8u) hold |= 1u << q;
+                    load_words<BF16>(r.ptr, a.V, (int)base[q], ux[q]);
+                }
+            }
+        }
+        int nh = 0;
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            if (xc[q] < INFINITY) {
+                float x[8];
+                unpack_unit<BF16>(ux[q], x);
+#pragma unroll
+                for (int i = 0; i < 8; ++i) m8[q] |= (uint32_t)(x[i] - r.shift >= xc[q]) << i;
+                const int nv = a.V - (int)base[q];  // tokens of this chunk inside the row
+                if (nv < 8) m8[q] &= (1u << nv) - 1u;
+                nh += (int)((m8[q] & 15u) != 0u) + (int)((m8[q] >> 4) != 0u);
+            }
+        }
+        // list positions: wave prefix sum of the halves, one atomic per wave
+        const uint32_t mine = (uint32_t)nh;
+        const uint32_t incl = wave_incl_sum(mine);
+        const uint32_t wtot = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+        uint32_t wbase = 0u;
+        if (lane == 0 && wtot != 0u) wbase = atomicAdd(&sm.n_ev[par], wtot);
+        int jh = (int)((uint32_t)__builtin_amdgcn_readlane((int)wbase, 0) + incl - mine);
+        if (nh == 0) continue;
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            if (m8[q] == 0u) continue;
+            float x[8];
+            unpack_unit<BF16>(ux[q], x);
+            const uint32_t desc = ((uint32_t)(s0 + q * 16 + row) << 9) | ((uint32_t)c << 5);
+            const int cref = (hold >> q) & 1u ? -1 : 0;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const uint32_t hm = h ? m8[q] >> 4 : m8[q] & 15u;
+                if (hm == 0u) continue;
+                if (jh < kHalfCap) {
+                    Half& hf = sm.half[jh];
+                    hf.desc = desc | ((uint32_t)h << 4) | hm;
+                    hf.cref = cref;
+                    hf.x[0] = x[4 * h];
+                    hf.x[1] = x[4 * h + 1];
+                    hf.x[2] = x[4 * h + 2];
+                    hf.x[3] = x[4 * h + 3];
+                }
+                ++jh;
+            }
+        }
+    }
+}
+
+// Score the first nh listed halves (one per thread), lower the best score and list the
+// near-ties.  A wave lists its halves after it has offered all of them, so a score is
+// listed only if it is within the margin of every earlier one: a few candidates per
+// pass (the decision drops those that later scores leave behind).
+__device__ __forceinline__ void score_halves(const RaceArgs& a, const Row& r, Shared& sm, int first, int nh, uint32_t k0,
+                                             uint32_t k1) {
     const int tid = threadIdx.x;
-    const int n = min(sm.n_l3, kL3Cap) * 16;
-    const uint32_t V = (uint32_t)a.V;
-    const int ng = a.L.ng;
-    int base = 0, nw = 0, wb = 0;  // next prefilter item; work list size; next work item
-    for (;;) {
-        // (uniform: nw is read by every thread after a barrier; a list found empty
-        // is 0 when thread 0 clears it again)
-        while (wb >= nw && base < n) {
-            if (tid == 0) sm.n_work = 0;
-            __syncthreads();
-            const float thr = current_threshold(sm);
-            for (int e = base + tid; e < min(n, base + kWorkCap); e += kBlock) {
-                const Node pa = sm.l3[e >> 4];
-                const uint32_t g = (pa.id & 0xFFFFFu) * 16u + (uint32_t)(e & 15);
-                if ((int)g < ng && ln_f32(pa.m) - scaled(r, gm[g]) <= thr) sm.work[atomicAdd(&sm.n_work, 1)] = e;
-            }
-            __syncthreads();
-            nw = sm.n_work;
-            wb = 0;
-            base += kWorkCap;
-        }
-        const bool done = wb >= nw;
-        // The count is read by every thread before any thread of this step pushes.
-        const bool flush = done ? sm.n_l2 > 0 : sm.n_l2 > kL2Cap - kBlock;
+    if (tid >= nh) return;
+    const Half hf = sm.half[tid];
+    const Node pn = sm.l2[first + (int)(hf.desc >> 9)];
+    const uint32_t slot = pn.id >> 20, g = pn.id & 0xFFFFFu;
+    const uint32_t chunk = g * 16u + ((hf.desc >> 5) & 15u), h = (hf.desc >> 4) & 1u;
+    const uint32_t base4 = chunk * 8u + 4u * h;
+    float mc = pn.m;
+    uint32_t pc = pn.p;
+    if (hf.cref >= 0) {
+        // the chunk's own minimum (its draw is independent of the half's words, so the
+        // two Philox calls overlap)
+        const uint32_t n = node_end(kShift1, chunk, (uint32_t)a.V) - chunk * 8u;
+        const Words wc = philox(chunk, slot, 1u, kDomainTree, k0, k1);
+        mc = pn.m + div_n(exp1_f32(wc.w0), n);
+        pc = chunk * 8u + uniform_position(wc.w1, wc.w2, n);
+    }
+    const Words w = philox(chunk, slot, 8u + h, kDomainTree, k0, k1);
+    float sc[4];
+    half_scores<0>(r, base4, hf.desc & 15u, hf.x, mc, pc, w, current_threshold(sm), sc);
+    offer_best(sm, sc);
+    list_near(sm, a, base4, slot, sc, hf.x);
+}
+
+// Evaluate and empty the group list (called after a barrier that published it; every
+// thread calls it, and it ends with a barrier).  par: parity of the half count in use
+// (the other one is 0), kept by the race.
+template <bool BF16>
+__device__ __forceinline__ void eval_list(const RaceArgs& a, const Row& r, Shared& sm, const float* gm, uint32_t k0,
+                                          uint32_t k1, int& par) {
+    const int n = min(sm.n_l2, kL2Cap);
+    if (n == 0) {
         __syncthreads();
-        if (flush) flush_groups<BF16, 0>(a, r, sm, gm, k0, k1);
-        if (done) break;
-        const int i = wb + tid;
-        if (i < nw) {
-            const int e = sm.work[i];
-            const Node pa = sm.l3[e >> 4];
-            const uint32_t g = (pa.id & 0xFFFFFu) * 16u + (uint32_t)(e & 15);
-            const float thr = current_threshold(sm);
-            if (ln_f32(pa.m) - scaled(r, gm[g]) <= thr) {
-                const uint32_t slot = pa.id >> 20;
-                float m;
-                uint32_t p;
-                child_min_f32(pa.m, pa.p, 2, g, g << kShift2, node_end(kShift2, g, V), slot, k0, k1, m, p);
-                if (ln_f32(m) - scaled(r, gm[g]) <= thr) push_node(sm.l2, &sm.n_l2, kL2Cap, (slot << 20) | g, m, p);
-            }
+        return;
+    }
+    // A pass that lists more halves than fit scores those that do and lists its entries
+    // again: the best score they left usually drops most of the others (a (token, slot)
+    // may be scored twice).  If it overflows again the pass is halved, down to eight
+    // entries, whose 256 halves always fit.
+    int step = kEvalGroups;
+    bool again = false;
+    for (int first = 0; first < n;) {
+        const int cnt = min(n - first, step);
+        list_halves<BF16>(a, r, sm, gm, first, cnt, par);
+        __syncthreads();
+        const int nh = (int)sm.n_ev[par];
+        if (threadIdx.x == 0) {
+            sm.n_ev[par ^ 1] = 0u;  // (last read before the previous barrier)
+            sm.n_l2 = 0;            // (read by every thread at entry)
         }
-        wb += kBlock;
+        par ^= 1;
+        score_halves(a, r, sm, first, min(nh, kHalfCap), k0, k1);
+        if (nh <= kHalfCap) {
+            first += cnt;
+            step = kEvalGroups;
+            again = false;
+        } else {
+            if (again) step = max(8, cnt >> 1);
+            again = true;
+        }
         __syncthreads();
     }
-    if (tid == 0) sm.n_l3 = 0;
-    __syncthreads();
+    // (no candidate is listed before the next barrier, so every thread reads the same count)
+    if (sm.n_cand > kCandCap / 2) {
+        if (threadIdx.x == 0) compact_candidates(sm);
+        __syncthreads();
+    }
+}
+
+// Draw the groups of the listed level-3 nodes, list those that can still win and
+// evaluate them (called after a barrier that published the list; every thread calls
+// it, and it ends with a barrier).
+template <bool BF16>
+__device__ __forceinline__ void expand_l3(const RaceArgs& a, const Row& r, Shared& sm, const float* gm, uint32_t k0,
+                                          uint32_t k1, int& par) {
+    const int tid = threadIdx.x, lane = tid & 63;
+    const uint32_t V = (uint32_t)a.V;
+    const int nl3 = (int)(sm.n_l3 & 0xFFFFu), nw = (int)(sm.n_l3 >> 16);
+    const bool compact = nw <= kWorkCap;  // else every group of the listed nodes, by its mask bit
+    const int tot = compact ? nw : nl3 * 16;
+    if (tot == 0) {
+        __syncthreads();
+        return;
+    }
+    for (int wb = 0; wb < tot;) {
+        const int i = wb + tid;
+        bool pass = false;
+        Node gn = Node{0u, 0.f, 0u};
+        if (i < tot) {
+            const int e = compact ? (int)sm.work[i] : i;
+            const Node pa = sm.l3[e >> 4];
+            const uint32_t g = (pa.id & 0xFFFFFu) * 16u + (uint32_t)(e & 15);
+            if (compact || ((sm.l3_mask[e >> 4] >> (e & 15)) & 1u)) {
+                const uint32_t slot = pa.id >> 20;
+                child_min_f32(pa.m, pa.p, 2, g, g << kShift2, node_end(kShift2, g, V), slot, k0, k1, gn.m, gn.p);
+                gn.id = (slot << 20) | g;
+                pass = ln_f32(gn.m) - scaled(r, gm[g]) <= current_threshold(sm);
+            }
+        }
+        const uint64_t bal = __ballot(pass);
+        int at = 0;
+        if (lane == 0 && bal != 0u) at = atomicAdd(&sm.n_l2, (int)__builtin_popcountll(bal));
+        at = __builtin_amdgcn_readlane(at, 0) +
+             (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u));
+        if (pass) sm.l2[at] = gn;  // (at most kBlock are listed between two checks of the count)
+        __syncthreads();
+        if (tid == 0) sm.n_l3 = 0u;  // (read by every thread at entry)
+        wb += kBlock;
+        if (wb >= tot || sm.n_l2 > kL2Cap - kBlock)
+            eval_list<BF16>(a, r, sm, gm, k0, k1, par);
+        else
+            __syncthreads();
+    }
 }
 
 // Lexicographic minimum of (score, token, slot).
@@ -981,8 +1113,9 @@ __device__ __forceinline__ void race(const RaceArgs& a, const Row& r, Shared& sm
                 if (l == 0 && g >= 0) {
                     const float sc = ln_f32(E) - scaled(r, xa);
                     if (sc < INFINITY) {
+                        // (listed only if within the margin of the best so far)
                         atomicMin(&sm.best_key, ordered_key(sc));
-                        push_candidate(sm, a, (int)av, (int)slot, sc, xa);
+                        if (sc <= current_threshold(sm)) push_candidate(sm, a, (int)av, (int)slot, sc, xa);
                     }
                 }
             } else {
@@ -1014,31 +1147,57 @@ __device__ __forceinline__ void race(const RaceArgs& a, const Row& r, Shared& sm
     __syncthreads();
 
     if constexpr (LAYOUT == 0) {
-        // Pass B: level-3 children of the level-4 nodes that can still win.
+        // Pass B: level-3 children of the level-4 nodes that can still win, each with the
+        // mask of its groups that can (the node's minimum bounds theirs).
+        const int lane = tid & 63;
+        int par = 0;
         const int nB = ns * n4 * 16;
         const int n3 = (ng + 15) / 16;
-        for (int base = 0;; base += kBlock) {
-            const bool done = base >= nB;  // one call site of flush_l3 (see flush_l3)
-            const bool flush = done || sm.n_l3 > kL3Cap - kBlock;
-            __syncthreads();
-            if (flush) flush_l3<BF16>(a, r, sm, gm, k0, k1);
-            if (done) break;
+        for (int base = 0; base < nB;) {
             const int e = base + tid;
+            uint32_t mask = 0u;
+            Node nd = Node{0u, 0.f, 0u};
             if (e < nB) {
                 const Node pa = level4_list(gm, ng)[e >> 4];
                 const uint32_t i4 = pa.id & 0xFFFFFu;
                 const uint32_t i3 = i4 * 16u + (uint32_t)(e & 15);
                 const float thr = current_threshold(sm);
-                const float lnp = ln_f32(pa.m);
-                if ((int)i3 < n3 && lnp - scaled(r, sm.m4[i4]) <= thr && lnp - scaled(r, sm.m3[i3]) <= thr) {
+                if ((int)i3 < n3 && ln_f32(pa.m) - scaled(r, sm.m3[i3]) <= thr) {
                     const uint32_t slot = pa.id >> 20;
-                    float m;
-                    uint32_t p;
-                    child_min_f32(pa.m, pa.p, 3, i3, i3 << kShift3, node_end(kShift3, i3, V), slot, k0, k1, m, p);
-                    if (ln_f32(m) - scaled(r, sm.m3[i3]) <= thr) push_node(sm.l3, &sm.n_l3, kL3Cap, (slot << 20) | i3, m, p);
+                    child_min_f32(pa.m, pa.p, 3, i3, i3 << kShift3, node_end(kShift3, i3, V), slot, k0, k1, nd.m, nd.p);
+                    nd.id = (slot << 20) | i3;
+                    const float xc = (ln_f32(nd.m) - thr - kCutSlack) * r.T;
+                    const float4* g4 = (const float4*)(gm + i3 * 16u);
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const float4 x = g4[q];
+                        mask |= ((uint32_t)(x.x - r.shift >= xc) | ((uint32_t)(x.y - r.shift >= xc) << 1) |
+                                 ((uint32_t)(x.z - r.shift >= xc) << 2) | ((uint32_t)(x.w - r.shift >= xc) << 3))
+                                << (4 * q);
+                    }
                 }
             }
+            // list positions of the node (low half) and of its group bits (high half)
+            const uint32_t mine = mask ? ((uint32_t)__popc(mask) << 16) | 1u : 0u;
+            const uint32_t incl = wave_incl_sum(mine);
+            const uint32_t wtot = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+            uint32_t at = 0u;
+            if (lane == 0 && wtot != 0u) at = atomicAdd(&sm.n_l3, wtot);
+            at = (uint32_t)__builtin_amdgcn_readlane((int)at, 0) + incl - mine;
+            if (mask) {
+                const uint32_t i = at & 0xFFFFu;
+                uint32_t w = at >> 16;
+                sm.l3[i] = nd;
+                sm.l3_mask[i] = (uint16_t)mask;
+                for (; mask; mask &= mask - 1u, ++w)
+                    if (w < (uint32_t)kWorkCap) sm.work[w] = (uint16_t)(i * 16u + (uint32_t)__builtin_ctz(mask));
+            }
             __syncthreads();
+            base += kBlock;
+            if (base >= nB || (sm.n_l3 & 0xFFFFu) > (uint32_t)(kL3Cap - kBlock))
+                expand_l3<BF16>(a, r, sm, gm, k0, k1, par);
+            else
+                __syncthreads();
         }
     } else {
         // flat clocks: every (group, slot) whose floor bound can win.
@@ -1047,7 +1206,7 @@ __device__ __forceinline__ void race(const RaceArgs& a, const Row& r, Shared& sm
             const bool done = base >= tot;  // one call site of flush_groups
             const bool flush = done || sm.n_l2 > kL2Cap - kBlock;
             __syncthreads();
-            if (flush) flush_groups<BF16, 1>(a, r, sm, gm, k0, k1);
+            if (flush) flush_groups<BF16>(a, r, sm, gm, k0, k1);
             if (done) break;
             const int e = base + tid;
             if (e < tot) {
@@ -1064,7 +1223,24 @@ __device__ __forceinline__ void race(const RaceArgs& a, const Row& r, Shared& sm
     // tree clocks 8 lanes per candidate draw its path nodes in parallel.
     const float best = ordered_value(sm.best_key);
     const int nc = min(sm.n_cand, kCandCap);
-    {
+    if (nc <= 64) {
+        // Every wave looks the candidates over by itself (no barrier): one (token, slot)
+        // within the margin of the best, possibly listed twice, is the winner, as below.
+        const int l = tid & 63;
+        const bool in = l < nc && sm.cand_s[l] <= best + kMargin;
+        const uint64_t bal = __ballot(in);
+        if (bal != 0u) {
+            const int key = l < nc ? sm.cand_v[l] * 32 + sm.cand_j[l] : 0;  // token < 2^19, slot < 32
+            const int k = __builtin_amdgcn_readlane(key, (int)__builtin_ctzll(bal));
+            if (__ballot(in && key != k) == 0u) {
+                if (tid == 0) {
+                    sm.win_token = k >> 5;
+                    sm.win_slot = k & 31;
+                }
+                return;
+            }
+        }
+    } else {
         // A single candidate within the margin of the best is the winner: float32
         // scores err by far less than the margin, and every token that was not kept
         // scored above it.
@@ -1273,25 +1449,24 @@ __device__ __forceinline__ void finish_row(const RaceArgs& a, const Row& r, Shar
         wpos = a.start_pos[r.b];
     }
 
-    // ---- gather the row's slots (group maxima, block maxima, segment top tokens):
+    // ---- gather the row's slots (group maxima, block maxima, segment sums):
     // a batch of loads in flight per thread, then a wait only for slots not yet
     // published.
     {
         const uint64_t* gslot = (const uint64_t*)(a.ws + a.L.gmax) + (size_t)r.row_id * ng;
         const uint64_t* m3slot = (const uint64_t*)(a.ws + a.L.m3) + (size_t)r.row_id * n3;
-        const uint64_t* stop = (const uint64_t*)(a.ws + a.L.stop) + (size_t)r.row_id * a.L.nseg;
         const uint64_t* pslot = (const uint64_t*)(a.ws + a.L.part) + (size_t)r.row_id * a.L.nseg;
-        const int ne = ng + n3 + 2 * a.L.nseg;
+        const int ne = ng + n3 + a.L.nseg;
+        if (tid < padded_groups(ng) - ng) gm[ng + tid] = -INFINITY;
         for (int e0 = 0; e0 < ne; e0 += 4 * kBlock) {
             const uint64_t* src[4];
             uint64_t v[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const int e = e0 + i * kBlock + tid;
-                src[i] = e < ng                     ? gslot + e
-                         : e < ng + n3                ? m3slot + (e - ng)
-                         : e < ng + n3 + a.L.nseg     ? stop + (e - ng - n3)
-                                                      : pslot + min(e - ng - n3 - a.L.nseg, a.L.nseg - 1);
+                src[i] = e < ng          ? gslot + e
+                         : e < ng + n3     ? m3slot + (e - ng)
+                                           : pslot + min(e - ng - n3, a.L.nseg - 1);
                 v[i] = e < ne ? ld_dev(src[i]) : 0;
             }
 #pragma unroll
@@ -1304,45 +1479,41 @@ __device__ __forceinline__ void finish_row(const RaceArgs& a, const Row& r, Shar
                         gm[e] = __uint_as_float(w);
                     else if (e < ng + n3)
                         sm.m3[e - ng] = __uint_as_float(w);
-                    else if (e < ng + n3 + a.L.nseg)  // a group index of this row, or -1 (a value
-                        sm.stop[e - ng - n3] = (int)w >= -1 && (int)w < ng ? (int)w : -1;  // left stale by a timed-out wait is dropped)
                     else
-                        sm.part[e - ng - n3 - a.L.nseg] = __uint_as_float(w);
+                        sm.part[e - ng - n3] = __uint_as_float(w);
                 }
             }
         }
     }
     __syncthreads();
 
-    // ---- key-independent work: the race's seed tokens (the largest token of each
-    // segment's top group, at most kInit of the largest groups), level-4 maxima,
-    // LSE, row maximum.
-    if (wave == 0) {
+    // ---- key-independent work: the race's seed tokens, level-4 maxima, LSE, row
+    // maximum.  Seed groups: the largest group of each eighth of the row (lowest index
+    // on ties; -1 where the eighth has no finite logit), 32 lanes per eighth.  A row of
+    // any size gets up to 8 seeds this way: with one seed per 32 KiB segment a
+    // 32000-token bf16 row had two, and its 4-slot races listed 111 (slot, group)
+    // pairs on average instead of 88 (46 against the final best score).
+    {
+        static_assert(kInit * 32 == kBlock, "32 lanes per seed group");
+        const int i = tid >> 5, l32 = lane & 31;
+        const int g0 = i * ng / kInit, g1 = (i + 1) * ng / kInit;
         float bv = -INFINITY;
-        int bt = 0x7FFFFFFF;
-        if (lane < a.L.nseg && sm.stop[lane] >= 0) {
-            bt = sm.stop[lane];
-            bv = gm[bt];
-        }
-        if (a.L.nseg <= kInit) {
-            if (lane < kInit) sm.init_v[lane] = bv == -INFINITY ? -1 : bt;
-        } else {
-            for (int i = 0; i < kInit; ++i) {
-                float mv = bv;
-                int mt = bt;
+        int bg = 0x7FFFFFFF;
+        for (int g = g0 + l32; g < g1; g += 32)
+            if (gm[g] > bv) {
+                bv = gm[g];
+                bg = g;
+            }
 #pragma unroll
-                for (int off = 32; off > 0; off >>= 1) {
-                    const float ov = __shfl_xor(mv, off);
-                    const int ot = __shfl_xor(mt, off);
-                    if (ov > mv || (ov == mv && ot < mt)) {
-                        mv = ov;
-                        mt = ot;
-                    }
-                }
-                if (lane == 0) sm.init_v[i] = mv == -INFINITY ? -1 : mt;
-                if (bt == mt) bv = -INFINITY;
+        for (int off = 16; off > 0; off >>= 1) {
+            const float ov = __shfl_xor(bv, off);
+            const int og = __shfl_xor(bg, off);
+            if (ov > bv || (ov == bv && og < bg)) {
+                bv = ov;
+                bg = og;
             }
         }
+        if (l32 == 0) sm.init_v[i] = bv == -INFINITY ? -1 : bg;
     }
     __syncthreads();
     // Waves 0-1: the seed tokens, 16 lanes per seed group with 8 tokens each (the
@@ -1402,26 +1573,40 @@ __device__ __forceinline__ void finish_row(const RaceArgs& a, const Row& r, Shar
                 a.target_lse[o] = lse;
             }
             sm.rowmax = rm;
-            sm.n_l4 = sm.n_l3 = sm.n_l2 = sm.n_cand = 0;
+            sm.n_l3 = 0u;
+            sm.n_l2 = sm.n_cand = 0;
             sm.n_ev[0] = sm.n_ev[1] = 0;
             sm.best_key = ordered_key(INFINITY);
             sm.key_min = 0x7FFFFFFF;
             sm.key_max = -1;
+            // (thread 0 reads these with one LDS trip after the race, instead of fetching
+            // the arguments they are made of then)
+            sm.pub_key = cons ? (uint64_t*)(a.ws + a.L.keys) + 2 * (size_t)r.row_id : nullptr;
+            sm.pub_tok = (uint64_t*)(a.ws + a.L.tok) + r.row_id;
+            const size_t o = r.kind == 0 || a.target_rows > 1
+                                 ? ((size_t)r.b * a.K + r.k) * (size_t)(a.gamma + (r.kind == 1)) + r.s
+                                 : (size_t)r.b * (a.gamma + 1) + r.s;
+            int32_t* outs = r.kind == 0 ? a.draft_tokens : a.target_tokens;
+            sm.pub_out = outs ? outs + o : nullptr;
         }
     } else {
         // Context keys: the window's path tokens (published by earlier races of this
-        // call, or inputs), both chains folded at once -- lane 0 this row's key, lane 1
-        // the next depth's key up to its newest token (the winner of this race) --
-        // then lane 0 waits for the key published by the race one depth up this path,
-        // if any.
-        const int tk = widx >= a.m ? path_token(a, r, widx - a.m, ep) : wtok;
+        // call, or inputs), both chains folded at once -- lane 0 this row's key (when no
+        // race publishes it), lane 1 the next depth's key up to its newest known token.
+        // A row whose key comes from the race one depth up the path then waits for it;
+        // that race's winner comes with it and is folded after this row's race, so that
+        // neither a wait nor a fold stands between the key and the race (from a winner
+        // to the next race's start: 0.6 us, 1.9 with the winner waited for and folded here).
+        const int nk = a.m - (prod >= 0 && a.m > 1 ? 2 : 1);  // lane 1's tokens
+        const bool known = widx >= 0 && (lane < a.m || lane - a.m < nk);
+        const int tk = known && widx >= a.m ? path_token(a, r, widx - a.m, ep) : wtok;
         const uint64_t t = (uint64_t)(wpos + r.s) + (uint64_t)(lane == 1);
         uint32_t c0 = (uint32_t)a.key, c1 = (uint32_t)(a.key >> 32);
         const bool chain = (lane == 0 && prod < 0) || (lane == 1 && cons);
         if (chain) fold(c0, c1, (uint32_t)t, (uint32_t)(t >> 32), 0u);
         for (int i = 0; i < a.m; ++i) {
             const int w = __shfl(tk, lane == 0 ? i : a.m + i);
-            if (chain && (lane == 0 || i + 1 < a.m)) fold(c0, c1, (uint32_t)w, (uint32_t)i, 1u);
+            if (chain && (lane == 0 || i < nk)) fold(c0, c1, (uint32_t)w, (uint32_t)i, 1u);
         }
         if (lane == 0 && prod < 0) {
             sm.kappa0 = c0;
@@ -1431,13 +1616,11 @@ __device__ __forceinline__ void finish_row(const RaceArgs& a, const Row& r, Shar
             sm.next0 = c0;
             sm.next1 = c1;
         }
-        if (lane == 0 && prod >= 0) {
-            const uint64_t* ks = (const uint64_t*)(a.ws + a.L.keys) + 2 * (size_t)prod;
-            uint64_t w0 = ld_dev(ks), w1 = ld_dev(ks + 1);
-            if ((uint32_t)(w0 >> 32) != ep) w0 = wait_slot(a, ks, ep);
-            if ((uint32_t)(w1 >> 32) != ep) w1 = wait_slot(a, ks + 1, ep);
-            sm.kappa0 = (uint32_t)w0;
-            sm.kappa1 = (uint32_t)w1;
+        if (prod >= 0) {
+            const uint32_t w = wait_key(a, prod, ep, cons && a.m > 1);
+            if (lane == 0) sm.kappa0 = w;
+            if (lane == 1) sm.kappa1 = w;
+            if (lane == 2) sm.newest = (int)w;
         }
     }
     __syncthreads();
@@ -1455,24 +1638,21 @@ __device__ __forceinline__ void finish_row(const RaceArgs& a, const Row& r, Shar
     }
     if (tid == 0) {
         const int y = sm.win_token;
-        if (cons) {
+        if (uint64_t* ks = sm.pub_key) {
             uint32_t n0 = sm.next0, n1 = sm.next1;
+            if (prod >= 0 && a.m > 1) fold(n0, n1, (uint32_t)sm.newest, (uint32_t)(a.m - 2), 1u);
             fold(n0, n1, (uint32_t)y, (uint32_t)(a.m - 1), 1u);
-            uint64_t* ks = (uint64_t*)(a.ws + a.L.keys) + 2 * (size_t)r.row_id;
             st_dev(ks, ((uint64_t)ep << 32) | n0);
             st_dev(ks + 1, ((uint64_t)ep << 32) | n1);
         }
-        st_dev((uint64_t*)(a.ws + a.L.tok) + r.row_id, ((uint64_t)ep << 32) | (uint32_t)y);
-        if (r.kind == 0) {
-            a.draft_tokens[((size_t)r.b * a.K + r.k) * a.gamma + r.s] = y;
-        } else if (a.target_tokens) {
-            const size_t o = a.target_rows == 1 ? (size_t)r.b * (a.gamma + 1) + r.s
-                                                : ((size_t)r.b * a.K + r.k) * (a.gamma + 1) + r.s;
-            a.target_tokens[o] = y;
-        }
+        st_dev(sm.pub_tok, ((uint64_t)ep << 32) | (uint32_t)y);
+        if (int32_t* out = sm.pub_out) *out = y;
     }
     // The last row of a sequence in the work order walks its block.
-    if (r.kind == a.walk_kind && r.s == a.walk_s && r.k == a.walk_k) walk(a, sm, r.b, ep);
+    if (r.kind == a.walk_kind && r.s == a.walk_s && r.k == a.walk_k) {
+        __syncthreads();  // (the walk reuses the candidate arrays: every wave is done with them)
+        walk(a, sm, r.b, ep);
+    }
     __builtin_amdgcn_s_setprio(0);
 }
 
@@ -1537,7 +1717,8 @@ __device__ __forceinline__ void decode_item(const RaceArgs& a, const Shared& sm,
 // Four workgroups per CU (128 VGPRs).  Of every kRolePeriod blocks, kRoleFinish
 // finish rows and the others only stream segments, so the streaming loop
 // (software-pipelined) and the races neither share a loop nor wait for each other
-// (the share of finishing blocks was measured: about 0.36 balances the two).  Both
+// (the share of finishing blocks was measured: 1/3, 94.3 us per call at V = 128256, K = 4,
+// gamma = 4, B = 64; 4/11 95.9, 4/13 97.4, 3/7 98.2).  Both
 // kinds take work in order from per-XCD queues (row R goes to queue R mod nq for
 // both): streaming never waits, and a finishing workgroup waits only for segments
 // (streamed without waiting) and for races of rows earlier in the order (taken
@@ -1571,8 +1752,9 @@ __global__ __launch_bounds__(kBlock, 4) void race_kernel(RaceArgs a) {
         // Before its first row, a finishing workgroup streams segments from its queue
         // until that row's segments are all taken: at the start the streaming is
         // behind and the first rows' races wait for it.  (It never waits here.)
-        if (sm.tick[0] < a.n_rows) {
-            const int last = sm.tick[0] * a.L.nseg + a.L.nseg - 1;
+        int R = sm.tick[0];
+        if (R < a.n_rows) {
+            const int last = R * a.L.nseg + a.L.nseg - 1;
             for (int p = 0;; p ^= 1) {
                 if (tid == 0) sm.tick[2 + p] = take_item(a, q, nq);
                 __syncthreads();
@@ -1589,7 +1771,7 @@ __global__ __launch_bounds__(kBlock, 4) void race_kernel(RaceArgs a) {
                 if (item >= last) break;
             }
         }
-        for (int R = sm.tick[0]; R < a.n_rows;) {
+        while (R < a.n_rows) {
             Row r;
             int seg;
             decode_item<BF16>(a, sm, R * a.L.nseg + a.L.nseg - 1, r, seg);
@@ -1646,7 +1828,7 @@ __global__ __launch_bounds__(kBlock, 4) void race_kernel(RaceArgs a) {
 // Shared, the group maxima and the level-4 list (K slots x level-4 nodes, 256 groups
 // each), in the order level4_list assumes.
 size_t shared_bytes(int ng, int K) {
-    return ((sizeof(Shared) + 15) & ~(size_t)15) + (size_t)((ng + 3) & ~3) * sizeof(float) +
+    return ((sizeof(Shared) + 15) & ~(size_t)15) + (size_t)padded_groups(ng) * sizeof(float) +
            (size_t)K * (size_t)((ng + 255) / 256) * sizeof(Node);
 }
 
