@@ -80,10 +80,11 @@ typedef enum { PSD_F32 = 0, PSD_BF16 = 1 } psd_dtype;
  *      source, the i-th smallest going to c's i-th path (increasing index).
  *      Target rows race slot 0 alone (MPFR(P, Pi(c), 1)); the walk is unchanged;
  *      detection scores the slot-0 clock (K = 1).  Drafting runs before the walk:
- *      one launch per depth, or, when the block's (sequence, path) workgroups fit
- *      the device together, one launch for every depth (each depth's contexts
- *      formed as the earlier drafts land); with a shared target chain, psd_verify
- *      races the chain beside it (see there). */
+ *      the draft rows are streamed, and the contexts sampled by one launch per depth,
+ *      or, when the block's (sequence, path) workgroups fit the device together, by one
+ *      launch for every depth (each depth's contexts formed as the earlier drafts
+ *      land); with a shared target chain, psd_verify races the chain beside it (see
+ *      there). */
 typedef enum { PSD_MODE_HET = 0, PSD_MODE_MPFR = 1 } psd_mode;
 
 /* TREE: clocks of a slot built top-down over a fixed token hierarchy (8-token
@@ -194,11 +195,12 @@ psd_status psd_draft(const psd_params *params, const psd_block *block, int32_t s
  * -1 or not a draft of an active path at depth s; else keep the active paths
  * that drafted y_s.  After gamma acceptances emit the bonus y_gamma.
  * Identical drafters (PSD_MODE_MPFR) with draft_logits and target_rows 1: the
- * target chain is raced on a library stream of the current device (created at
- * the first such call and kept until the process ends) beside the drafting
- * launches on `stream`; `stream` waits for it through an event before the walk.
+ * target chain is raced, and the draft rows are streamed, on two library streams of
+ * the current device (created at the first such call and kept until the process
+ * ends) beside the sampling launches on `stream`; `stream` waits for both through
+ * events before the walk.
  * Under stream capture the whole call stays on `stream`.  Such calls on one
- * device share that stream (calls from several host threads are serialised
+ * device share those streams (calls from several host threads are serialised
  * while they enqueue). */
 psd_status psd_verify(const psd_params *params, const psd_block *block, int32_t target_rows,
                       const void *target_logits, const void *draft_logits, int32_t *draft_tokens,

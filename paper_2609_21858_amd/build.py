@@ -14,12 +14,14 @@ ARCH = "gfx950"
 # Packed-fp32 VALU forms are kept out of every kernel.
 FLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}", "-Xclang", "-target-feature", "-Xclang",
          "-packed-fp32-ops", "-Wno-unused-command-line-argument"]
-# The race kernel treats NaN logits as undefined input, so float max needs no NaN quieting.
-# Its LDS atomics (the best score, list counters) are issued as they are: the default
-# atomic optimizer turns a same-address atomic with per-lane values into a scalar
+# The kernels that read logits treat NaN as undefined input, so a float max needs no NaN
+# quieting (which costs an instruction per loaded value in the streaming passes).
+# The race kernel's LDS atomics (the best score, list counters) are issued as they are:
+# the default atomic optimizer turns a same-address atomic with per-lane values into a scalar
 # loop over the active lanes (about 70 cycles per lane), far slower than the LDS
 # serialising the lanes' atomics itself.
 EXTRA = {"psd_race.hip": ["-fno-honor-nans", "-mllvm", "-amdgpu-atomic-optimizer-strategy=None"],
+         "psd_mpfr.hip": ["-fno-honor-nans"], "psd_topk.hip": ["-fno-honor-nans"],
          "psd_gen.hip": ["-ffp-contract=off"]}
 
 

@@ -23,15 +23,16 @@ thread_local char g_err[512] = "";
 constexpr uint32_t kDefaultSpinLimit = 1u << 22;
 std::atomic<uint32_t> g_spin_limit{kDefaultSpinLimit};
 
-// A side stream and a fork and a join event per device, created on first use and
-// kept until the process ends.  They let an identical-drafter call race its
-// target chain beside its drafting launches.  The mutex is held from the fork's
+// Two side streams and fork and join events per device, created on first use and
+// kept until the process ends.  They let an identical-drafter call stream its draft
+// rows and race its target chain beside its sampling launches.  The mutex is held from the fork's
 // record to the join's wait, so calls from several host threads never mix up
 // their events.
 constexpr int kMaxForkDevices = 64;
 struct Fork {
-    hipStream_t side;
-    hipEvent_t in, out;
+    hipStream_t side, race;
+    hipEvent_t in, out, raced;
+    hipEvent_t depth[PSD_MAX_GAMMA];  // a depth's draft rows are streamed (created on first use)
 };
 std::mutex g_fork_mu;
 Fork g_fork[kMaxForkDevices] = {};
@@ -43,18 +44,21 @@ Fork* fork_objects() {
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxForkDevices) return nullptr;
     Fork& f = g_fork[dev];
     if (!f.side) {
-        hipStream_t st = nullptr;
-        hipEvent_t e0 = nullptr, e1 = nullptr;
-        if (hipStreamCreateWithFlags(&st, hipStreamNonBlocking) != hipSuccess) return nullptr;
-        if (hipEventCreateWithFlags(&e0, hipEventDisableTiming) != hipSuccess ||
-            hipEventCreateWithFlags(&e1, hipEventDisableTiming) != hipSuccess) {
-            if (e0) (void)hipEventDestroy(e0);
-            (void)hipStreamDestroy(st);
+        Fork n = {};
+        const bool ok = hipStreamCreateWithFlags(&n.side, hipStreamNonBlocking) == hipSuccess &&
+                        hipStreamCreateWithFlags(&n.race, hipStreamNonBlocking) == hipSuccess &&
+                        hipEventCreateWithFlags(&n.in, hipEventDisableTiming) == hipSuccess &&
+                        hipEventCreateWithFlags(&n.out, hipEventDisableTiming) == hipSuccess &&
+                        hipEventCreateWithFlags(&n.raced, hipEventDisableTiming) == hipSuccess;
+        if (!ok) {
+            if (n.raced) (void)hipEventDestroy(n.raced);
+            if (n.out) (void)hipEventDestroy(n.out);
+            if (n.in) (void)hipEventDestroy(n.in);
+            if (n.race) (void)hipStreamDestroy(n.race);
+            if (n.side) (void)hipStreamDestroy(n.side);
             return nullptr;
         }
-        f.in = e0;
-        f.out = e1;
-        f.side = st;
+        f = n;
     }
     return &f;
 }
@@ -183,10 +187,8 @@ void build_depths(psd::RaceArgs& a, int n_depth) {
     a.n_rows = first / a.L.nseg;
 }
 
-// Identical drafters: depths [s_begin, s_begin + s_count) drafted one launch per depth
-// (each depth's contexts depend on the previous depth's drafts).  mpfr_args fills
-// the arguments, mpfr_stream_rows launches the call's streaming pass when there is
-// one, mpfr_sample_depths the depth launches.
+// Identical drafters.  mpfr_args fills the arguments, mpfr_prepare chooses the form of
+// the call, mpfr_stream_rows launches a streaming pass, mpfr_sample a sampling launch.
 psd::MpfrArgs mpfr_args(const psd_params* p, const psd_block* b, int32_t s_begin, int32_t s_count,
                         const void* draft_logits, int32_t* draft_tokens, float* draft_lse) {
     psd::MpfrArgs m;
@@ -212,18 +214,24 @@ psd::MpfrArgs mpfr_args(const psd_params* p, const psd_block* b, int32_t s_begin
     return m;
 }
 
-// A depth's launch has one workgroup per (sequence, path), each streaming its row.
-// When those cannot fill the device (B K < 1024), every draft row of the call is
-// streamed first in one launch (group maxima, maxima, LSE) and the depths only sample
-// (in one launch when its workgroups fit the device together); otherwise each depth's
-// streaming overlaps its contexts' sampling.
-// Sets the streamed rows' words and the form of the sampling (one launch for every
-// depth when it fits the device, else one per depth); *streamed tells whether the call
-// has a streaming launch.
-psd_status mpfr_prepare(const psd_params* p, const psd_block* b, psd::MpfrArgs& m, bool* streamed) {
-    *streamed = (long)b->batch * p->num_drafts < psd::kMpfrStreamBelow;
-    if (!*streamed) return PSD_OK;
+// When a depth's B K (sequence, path) workgroups cannot fill the device (B K < 1024),
+// every draft row of the call is streamed in one launch (group maxima, maxima, seeds,
+// LSE) and the sampling is one launch for every depth when its workgroups fit the device
+// together (tok_slot), else one per depth.  Otherwise each depth has a streaming launch
+// and a sampling launch, so that a depth's rows can stream while the previous depth is
+// sampled: at V=256000, K=16, gamma=4, B=256 2182 us per call against 3036 with one
+// launch per depth whose workgroups streamed a row each and then sampled (sized for
+// sampling, they read at 3.9 TB/s).
+psd_status mpfr_prepare(const psd_params* p, const psd_block* b, psd::MpfrArgs& m, bool* by_depth) {
     const psd::WsLayout L = psd::ws_layout(b->batch, p->num_drafts, b->gamma, p->vocab, p->dtype == PSD_BF16);
+    m.stream_s = m.s_begin;
+    m.stream_n = m.s_count;
+    *by_depth = (long)b->batch * p->num_drafts >= psd::kMpfrStreamBelow;
+    if (*by_depth) {
+        m.row_gm = (uint64_t*)((unsigned char*)b->workspace + L.gmax);  // (draft row ids come first)
+        m.stream_n = 1;
+        return PSD_OK;
+    }
     const psd::MpfrLayout M = psd::mpfr_layout(L, b->batch, p->num_drafts, b->gamma);
     m.row_gm = (uint64_t*)((unsigned char*)b->workspace + M.gm);
     m.row_max = (uint64_t*)((unsigned char*)b->workspace + M.rmax);
@@ -232,30 +240,48 @@ psd_status mpfr_prepare(const psd_params* p, const psd_block* b, psd::MpfrArgs& 
     hipError_t e = psd::mpfr_all_depths_fit(m, p->dtype == PSD_BF16, p->clocks, &fits);
     if (e != hipSuccess) return hip_fail(e, "MPFR occupancy query");
     m.tok_slot = fits ? (uint64_t*)((unsigned char*)b->workspace + M.slot) : nullptr;
-    m.stream_records_epoch = fits ? 0 : 1;
+    // half as many streaming workgroups as rows (two rows each, depth-major; at least 512
+    // or every row): the first depths' rows land sooner
+    m.stream_grid = std::max((m.B * m.K * m.s_count + 1) / 2, std::min(m.B * m.K * m.s_count, 512));
     return PSD_OK;
 }
 
-psd_status mpfr_stream_rows(const psd_params* p, psd::MpfrArgs& m, hipStream_t stream) {
+psd_status mpfr_stream_rows(const psd_params* p, const psd::MpfrArgs& m, hipStream_t stream) {
     hipError_t e = psd::launch_mpfr_stream(m, p->dtype == PSD_BF16, stream);
     if (e != hipSuccess) return hip_fail(e, "MPFR stream kernel launch");
     return PSD_OK;
 }
 
-psd_status mpfr_sample_depths(const psd_params* p, psd::MpfrArgs& m, hipStream_t stream) {
-    hipError_t e = psd::launch_mpfr_depths(m, p->dtype == PSD_BF16, p->clocks, stream);
+psd_status mpfr_sample(const psd_params* p, const psd::MpfrArgs& m, hipStream_t stream) {
+    hipError_t e = psd::launch_mpfr_sample(m, p->dtype == PSD_BF16, p->clocks, stream);
     if (e != hipSuccess) return hip_fail(e, "MPFR draft kernel launch");
     return PSD_OK;
 }
 
+// The sampling launches after a streaming launch of every row.
+psd_status mpfr_sample_depths(const psd_params* p, psd::MpfrArgs m, hipStream_t stream) {
+    if (m.tok_slot) return mpfr_sample(p, m, stream);
+    psd_status st = PSD_OK;
+    for (m.s = m.s_begin; m.s < m.s_begin + m.s_count && st == PSD_OK; ++m.s) st = mpfr_sample(p, m, stream);
+    return st;
+}
+
+// Every launch on one stream.
 psd_status run_mpfr_drafts(const psd_params* p, const psd_block* b, int32_t s_begin, int32_t s_count,
                            const void* draft_logits, int32_t* draft_tokens, float* draft_lse, hipStream_t stream) {
     psd::MpfrArgs m = mpfr_args(p, b, s_begin, s_count, draft_logits, draft_tokens, draft_lse);
-    bool streamed = false;
-    psd_status st = mpfr_prepare(p, b, m, &streamed);
-    if (st == PSD_OK && streamed) st = mpfr_stream_rows(p, m, stream);
+    bool by_depth = false;
+    psd_status st = mpfr_prepare(p, b, m, &by_depth);
     if (st != PSD_OK) return st;
-    return mpfr_sample_depths(p, m, stream);
+    if (!by_depth) {
+        if ((st = mpfr_stream_rows(p, m, stream)) != PSD_OK) return st;
+        return mpfr_sample_depths(p, m, stream);
+    }
+    for (int d = s_begin; d < s_begin + s_count && st == PSD_OK; ++d) {
+        m.stream_s = m.s = d;
+        if ((st = mpfr_stream_rows(p, m, stream)) == PSD_OK) st = mpfr_sample(p, m, stream);
+    }
+    return st;
 }
 
 // Truncated logits: the kept list of every row of the call, then one workgroup per
@@ -445,44 +471,59 @@ psd_status verify_mpfr_forked(const psd_params* params, const psd_block* block, 
     a.walk_kind = -1;  // no row walks: the walk kernel does, after the drafts
     a.status = ctrl + psd::kCtrlRaceBits;
     psd::MpfrArgs m = mpfr_args(params, block, 0, block->gamma, draft_logits, draft_tokens, draft_lse);
-    bool streamed = false;
-    psd_status st = mpfr_prepare(params, block, m, &streamed);
+    bool by_depth = false;
+    psd_status st = mpfr_prepare(params, block, m, &by_depth);
     if (st != PSD_OK) return st;
     hipError_t e;
     psd_status sd;
-    if (streamed && m.tok_slot) {
+    if (by_depth)
+        for (int d = 0; d < m.gamma; ++d)
+            if (!f.depth[d] && (e = hipEventCreateWithFlags(&f.depth[d], hipEventDisableTiming)) != hipSuccess) {
+                f.depth[d] = nullptr;
+                return hip_fail(e, "depth event");
+            }
+    if ((e = hipEventRecord(f.in, stream)) != hipSuccess) return hip_fail(e, "fork event record");
+    if ((e = hipStreamWaitEvent(f.side, f.in, 0)) != hipSuccess ||
+        (e = hipStreamWaitEvent(f.race, f.in, 0)) != hipSuccess)
+        return hip_fail(e, "fork event wait");
+    // From here on both joins are always enqueued, so the caller's stream never runs
+    // ahead of the side streams.  The target race runs beside everything else with fewer
+    // workgroups than it would take alone, which leaves room for the others': per call
+    // at V=128256, K=4, gamma=4, B=64 (V=256000, K=16, B=256) 384 take 136 (2190) us,
+    // 256 146 (2230), 512 141 (2200), 1024 152 (2330).
+    a.max_grid = 384;
+    if (by_depth) {
+        // Each depth's rows on the side stream, its sampling on the caller's once they are
+        // streamed.
+        sd = PSD_OK;
+        for (int d = 0; d < m.gamma && sd == PSD_OK; ++d) {
+            m.stream_s = m.s = d;
+            if ((sd = mpfr_stream_rows(params, m, f.side)) != PSD_OK) break;
+            if (d == 0 && (sd = run_race(params, a, f.race)) != PSD_OK) break;
+            if ((e = hipEventRecord(f.depth[d], f.side)) != hipSuccess ||
+                (e = hipStreamWaitEvent(stream, f.depth[d], 0)) != hipSuccess)
+                sd = hip_fail(e, "depth event");
+            else
+                sd = mpfr_sample(params, m, stream);
+        }
+    } else if (m.tok_slot) {
         // One sampling launch for every depth on the caller's stream, which waits for
-        // the streamed rows' tagged words, beside the streaming launch and then the
-        // target race on the side stream (the streaming launch never waits, and both
-        // launches' workgroups fit the device together).  The streaming launch is
-        // enqueued first, so a sampling launch never waits for rows that will not come.
-        // Half as many streaming workgroups as rows (two rows each, depth-major; at least
-        // 512 or every row) land the first depths' rows sooner: 178 vs 185 us per call
-        // with one per row at V=128256, K=4, gamma=4, B=64 (384: 191 us, 256: 209 us).
-        const int rows = m.B * m.K * m.s_count;
-        m.stream_grid = std::max((rows + 1) / 2, std::min(rows, 512));
-        if ((e = hipEventRecord(f.in, stream)) != hipSuccess) return hip_fail(e, "fork event record");
-        if ((e = hipStreamWaitEvent(f.side, f.in, 0)) != hipSuccess) return hip_fail(e, "fork event wait");
-        if ((st = mpfr_stream_rows(params, m, f.side)) != PSD_OK) return st;
-        // from here on the join is always enqueued, so the caller's stream never runs
-        // ahead of the side stream
-        sd = mpfr_sample_depths(params, m, stream);
-        if (sd == PSD_OK) sd = run_race(params, a, f.side);
+        // the streamed rows' tagged words, beside the streaming launch (which never
+        // waits; both launches' workgroups fit the device together).  The streaming launch
+        // is enqueued first, so a sampling launch never waits for rows that will not come.
+        sd = mpfr_stream_rows(params, m, f.side);
+        if (sd == PSD_OK) sd = mpfr_sample(params, m, stream);
+        if (sd == PSD_OK) sd = run_race(params, a, f.race);
     } else {
-        // The streaming pass (when there is one) first, on the caller's stream: the race
-        // kernel, whose streaming workgroups would otherwise hold the device while it
-        // runs, then overlaps only the depth launches (236 vs 256 us per call at
-        // V=128256, K=4, gamma=4, B=64 with one launch per depth).
-        if (streamed && (st = mpfr_stream_rows(params, m, stream)) != PSD_OK) return st;
-        if ((e = hipEventRecord(f.in, stream)) != hipSuccess) return hip_fail(e, "fork event record");
-        if ((e = hipStreamWaitEvent(f.side, f.in, 0)) != hipSuccess) return hip_fail(e, "fork event wait");
-        if ((st = run_race(params, a, f.side)) != PSD_OK) return st;
-        // from here on the join is always enqueued, so the caller's stream never runs
-        // ahead of the side stream's race
-        sd = mpfr_sample_depths(params, m, stream);
+        sd = mpfr_stream_rows(params, m, stream);
+        if (sd == PSD_OK) sd = run_race(params, a, f.race);
+        if (sd == PSD_OK) sd = mpfr_sample_depths(params, m, stream);
     }
-    if ((e = hipEventRecord(f.out, f.side)) != hipSuccess) return hip_fail(e, "join event record");
-    if ((e = hipStreamWaitEvent(stream, f.out, 0)) != hipSuccess) return hip_fail(e, "join event wait");
+    if ((e = hipEventRecord(f.out, f.side)) != hipSuccess || (e = hipEventRecord(f.raced, f.race)) != hipSuccess)
+        return hip_fail(e, "join event record");
+    if ((e = hipStreamWaitEvent(stream, f.out, 0)) != hipSuccess ||
+        (e = hipStreamWaitEvent(stream, f.raced, 0)) != hipSuccess)
+        return hip_fail(e, "join event wait");
     if (sd != PSD_OK) return sd;
     psd::TopkRaceArgs w;
     memset(&w, 0, sizeof w);

@@ -234,16 +234,43 @@ __device__ __forceinline__ double flat_clock_f64(uint32_t slot, uint32_t v, uint
 
 // ---------------------------------------------------------------- lane reductions
 
+// A lane's value moved within its 16-lane DPP row.  Every source lane exists (quad
+// permutations and mirrors), so the bound control changes nothing but lets the move
+// fold into the instruction that uses it.
+template <int CTRL>
+__device__ __forceinline__ float dpp_row(float x) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xF, 0xF, true));
+}
+
 // Max over each 16-lane DPP row; every lane of the row receives the result.
 __device__ __forceinline__ float row16_max(float x) {
-    int v = __float_as_int(x);
-    x = fmaxf(x, __int_as_float(__builtin_amdgcn_update_dpp(v, v, 0xB1, 0xF, 0xF, false)));  // quad [1,0,3,2]
-    v = __float_as_int(x);
-    x = fmaxf(x, __int_as_float(__builtin_amdgcn_update_dpp(v, v, 0x4E, 0xF, 0xF, false)));  // quad [2,3,0,1]
-    v = __float_as_int(x);
-    x = fmaxf(x, __int_as_float(__builtin_amdgcn_update_dpp(v, v, 0x141, 0xF, 0xF, false)));  // row_half_mirror
-    v = __float_as_int(x);
-    x = fmaxf(x, __int_as_float(__builtin_amdgcn_update_dpp(v, v, 0x140, 0xF, 0xF, false)));  // row_mirror
+    x = fmaxf(x, dpp_row<0xB1>(x));   // quad [1,0,3,2]
+    x = fmaxf(x, dpp_row<0x4E>(x));   // quad [2,3,0,1]
+    x = fmaxf(x, dpp_row<0x141>(x));  // row_half_mirror
+    x = fmaxf(x, dpp_row<0x140>(x));  // row_mirror
+    return x;
+}
+
+// The same for N values at once, step by step over all of them: a DPP operand must be two
+// instructions old, so one value's steps on their own wait between each other.
+template <int N>
+__device__ __forceinline__ void row16_max_n(float (&x)[N]) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) x[i] = fmaxf(x[i], dpp_row<0xB1>(x[i]));
+#pragma unroll
+    for (int i = 0; i < N; ++i) x[i] = fmaxf(x[i], dpp_row<0x4E>(x[i]));
+#pragma unroll
+    for (int i = 0; i < N; ++i) x[i] = fmaxf(x[i], dpp_row<0x141>(x[i]));
+#pragma unroll
+    for (int i = 0; i < N; ++i) x[i] = fmaxf(x[i], dpp_row<0x140>(x[i]));
+}
+
+// Sum over each 16-lane DPP row; every lane of the row receives the same sum.
+__device__ __forceinline__ float row16_sum(float x) {
+    x += dpp_row<0xB1>(x);
+    x += dpp_row<0x4E>(x);
+    x += dpp_row<0x141>(x);
+    x += dpp_row<0x140>(x);
     return x;
 }
 
@@ -259,16 +286,42 @@ __device__ __forceinline__ uint32_t wave_incl_sum(uint32_t v) {
     return v;
 }
 
-__device__ __forceinline__ float row16_min(float x) {
-    int v = __float_as_int(x);
-    x = fminf(x, __int_as_float(__builtin_amdgcn_update_dpp(v, v, 0xB1, 0xF, 0xF, false)));
-    v = __float_as_int(x);
-    x = fminf(x, __int_as_float(__builtin_amdgcn_update_dpp(v, v, 0x4E, 0xF, 0xF, false)));
-    v = __float_as_int(x);
-    x = fminf(x, __int_as_float(__builtin_amdgcn_update_dpp(v, v, 0x141, 0xF, 0xF, false)));
-    v = __float_as_int(x);
-    x = fminf(x, __int_as_float(__builtin_amdgcn_update_dpp(v, v, 0x140, 0xF, 0xF, false)));
-    return x;
+// ---------------------------------------------------------------- running sum of exponentials
+
+// sum of exp2(x - m) over a lane's values in fp32, with a reference m that is raised
+// only when a value exceeds it by more than kRefSlack: the terms then stay below
+// 2^kRefSlack and their sum far below the float range, and the sum's relative precision
+// does not depend on the reference.  (Raising it to every new maximum costs an
+// exponential and four more instructions per 8 values.)
+constexpr float kNegBig = -1e30f;   // finite stand-in for the reference of no value (no inf - inf)
+constexpr float kRefSlack = 60.f;
+
+struct ExpSum {
+    float m, s;
+};
+// Before terms up to t are added; wave-uniform branch.
+__device__ __forceinline__ void expsum_raise(ExpSum& e, float t) {
+    if (__ballot(t > e.m + kRefSlack) != 0u) {
+        const float n = t > e.m + kRefSlack ? t : e.m;
+        e.s *= __builtin_amdgcn_exp2f(e.m - n);
+        e.m = n;
+    }
+}
+// Eight terms exp2(x c2 - m).
+__device__ __forceinline__ void expsum_add8(ExpSum& e, const float (&x)[8], float c2) {
+    float v[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = __builtin_amdgcn_exp2f(fmaf(x[i], c2, -e.m));
+    e.s += ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
+}
+// The wave's sum relative to its maximum M (at least kNegBig) of the lanes' t.
+__device__ __forceinline__ float expsum_wave(const ExpSum& e, float t, float& M) {
+    float m = row16_max(fmaxf(t, kNegBig));
+    m = fmaxf(m, __shfl_xor(m, 16));
+    M = fmaxf(m, __shfl_xor(m, 32));
+    float s = row16_sum(e.s * __builtin_amdgcn_exp2f(e.m - M));
+    s += __shfl_xor(s, 16);
+    return s + __shfl_xor(s, 32);
 }
 
 // Order-preserving map float -> int (for integer atomic min on scores).

@@ -58,17 +58,18 @@ struct MpfrArgs {
     int V, K, m, B, gamma;
     int s_begin, s_count, s;    // depth of this launch: s_begin <= s < s_begin + s_count
     float T, invT;
-    // Written by the streaming launch and read by the sampling launches, each word
-    // (epoch << 32) | payload (draft row ids): a sampling launch that runs every depth
-    // may run beside the streaming launch and waits for the tags.
+    // Written by the streaming launches and read by the sampling launches (draft row ids).
+    // With tok_slot each word is (epoch << 32) | payload: a sampling launch that runs every
+    // depth may run beside the streaming launch and waits for the tags.  Otherwise the
+    // streams order the launches and the tag is 0.  row_max and row_seed may be null: the
+    // sampling launches then find both from the group maxima.
     uint64_t* row_gm;           // [B*K*gamma][groups] group maxima of the draft rows (float bits)
     uint64_t* row_max;          // [B*K*gamma] their maxima (float bits)
     uint64_t* row_seed;         // [B*K*gamma][8] their seed tokens (-1: none)
     uint64_t* tok_slot;         // nullable [B*K*gamma]: the drafts of a launch that runs every
                                 // depth, as (epoch << 32) | token, for the later depths' waits
     uint32_t spin_limit;        // polls of a bounded wait before it gives up
-    int stream_records_epoch;   // the streaming launch records its epoch (no sampling launch
-                                // that runs every depth follows it to do so)
+    int stream_s, stream_n;     // depths of a streaming launch: [stream_s, stream_s + stream_n)
     int stream_grid;            // workgroups of the streaming launch (0: one per row); each
                                 // streams rows blockIdx.x, blockIdx.x + grid, ... (depth-major)
 };
@@ -80,13 +81,13 @@ struct MpfrLayout {
     size_t gm, rmax, seed, slot, ytok, total;
 };
 // Identical-drafter calls with fewer than this many (sequence, path) workgroups per
-// depth stream their draft rows in a launch of their own; larger ones stream each
-// depth's rows in its sampling launch.
+// depth stream every draft row in one launch, whose words have a region of their own;
+// larger ones stream each depth in a launch, into the draft rows' group slots of the
+// race kernel (which such a call does not use, tag 0 matching no call's epoch).
 constexpr long kMpfrStreamBelow = 1024;
 
 inline MpfrLayout mpfr_layout(const WsLayout& L, int B, int K, int gamma) {
     MpfrLayout M;
-    // the streamed rows' words exist only when the call has a streaming launch
     const size_t rows = (long)B * K < kMpfrStreamBelow ? (size_t)B * K * gamma : 0;
     M.gm = L.total;
     M.rmax = align256(M.gm + rows * (size_t)L.ng * 8);
@@ -210,11 +211,9 @@ hipError_t launch_topk_race(const TopkRaceArgs& a, int layout, hipStream_t strea
 hipError_t launch_walk(const TopkRaceArgs& a, hipStream_t stream);
 
 hipError_t launch_race(const RaceArgs& a, bool bf16, int layout, hipStream_t stream);
-// The sampling of depths [s_begin, s_begin + s_count): one launch that runs every
-// depth when the drafts can be handed over in tagged slots (tok_slot set, more than
-// one depth) and every workgroup of it can be resident at once, else one launch per
-// depth.
-hipError_t launch_mpfr_depths(MpfrArgs a, bool bf16, int layout, hipStream_t stream);
+// A sampling launch: of every depth when the drafts are handed over in tagged slots
+// (tok_slot set; the caller checked mpfr_all_depths_fit), else of depth a.s.
+hipError_t launch_mpfr_sample(const MpfrArgs& a, bool bf16, int layout, hipStream_t stream);
 // Whether one sampling launch can run every depth of a: more than one depth, and all
 // B K workgroups resident together.  *fits is set; a HIP error of the query is returned.
 hipError_t mpfr_all_depths_fit(const MpfrArgs& a, bool bf16, int layout, bool* fits);

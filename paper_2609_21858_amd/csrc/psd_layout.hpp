@@ -116,6 +116,7 @@ struct RaceArgs {
     int walk_kind, walk_s, walk_k;
     uint32_t* status;     // nullable: this call's error bits, written by its last workgroup
     uint32_t spin_limit;  // polls of a bounded wait before it gives up (psd_set_spin_limit)
+    int max_grid;         // most workgroups of the launch (0: as many as fit the device)
 };
 
 }  // namespace psd

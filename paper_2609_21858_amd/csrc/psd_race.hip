@@ -340,9 +340,6 @@ __device__ __forceinline__ void lse_combine(float& m, float& s, float om, float 
     m = mn;
 }
 
-// Running maxima start at a finite sentinel, so that rescaling never meets inf - inf.
-constexpr float kNegBig = -1e30f;
-
 __device__ __forceinline__ void lse_merge_finite(float& m, float& s, float om, float os) {
     const float mn = fmaxf(m, om);
     s = s * __builtin_amdgcn_exp2f(m - mn) + os * __builtin_amdgcn_exp2f(om - mn);
@@ -401,6 +398,9 @@ __device__ __forceinline__ void consume_segment(const RaceArgs& a, const Row& r,
         const float um = fmaxf(fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])), fmaxf(fmaxf(x[4], x[5]), fmaxf(x[6], x[7])));
         const float g = row16_max(um);
         if ((lane & 15) == 0) sm.gst[p][q * 16 + (tid >> 4)] = g;
+        // (the reference is raised to every new maximum: a branch around that, as in the
+        // identical-drafter streaming pass, splits the loop in which the loads are waited for
+        // one by one: 118 vs 95 us per call at V = 128256, K = 4, B = 64)
         const float mn = fmaxf(mrun, um * c2);
         float acc = srun * __builtin_amdgcn_exp2f(mrun - mn);
 #pragma unroll
@@ -1846,6 +1846,7 @@ hipError_t launch_one(const RaceArgs& a, hipStream_t stream) {
     // both kinds of workgroup: at least kRolePeriod blocks
     long grid = (long)per_cu * cus;
     if (grid > (long)kRolePeriod * a.n_items) grid = (long)kRolePeriod * a.n_items;
+    if (a.max_grid > 0 && grid > a.max_grid) grid = a.max_grid;
     if (grid < kRolePeriod) grid = kRolePeriod;
     hipLaunchKernelGGL(fn, dim3((unsigned)grid), dim3(kBlock), smem, stream, a);
     return hipGetLastError();

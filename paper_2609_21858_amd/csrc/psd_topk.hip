@@ -238,15 +238,19 @@ __device__ __forceinline__ void stream_group_max(SelShared& sm, const unsigned c
                 }
             }
         }
+        float mx[kUnroll];
 #pragma unroll
         for (int u = 0; u < kUnroll; ++u) {
-            float mx = __uint_as_float(elem_bits<BF16>(wv[u], 0));
+            mx[u] = __uint_as_float(elem_bits<BF16>(wv[u], 0));
 #pragma unroll
-            for (int i = 1; i < EPT; ++i) mx = fmaxf(mx, __uint_as_float(elem_bits<BF16>(wv[u], i)));
-            mx = row16_max(mx);
-            if (LPG == 32) mx = fmaxf(mx, __shfl_xor(mx, 16));
+            for (int i = 1; i < EPT; ++i) mx[u] = fmaxf(mx[u], __uint_as_float(elem_bits<BF16>(wv[u], i)));
+        }
+        row16_max_n<kUnroll>(mx);
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) {
+            if (LPG == 32) mx[u] = fmaxf(mx[u], __shfl_xor(mx[u], 16));
             const int g = (c0 + u * kWaves) * (WCH / kGroupTokens) + lane / LPG;
-            if (lane % LPG == 0 && g < ng) sm.u.gm[g] = mx;
+            if (lane % LPG == 0 && g < ng) sm.u.gm[g] = mx[u];
         }
     }
 }
@@ -1013,7 +1017,9 @@ __global__ __launch_bounds__(64 * (kChainWaves + 1)) void topk_chain_kernel(Topk
     __shared__ ChainShared sm;
     const int K = a.K, G = a.gamma;
     const int nd = a.s_count > 0 ? K : 0, R = nd + (a.target_rows == 1 ? 1 : 0);
-    const int b = (int)blockIdx.x / R, r = (int)blockIdx.x % R;
+    // chain-major, the target chains (the longest) first: each kind of chain spreads over
+    // the XCDs, which consecutive workgroups go to in turn
+    const int b = (int)blockIdx.x % a.B, r = R - 1 - (int)blockIdx.x / a.B;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int64_t t0 = a.start_pos[b];
     const int d_end = a.s_begin + a.s_count;
