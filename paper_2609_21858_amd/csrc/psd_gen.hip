@@ -34,6 +34,8 @@
 
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "psd_launch.hpp"
 
 // The toy rows' definition rounds every product and sum once: no contraction into
@@ -60,15 +62,6 @@ __device__ __forceinline__ uint32_t lowbias32(uint32_t x) {
     return x;
 }
 
-__device__ __forceinline__ uint32_t gcd32(uint32_t a, uint32_t b) {
-    while (b) {
-        const uint32_t t = a % b;
-        a = b;
-        b = t;
-    }
-    return a;
-}
-
 // Sum of the two (q + 1/2) / 2^16 uniforms held in the halves of h (exact in fp32).
 __device__ __forceinline__ float two_uniforms(uint32_t h) {
     return ((float)(h & 0xFFFFu) + (float)(h >> 16) + 1.0f) * 0x1p-16f;
@@ -79,8 +72,51 @@ __device__ __forceinline__ uint16_t bf16_rne(float f) {
     return (uint16_t)((u + 0x7FFFu + ((u >> 16) & 1u)) >> 16);
 }
 
-// One workgroup per (sequence b, depth s): the target row at t = start[b] + s and,
-// for s < gamma, the K draft rows of that depth.
+// 8 consecutive logits of a row from element `at` (any alignment: one or two 16-byte
+// stores), the row's last ones singly.
+typedef uint32_t u32x4_f32 __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t u32x4_b16 __attribute__((ext_vector_type(4), aligned(2)));
+template <bool BF16>
+__device__ __forceinline__ void store8(void* rows, size_t at, int n, const float (&z)[8]) {
+    if constexpr (BF16) {
+        uint16_t* p = (uint16_t*)rows + at;
+        uint16_t h[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) h[i] = bf16_rne(z[i]);
+        if (n >= 8) {
+            u32x4_b16 w;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) w[i] = (uint32_t)h[2 * i] | ((uint32_t)h[2 * i + 1] << 16);
+            *(u32x4_b16*)p = w;
+        } else {
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                if (i < n) p[i] = h[i];
+        }
+    } else {
+        float* p = (float*)rows + at;
+        if (n >= 8) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                u32x4_f32 w;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) w[i] = __float_as_uint(z[4 * h + i]);
+                *(u32x4_f32*)(p + 4 * h) = w;
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                if (i < n) p[i] = z[i];
+        }
+    }
+}
+
+// gridDim.y workgroups per (sequence b, depth s): the target row at t = start[b] + s and,
+// for s < gamma, the K draft rows of that depth, 8 consecutive tokens per thread.
+// Bound by integer arithmetic (about 24 issue slots per logit, two 32-bit products
+// among them), so the rows are split over enough workgroups to fill the device
+// (13.3 M logits at V = 32000, K = 4, gamma = 5, B = 16: 19 us; one workgroup per
+// (b, s), a thread per token and a gcd per thread took 54 us).
 template <bool BF16>
 __global__ __launch_bounds__(256) void toy_rows_kernel(ToyArgs a) {
     const int G1 = a.gamma + 1;
@@ -92,7 +128,13 @@ __global__ __launch_bounds__(256) void toy_rows_kernel(ToyArgs a) {
     const uint32_t c = (uint32_t)(RP % V);
     uint32_t am = (uint32_t)((RP >> 32) % V);
     if (am == 0u) am = 1u;
-    while (gcd32(am, V) != 1u) am = am + 1u == V ? 1u : am + 1u;
+    // up to the first multiplier coprime to V: divisible by none of V's prime factors
+    for (;;) {
+        bool coprime = true;
+        for (int i = 0; i < a.n_primes; ++i) coprime = coprime && am % a.primes[i] != 0u;
+        if (coprime) break;
+        am = am + 1u == V ? 1u : am + 1u;
+    }
     const float tau = b < a.tau_split ? a.tau0 : a.tau1;
     const bool drafts = s < a.gamma && a.draft_logits;
     __shared__ uint32_t rd[32];  // lo32(R_D) of each drafter at this (b, t)
@@ -101,30 +143,37 @@ __global__ __launch_bounds__(256) void toy_rows_kernel(ToyArgs a) {
                                                              ((uint64_t)b << 32) ^ (t & 0xFFFFFFFFull)));
     __syncthreads();
     const size_t trow = ((size_t)b * G1 + s) * V;
-    // r(v) stepped along this thread's stride: r(v + stride) = r(v) + a * stride (mod V)
-    uint32_t r = (uint32_t)(((uint64_t)am * threadIdx.x + c) % V);
-    const uint32_t step = (uint32_t)(((uint64_t)am * blockDim.x) % V);
-    for (uint32_t v = threadIdx.x; v < V; v += blockDim.x) {
-        const uint32_t x = (uint32_t)RT + v * 0x9E3779B9u;
-        const float u4 = two_uniforms(lowbias32(x)) + two_uniforms(lowbias32(x ^ (uint32_t)(RT >> 32)));
-        const float n = __fmul_rn(u4 - 2.0f, 1.7320508075688772f);
-        const float q = (float)(int32_t)(__float_as_uint((float)(r + 1u)) - 0x3F800000u);
-        const float z = __fadd_rn(__fmul_rn(a.sigma, n), __fmul_rn(a.w, q));
-        r += step;
-        if (r >= V) r -= V;
-        if (BF16)
-            ((uint16_t*)a.target_logits)[trow + v] = bf16_rne(z);
-        else
-            ((float*)a.target_logits)[trow + v] = z;
+    const uint32_t stride = 8u * blockDim.x * gridDim.y;
+    uint32_t v0 = 8u * (blockIdx.y * blockDim.x + threadIdx.x);
+    // r(v) stepped along this thread's tokens: r(v + d) = r(v) + a d (mod V)
+    uint32_t r0 = (uint32_t)(((uint64_t)am * v0 + c) % V);
+    const uint32_t step = (uint32_t)(((uint64_t)am * stride) % V);
+    for (; v0 < V; v0 += stride) {
+        float z[8];
+        uint32_t r = r0;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const uint32_t x = (uint32_t)RT + (v0 + (uint32_t)i) * 0x9E3779B9u;
+            const float u4 = two_uniforms(lowbias32(x)) + two_uniforms(lowbias32(x ^ (uint32_t)(RT >> 32)));
+            const float n = __fmul_rn(u4 - 2.0f, 1.7320508075688772f);
+            const float q = (float)(int32_t)(__float_as_uint((float)(r + 1u)) - 0x3F800000u);
+            z[i] = __fadd_rn(__fmul_rn(a.sigma, n), __fmul_rn(a.w, q));
+            r += am;
+            if (r >= V) r -= V;
+        }
+        r0 += step;
+        if (r0 >= V) r0 -= V;
+        const int n = (int)min(V - v0, 8u);
+        store8<BF16>(a.target_logits, trow + v0, n, z);
         if (!drafts) continue;
         for (int k = 0; k < a.K; ++k) {
-            const float n2 = __fmul_rn(two_uniforms(lowbias32(rd[k] + v * 0x9E3779B9u)) - 1.0f, 2.449489742783178f);
-            const float d = __fadd_rn(z, __fmul_rn(tau, n2));
-            const size_t drow = (((size_t)b * a.K + k) * a.gamma + s) * V;
-            if (BF16)
-                ((uint16_t*)a.draft_logits)[drow + v] = bf16_rne(d);
-            else
-                ((float*)a.draft_logits)[drow + v] = d;
+            float d[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const float n2 = __fmul_rn(two_uniforms(lowbias32(rd[k] + (v0 + (uint32_t)i) * 0x9E3779B9u)) - 1.0f, 2.449489742783178f);
+                d[i] = __fadd_rn(z[i], __fmul_rn(tau, n2));
+            }
+            store8<BF16>(a.draft_logits, (((size_t)b * a.K + k) * a.gamma + s) * V + v0, n, d);
         }
     }
 }
@@ -172,13 +221,25 @@ __global__ __launch_bounds__(kAdvBlock) void advance_kernel(AdvanceArgs a) {
 
 }  // namespace
 
-hipError_t launch_toy_rows(const ToyArgs& a, bool bf16, hipStream_t stream) {
-    const long blocks = (long)a.B * (a.gamma + 1);
-    if (blocks <= 0) return hipSuccess;
+hipError_t launch_toy_rows(const ToyArgs& args, bool bf16, hipStream_t stream) {
+    const long rows = (long)args.B * (args.gamma + 1);
+    if (rows <= 0) return hipSuccess;
+    ToyArgs a = args;
+    a.n_primes = 0;
+    int rest = a.V;
+    for (int p = 2; p * p <= rest; ++p) {
+        if (rest % p) continue;
+        a.primes[a.n_primes++] = (uint32_t)p;
+        while (rest % p == 0) rest /= p;
+    }
+    if (rest > 1) a.primes[a.n_primes++] = (uint32_t)rest;
+    // 2048 tokens per workgroup step; enough workgroups for 8 per CU, at most one step each
+    const long steps = (a.V + 2047) / 2048, want = (2048 + rows - 1) / rows;
+    const dim3 grid((unsigned)rows, (unsigned)std::min(steps, std::max(1L, want)));
     if (bf16)
-        hipLaunchKernelGGL(toy_rows_kernel<true>, dim3((unsigned)blocks), dim3(256), 0, stream, a);
+        hipLaunchKernelGGL(toy_rows_kernel<true>, grid, dim3(256), 0, stream, a);
     else
-        hipLaunchKernelGGL(toy_rows_kernel<false>, dim3((unsigned)blocks), dim3(256), 0, stream, a);
+        hipLaunchKernelGGL(toy_rows_kernel<false>, grid, dim3(256), 0, stream, a);
     return hipGetLastError();
 }
 

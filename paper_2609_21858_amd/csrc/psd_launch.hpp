@@ -185,6 +185,8 @@ struct ToyArgs {
     float tau0, tau1;    // draft noise of sequences b < tau_split, and of the others
     int tau_split;
     int V, K, B, gamma;
+    uint32_t primes[8];  // V's distinct prime factors (V <= 2^19 has at most 7; set by the launcher)
+    int n_primes;
 };
 
 // Commit one block's emitted tokens into the texts (out_len NULL: first block, from
