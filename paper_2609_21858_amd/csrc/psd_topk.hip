@@ -175,11 +175,29 @@ __device__ __forceinline__ double block_incl_sum_f64(SelShared& sm, double x, do
 // ---------------------------------------------------------------- one-wave selection
 
 // The need-th largest key class t of Q keys per lane (0: no entry) with the wave's
-// ballots alone (no barrier): largest t (bits below kLow clear) with #{key >= t} >= need.
+// ballots alone (no barrier): largest t (bits below kLow clear) with #{key >= t} >= need
+// (0 if there are fewer keys).  t lies between the smallest and the largest key, so it
+// has their common leading bits and the search starts below them.
 template <int Q, int kLow>
 __device__ __forceinline__ uint32_t wave_kth_class(const uint32_t (&kk)[Q], int need) {
-    uint32_t t = 0u;
-    for (int bit = 31; bit >= kLow; --bit) {
+    uint32_t mx = 0u, mn = 0xFFFFFFFFu;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        mx = max(mx, kk[q]);
+        mn = min(mn, kk[q] ? kk[q] : 0xFFFFFFFFu);
+    }
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        mx = max(mx, (uint32_t)__shfl_xor((int)mx, o));
+        mn = min(mn, (uint32_t)__shfl_xor((int)mn, o));
+    }
+    mx = (uint32_t)__builtin_amdgcn_readfirstlane((int)mx);
+    mn = (uint32_t)__builtin_amdgcn_readfirstlane((int)mn);
+    if (wave_count<Q>([&](int q) { return kk[q] != 0u; }) < need) return 0u;
+    if (mx == mn) return mx >> kLow << kLow;
+    const int top = 31 - __builtin_clz(mx ^ mn);  // the highest bit they differ in
+    uint32_t t = (uint32_t)((uint64_t)mx >> (top + 1) << (top + 1)) >> kLow << kLow;
+    for (int bit = top; bit >= kLow; --bit) {
         const uint32_t cand = t | (1u << bit);
         if (wave_count<Q>([&](int q) { return kk[q] >= cand; }) >= need) t = cand;
     }
@@ -255,6 +273,20 @@ __device__ __forceinline__ void stream_group_max(SelShared& sm, const unsigned c
     }
 }
 
+// The top_k-th largest 16-bit key class of ng <= 64 Q group maxima, by one wave.
+template <int Q>
+__device__ __forceinline__ uint32_t group_threshold(const float* gm, int ng, int top_k) {
+    const int lane = threadIdx.x & 63;
+    uint32_t kw[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        const int g = lane + 64 * q;
+        const float m = g < ng ? gm[g] : -INFINITY;
+        kw[q] = m >= -3.40282347e38f ? key_f32(__float_as_uint(m)) : 0u;
+    }
+    return wave_kth_class<Q, 16>(kw, top_k);
+}
+
 // The candidates of the row's top-k set, without a per-logit pass over the row: t =
 // the top_k-th largest key class among the group maxima (a bisection with ballot
 // counts, in one wave when it holds every group maximum, else block-wide), so
@@ -285,24 +317,18 @@ __device__ __forceinline__ bool select_candidates(SelShared& sm, const unsigned 
     }
     int it = 0;
     uint32_t t = 0u;
-    constexpr int QW = 16;  // group maxima per lane when one wave holds them all
-    if (ng >= top_k && ng <= 64 * QW) {
+    // (any t not above the top_k-th largest group maximum will do, so the search stops at
+    // 16-bit classes for fp32 rows too)
+    if (ng >= top_k && ng <= 1024) {
         // one wave finds t over all the group maxima; the others wait at one barrier
         if (w == 0) {
-            uint32_t kw[QW];
-#pragma unroll
-            for (int q = 0; q < QW; ++q) {
-                const int g = lane + 64 * q;
-                const float m = g < ng ? sm.u.gm[g] : -INFINITY;
-                kw[q] = m >= -3.40282347e38f ? key_f32(__float_as_uint(m)) : 0u;
-            }
-            const uint32_t tw = wave_kth_class<QW, KeyBits<BF16>::kLow>(kw, top_k);
+            const uint32_t tw = ng <= 256 ? group_threshold<4>(sm.u.gm, ng, top_k) : group_threshold<16>(sm.u.gm, ng, top_k);
             if (lane == 0) sm.tsel = tw;
         }
         __syncthreads();
         t = sm.tsel;
     } else if (ng >= top_k) {
-        for (int bit = 31; bit >= KeyBits<BF16>::kLow; --bit) {
+        for (int bit = 31; bit >= 16; --bit) {
             const uint32_t cand = t | (1u << bit);
             if (block_sum_waves(sm, wave_count<QG>([&](int q) { return fin[q] && kg[q] >= cand; }), it) >= top_k)
                 t = cand;
@@ -682,6 +708,11 @@ struct RaceShared {
     int tv[8], tj[8];
     int pre[16];          // the sequence's context window before the block (m <= 16)
     uint32_t tp[2][2];    // the shared chain's next key without its newest token (by depth parity)
+    float fin_s[8][64];   // per wave: arrivals that can be among a context's samples
+    int fin_c[8][64];
+    float ts1[8], ts2[8];  // float32 minima of a shared-chain target race, one per target wave
+    int tvj[8];
+    int tclear;            // whether they decide it
 };
 
 // Context key of the token at absolute position t whose previous tokens are the last
@@ -699,6 +730,49 @@ __device__ __forceinline__ void list_key(const TopkRaceArgs& a, const int* pre, 
         fold(k0, k1, (uint32_t)w, (uint32_t)i, 1u);
     }
 }
+
+template <int LAYOUT>
+__device__ __forceinline__ float tclock32(uint32_t V, uint32_t slot, uint32_t v, uint32_t k0, uint32_t k1) {
+    return LAYOUT == 0 ? tree_clock_f32(V, slot, v, k0, k1) : flat_clock_f32(slot, v, k0, k1);
+}
+
+// Races are decided by float32 scores where those are certain: the fp32 clocks are within
+// 1e-6 relative of the exact ones (-ln U within 1.7e-7, over all its inputs) and scores
+// use (l - l_max) / T, so a score errs by about 1e-5 and entries further apart than
+// kTMargin are in their exact order.  Closer ones are decided by the exact fp64 race
+// (about one race in a thousand).  An fp64 tree clock costs five logarithms and four
+// divisions in fp64: a depth of the shared target chain took 4.2 us with it.
+constexpr float kTMargin = 1e-3f;
+
+// The smallest score of a set of (token, slot) entries, its entry (token * 32 + slot) and
+// the second-smallest score.
+struct Best2 {
+    float s1, s2;
+    int vj;
+};
+__device__ __forceinline__ void best2_add(Best2& b, float s, int vj) {
+    if (s < b.s1) {
+        b.s2 = b.s1;
+        b.s1 = s;
+        b.vj = vj;
+    } else {
+        b.s2 = fminf(b.s2, s);
+    }
+}
+__device__ __forceinline__ void best2_merge(Best2& b, float s1, float s2, int vj) {
+    b.s2 = fminf(fminf(b.s2, s2), fmaxf(b.s1, s1));
+    if (s1 < b.s1) {
+        b.s1 = s1;
+        b.vj = vj;
+    }
+}
+__device__ __forceinline__ void best2_wave(Best2& b) {
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1)
+        best2_merge(b, __shfl_xor(b.s1, o), __shfl_xor(b.s2, o), __shfl_xor(b.vj, o));
+}
+// Whether the smallest score is certain (an empty set, or one of infinite scores, is).
+__device__ __forceinline__ bool best2_clear(const Best2& b) { return !(b.s2 - b.s1 <= kTMargin); }
 
 // The race of one row's list over slots [slot0, slot0 + nslots) -- argmin of
 // ln E_j[v] - l_v / T (exact, fp64) -- over the (token, slot) entries of 64-entry units
@@ -734,53 +808,165 @@ __device__ int wave_race(const TopkRaceArgs& a, int rid, int slot0, int nslots, 
 
 // A lane's first (token, slot) entry of a list race, loaded ahead: the list's length
 // and the token and logit of the lane's entry (its index clamped into the row's list,
-// so the loads never wait for the length and never leave the list).
+// so the loads never wait for the length and never leave the list), and the list's
+// largest logit.
 struct ListHead {
     int n, v;
-    float x;
+    float x, xmax;
 };
 
 __device__ __forceinline__ ListHead list_head(const TopkRaceArgs& a, int rid, int nslots, int part) {
     const int c = min((part * 64 + (int)(threadIdx.x & 63)) / nslots, a.cap - 1);
-    return ListHead{a.list_len[rid], a.list_tok[(size_t)rid * a.cap + c], a.list_val[(size_t)rid * a.cap + c]};
+    return ListHead{a.list_len[rid], a.list_tok[(size_t)rid * a.cap + c], a.list_val[(size_t)rid * a.cap + c],
+                    a.list_val[(size_t)rid * a.cap]};
 }
 
-// wave_race with the lane's first entry taken from h (loaded while the previous race
-// of the chain ran); later entries are loaded in place.
+// The float32 scores of the row's (token, slot) entries of 64-entry units part, part +
+// nparts, ..., by one wave; the lane's first entry is taken from h (loaded while the
+// previous race of the chain ran), xmax is the list's largest logit.
 template <int LAYOUT>
-__device__ int wave_race_h(const TopkRaceArgs& a, const ListHead& h, int rid, int slot0, int nslots, float T,
-                           uint32_t k0, uint32_t k1, int part, int nparts, double* out_s, int* out_j) {
+__device__ Best2 wave_race32(const TopkRaceArgs& a, const ListHead& h, int rid, int slot0, int nslots, float T,
+                             uint32_t k0, uint32_t k1, int part, int nparts) {
     const int lane = threadIdx.x & 63;
     const int n = h.n;
     const int* lt = a.list_tok + (size_t)rid * a.cap;
     const float* lv = a.list_val + (size_t)rid * a.cap;
-    // (token, slot) packed as token * 32 + slot (tokens < 2^19, slots < 32): the same
-    // order, one word less in each shuffle step
-    double bs = INFINITY;
-    int bvj = 0x7FFFFFFF;
+    const float invT = 1.0f / T;
+    // (token, slot) packed as token * 32 + slot (tokens < 2^19, slots < 32)
+    // (a +inf logit has no float32 score here: never certain, so the exact race decides)
+    if (n > 0 && !(h.xmax < INFINITY)) return Best2{0.f, 0.f, -1};
+    Best2 b{INFINITY, INFINITY, -1};
     for (int e = part * 64 + lane, first = 1; e < n * nslots; e += 64 * nparts, first = 0) {
         const int c = e / nslots, j = slot0 + e % nslots;
         const int v = first ? h.v : lt[c];
         const float x = first ? h.x : lv[c];
-        const double s = log(tclock<LAYOUT>((uint32_t)a.V, (uint32_t)j, (uint32_t)v, k0, k1)) - (double)x / (double)T;
-        const int vj = (v << 5) | j;
-        if (s < bs || (s == bs && vj < bvj)) {
-            bs = s;
-            bvj = vj;
-        }
+        best2_add(b, ln_f32(tclock32<LAYOUT>((uint32_t)a.V, (uint32_t)j, (uint32_t)v, k0, k1)) - (x - h.xmax) * invT,
+                  (v << 5) | j);
     }
+    best2_wave(b);
+    return b;
+}
+
+// A whole race by one wave: the winning token, -1 when the list is empty.
+template <int LAYOUT>
+__device__ int wave_race_one(const TopkRaceArgs& a, const ListHead& h, int rid, int slot0, int nslots, float T,
+                             uint32_t k0, uint32_t k1) {
+    const Best2 b = wave_race32<LAYOUT>(a, h, rid, slot0, nslots, T, k0, k1, 0, 1);
+    if (best2_clear(b)) return b.vj >= 0 ? b.vj >> 5 : -1;
+    return wave_race<LAYOUT>(a, rid, slot0, nslots, T, k0, k1);
+}
+
+// The nu MPFR samples of one context from its row's list, by one wave, when float32
+// scores decide them: theta = the nu-th smallest first-arrival score bounds the nu-th
+// smallest of all, so an entry draws arrivals only while they reach theta; the nu + 1
+// smallest are taken out one by one and have to be kTMargin apart.  fin: the wave's LDS
+// scratch of 64 scores and entries.  Returns false when they are not (or more than 64
+// arrivals reach theta).
+constexpr int kTFin = 64;
+template <int LAYOUT>
+__device__ bool wave_mpfr32(const TopkRaceArgs& a, RaceShared& sm, int w, int rid, uint32_t members, int s, float T,
+                            uint32_t k0, uint32_t k1) {
+    constexpr int Q = kMaxTopK / 64;
+    const int lane = threadIdx.x & 63;
+    const int n = a.list_len[rid];
+    const int nu = __popc(members);
+    if (n == 0) {
+        if (lane < nu) {
+            uint32_t mm = members;
+            for (int r = 0; r < lane; ++r) mm &= mm - 1u;
+            sm.path[(__ffs((int)mm) - 1) * 33 + s] = -1;
+        }
+        return true;
+    }
+    const int* lt = a.list_tok + (size_t)rid * a.cap;
+    const float* lv = a.list_val + (size_t)rid * a.cap;
+    const float invT = 1.0f / T, xmax = lv[0];
+    if (!(xmax < INFINITY)) return false;
+    float G[Q], xs[Q], sc[Q];
+    int tok[Q];
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        const double os = __shfl_xor(bs, o);
-        const int ovj = __shfl_xor(bvj, o);
-        if (os < bs || (os == bs && ovj < bvj)) {
-            bs = os;
-            bvj = ovj;
+    for (int q = 0; q < Q; ++q) {
+        const int c = lane + 64 * q;
+        tok[q] = -1;
+        xs[q] = G[q] = 0.f;
+        sc[q] = INFINITY;
+        if (c < n) {
+            tok[q] = lt[c];
+            xs[q] = (lv[c] - xmax) * invT;
+            G[q] = tclock32<LAYOUT>((uint32_t)a.V, 0u, (uint32_t)tok[q], k0, k1);
+            sc[q] = ln_f32(G[q]) - xs[q];
         }
     }
-    *out_s = bs;
-    *out_j = bs < INFINITY ? (bvj & 31) : 0x7FFFFFFF;
-    return bs < INFINITY ? (bvj >> 5) : -1;
+    // theta: nu smallest first arrivals, taken out one by one (the register copies)
+    float theta = INFINITY;
+    if (n >= nu) {
+        float t[Q];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) t[q] = sc[q];
+        for (int r = 0; r < nu; ++r) {
+            float m = fminf(fminf(t[0], t[1]), fminf(t[2], t[3]));
+            static_assert(Q == 4, "four entries per lane");
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) m = fminf(m, __shfl_xor(m, o));
+            theta = m;
+#pragma unroll
+            for (int q = 0; q < Q; ++q)
+                if (t[q] == m) t[q] = INFINITY;  // (equal scores go together: a looser theta)
+        }
+        theta += 2.f * kTMargin;
+    }
+    // every arrival up to theta
+    int cnt = 0;
+    float* fs = sm.fin_s[w];
+    int* fc = sm.fin_c[w];
+    for (int j = 0; j < nu; ++j) {
+        bool more = false;
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            if (64 * q >= n) break;  // (uniform)
+            const bool in = sc[q] <= theta && sc[q] < INFINITY;
+            const uint64_t m = __ballot(in);
+            const int pos = cnt + lanes_below(m);
+            if (in && pos < kTFin) {
+                fs[pos] = sc[q];
+                fc[pos] = tok[q];
+            }
+            cnt += (int)__popcll(m);
+            if (m != 0u && j + 1 < nu) {
+                if (in) {
+                    G[q] += tclock32<LAYOUT>((uint32_t)a.V, (uint32_t)(j + 1), (uint32_t)tok[q], k0, k1);
+                    sc[q] = ln_f32(G[q]) - xs[q];
+                } else {
+                    sc[q] = INFINITY;
+                }
+                more = true;
+            } else {
+                sc[q] = INFINITY;
+            }
+        }
+        if (!more) break;
+    }
+    if (cnt > kTFin || cnt < nu) return false;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    // rank by counting (one arrival per lane)
+    const float mine = lane < cnt ? fs[lane] : INFINITY;
+    const int mt = lane < cnt ? fc[lane] : -1;
+    int rk = 0;
+    bool near = false;
+    for (int i = 0; i < cnt; ++i) {
+        const float o = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(mine), i));
+        rk += o < mine || (o == mine && i < lane);
+        near = near || (i != lane && fabsf(o - mine) <= kTMargin);
+    }
+    if (__ballot(lane < cnt && rk < nu && near) != 0u) return false;
+    if (lane < cnt && rk < nu) {
+        uint32_t mm = members;
+        for (int r = 0; r < rk; ++r) mm &= mm - 1u;
+        sm.path[(__ffs((int)mm) - 1) * 33 + s] = mt;
+    }
+    return true;
 }
 
 // The nu MPFR samples of one context from its row's list, by one wave: the nu
@@ -882,7 +1068,8 @@ __global__ __launch_bounds__(512) void topk_race_kernel(TopkRaceArgs a) {
             for (int k = w; k < K; k += dw) {
                 if (!a.mpfr) {
                     list_key(a, sm.pre, t0 + s, &sm.path[k * 33], s, k0, k1, a.m);
-                    const int y = wave_race<LAYOUT>(a, (b * K + k) * G + s, k, 1, a.T_draft, k0, k1);
+                    const int rid = (b * K + k) * G + s;
+                    const int y = wave_race_one<LAYOUT>(a, list_head(a, rid, 1, 0), rid, k, 1, a.T_draft, k0, k1);
                     if (lane == 0) sm.path[k * 33 + s] = y;
                 } else {
                     // the context of path k: the paths with its drafts at depths < s; its
@@ -899,7 +1086,8 @@ __global__ __launch_bounds__(512) void topk_race_kernel(TopkRaceArgs a) {
                     }
                     if (!rep) continue;
                     list_key(a, sm.pre, t0 + s, &sm.path[k * 33], s, k0, k1, a.m);
-                    wave_mpfr<LAYOUT>(a, sm, (b * K + k) * G + s, members, s, a.T_draft, k0, k1);
+                    if (!wave_mpfr32<LAYOUT>(a, sm, w, (b * K + k) * G + s, members, s, a.T_draft, k0, k1))
+                        wave_mpfr<LAYOUT>(a, sm, (b * K + k) * G + s, members, s, a.T_draft, k0, k1);
                 }
             }
         }
@@ -914,13 +1102,12 @@ __global__ __launch_bounds__(512) void topk_race_kernel(TopkRaceArgs a) {
             } else {
                 list_key(a, sm.pre, t0 + s, sm.chain, s, k0, k1, a.m);
             }
-            double ps;
-            int pj;
-            const int pv = wave_race<LAYOUT>(a, D + b * (G + 1) + s, 0, tslots, a.T_target, k0, k1, ti, twv, &ps, &pj);
+            const int rid = D + b * (G + 1) + s;
+            const Best2 p = wave_race32<LAYOUT>(a, list_head(a, rid, tslots, ti), rid, 0, tslots, a.T_target, k0, k1, ti, twv);
             if (lane == 0) {
-                sm.ts[ti] = ps;
-                sm.tv[ti] = pv;
-                sm.tj[ti] = pj;
+                sm.ts1[ti] = p.s1;
+                sm.ts2[ti] = p.s2;
+                sm.tvj[ti] = p.vj;
             }
         }
         if (a.target_rows == 1 && w == 0 && a.m > 0 && s < G) {
@@ -937,24 +1124,45 @@ __global__ __launch_bounds__(512) void topk_race_kernel(TopkRaceArgs a) {
         if (per)
             for (int k = w; k < K; k += nw) {
                 list_key(a, sm.pre, t0 + s, &sm.path[k * 33], s, k0, k1, a.m);
-                const int y = wave_race<LAYOUT>(a, D + (b * K + k) * (G + 1) + s, 0, tslots, a.T_target, k0, k1);
+                const int rid = D + (b * K + k) * (G + 1) + s;
+                const int y = wave_race_one<LAYOUT>(a, list_head(a, rid, tslots, 0), rid, 0, tslots, a.T_target, k0, k1);
                 if (lane == 0) sm.pchain[k * 33 + s] = y;
             }
         __syncthreads();
         if (twv > 0) {
-            // the shared-chain target of depth s: the lexicographic minimum of the waves' parts
+            // the shared-chain target of depth s: the minimum of the waves' parts
             if (tid == 0) {
-                double bs = sm.ts[0];
-                int bv = sm.tv[0], bj = sm.tj[0];
-                for (int i = 1; i < twv; ++i)
-                    if (tlex(sm.ts[i], sm.tv[i], sm.tj[i], bs, bv, bj)) {
-                        bs = sm.ts[i];
-                        bv = sm.tv[i];
-                        bj = sm.tj[i];
-                    }
-                sm.chain[s] = bs < INFINITY ? bv : -1;
+                Best2 p{sm.ts1[0], sm.ts2[0], sm.tvj[0]};
+                for (int i = 1; i < twv; ++i) best2_merge(p, sm.ts1[i], sm.ts2[i], sm.tvj[i]);
+                sm.chain[s] = p.vj >= 0 ? p.vj >> 5 : -1;
+                sm.tclear = best2_clear(p);
             }
             __syncthreads();
+            if (!sm.tclear) {  // (uniform)
+                if (w >= dw) {
+                    double ps;
+                    int pj;
+                    const int pv = wave_race<LAYOUT>(a, D + b * (G + 1) + s, 0, tslots, a.T_target, k0, k1, w - dw, twv, &ps, &pj);
+                    if (lane == 0) {
+                        sm.ts[w - dw] = ps;
+                        sm.tv[w - dw] = pv;
+                        sm.tj[w - dw] = pj;
+                    }
+                }
+                __syncthreads();
+                if (tid == 0) {
+                    double bs = sm.ts[0];
+                    int bv = sm.tv[0], bj = sm.tj[0];
+                    for (int i = 1; i < twv; ++i)
+                        if (tlex(sm.ts[i], sm.tv[i], sm.tj[i], bs, bv, bj)) {
+                            bs = sm.ts[i];
+                            bv = sm.tv[i];
+                            bj = sm.tj[i];
+                        }
+                    sm.chain[s] = bs < INFINITY ? bv : -1;
+                }
+                __syncthreads();
+            }
         }
     }
     if (a.s_count > 0)
@@ -1005,7 +1213,10 @@ __global__ __launch_bounds__(512) void topk_race_kernel(TopkRaceArgs a) {
 struct ChainShared {
     int path[33];          // this workgroup's chain: drafts of one path, or the targets
     int pre[16];           // the sequence's context window before the block (m <= 16)
-    double ts[4];          // partial minima of a target race, one per wave
+    float ts1[4], ts2[4];  // float32 minima of a target race, one per wave
+    int tvj[4];
+    int tclear;            // whether they decide it
+    double ts[4];          // exact partial minima of a target race, one per wave
     int tv[4], tj[4];
     uint32_t tp[2][2];     // the chain's next key without its newest token (by depth parity)
 };
@@ -1038,9 +1249,7 @@ __global__ __launch_bounds__(64 * (kChainWaves + 1)) void topk_chain_kernel(Topk
             list_key(a, sm.pre, t0 + s, sm.path, s, k0, k1, a.m);
             const ListHead hs = h;
             if (s + 1 < d_end) h = list_head(a, (b * K + k) * G + s + 1, 1, 0);  // the next depth's, in flight
-            double ps;
-            int pj;
-            sm.path[s] = wave_race_h<LAYOUT>(a, hs, (b * K + k) * G + s, k, 1, a.T_draft, k0, k1, 0, 1, &ps, &pj);
+            sm.path[s] = wave_race_one<LAYOUT>(a, hs, (b * K + k) * G + s, k, 1, a.T_draft, k0, k1);
         }
         for (int s = a.s_begin + lane; s < d_end; s += 64) a.draft_tokens[((size_t)b * K + k) * G + s] = sm.path[s];
         return;
@@ -1063,6 +1272,10 @@ __global__ __launch_bounds__(64 * (kChainWaves + 1)) void topk_chain_kernel(Topk
             }
             __syncthreads();
             __syncthreads();
+            if (!sm.tclear) {
+                __syncthreads();
+                __syncthreads();
+            }
             continue;
         }
         if (s > 0 && a.m > 0) {
@@ -1074,27 +1287,43 @@ __global__ __launch_bounds__(64 * (kChainWaves + 1)) void topk_chain_kernel(Topk
         }
         const ListHead hs = h;
         if (s < G) h = list_head(a, trow + s + 1, tslots, w);  // the next depth's, in flight
-        double ps;
-        int pj;
-        const int pv = wave_race_h<LAYOUT>(a, hs, trow + s, 0, tslots, a.T_target, k0, k1, w, kChainWaves, &ps, &pj);
+        const Best2 p = wave_race32<LAYOUT>(a, hs, trow + s, 0, tslots, a.T_target, k0, k1, w, kChainWaves);
         if (lane == 0) {
-            sm.ts[w] = ps;
-            sm.tv[w] = pv;
-            sm.tj[w] = pj;
+            sm.ts1[w] = p.s1;
+            sm.ts2[w] = p.s2;
+            sm.tvj[w] = p.vj;
         }
         __syncthreads();
         if (tid == 0) {
-            double bs = sm.ts[0];
-            int bv = sm.tv[0], bj = sm.tj[0];
-            for (int i = 1; i < kChainWaves; ++i)
-                if (tlex(sm.ts[i], sm.tv[i], sm.tj[i], bs, bv, bj)) {
-                    bs = sm.ts[i];
-                    bv = sm.tv[i];
-                    bj = sm.tj[i];
-                }
-            sm.path[s] = bs < INFINITY ? bv : -1;
+            Best2 q{sm.ts1[0], sm.ts2[0], sm.tvj[0]};
+            for (int i = 1; i < kChainWaves; ++i) best2_merge(q, sm.ts1[i], sm.ts2[i], sm.tvj[i]);
+            sm.path[s] = q.vj >= 0 ? q.vj >> 5 : -1;
+            sm.tclear = best2_clear(q);
         }
         __syncthreads();
+        if (!sm.tclear) {  // (uniform)
+            double ps;
+            int pj;
+            const int pv = wave_race<LAYOUT>(a, trow + s, 0, tslots, a.T_target, k0, k1, w, kChainWaves, &ps, &pj);
+            if (lane == 0) {
+                sm.ts[w] = ps;
+                sm.tv[w] = pv;
+                sm.tj[w] = pj;
+            }
+            __syncthreads();
+            if (tid == 0) {
+                double bs = sm.ts[0];
+                int bv = sm.tv[0], bj = sm.tj[0];
+                for (int i = 1; i < kChainWaves; ++i)
+                    if (tlex(sm.ts[i], sm.tv[i], sm.tj[i], bs, bv, bj)) {
+                        bs = sm.ts[i];
+                        bv = sm.tv[i];
+                        bj = sm.tj[i];
+                    }
+                sm.path[s] = bs < INFINITY ? bv : -1;
+            }
+            __syncthreads();
+        }
     }
     for (int s = tid; s <= G; s += blockDim.x) {
         a.chain[(size_t)b * (G + 1) + s] = sm.path[s];
