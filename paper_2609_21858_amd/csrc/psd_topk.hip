@@ -38,7 +38,9 @@ namespace psd {
 namespace {
 
 constexpr int kTBlock = 256;
-constexpr int kUnroll = 4;  // 16-byte loads in flight per thread
+constexpr int kUnroll = 4;        // candidate groups in flight per thread
+constexpr int kStreamUnroll = 8;  // 16-byte loads in flight per thread of the streaming pass (4: 130 vs 123 us per
+                                  // top-k 50 call at V = 128256, K = 4, B = 64)
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 // 16 bytes at any element boundary in one load (rows of an odd vocabulary start off
 // the 16-byte grid).
@@ -76,8 +78,13 @@ struct SelShared {
         int hist[2048];         // radix passes (the candidates are given up first)
         float gm[kMaxGroups];   // group maxima of the streaming pass
     } u;
-    int tok[kMaxTopK];
-    float val[kMaxTopK];
+    union {
+        struct {
+            int tok[kMaxTopK];
+            float val[kMaxTopK];
+        };
+        __align__(16) uint64_t comp[kTBlock];  // candidates being ranked
+    };
     union {
         struct {
             int stok[kMaxTopK];
@@ -219,19 +226,19 @@ __device__ __forceinline__ uint32_t elem_bits(const uint32_t (&w)[4], int i) {
 }
 
 // Group maxima of the row (128-token groups) into sm.u.gm: one wave per 64 x EPT-token
-// chunk in turn (wave w takes chunks w, w + 4, ...; four 16-byte loads per lane in
+// chunk in turn (wave w takes chunks w, w + 4, ...; eight 16-byte loads per lane in
 // flight), the maximum of each lane's tokens, then of the lanes of a group.  Only a
 // maximum per token: the pass costs little more than reading the row.
 template <bool BF16>
 __device__ __forceinline__ void stream_group_max(SelShared& sm, const unsigned char* row, int V) {
-    constexpr int EPT = BF16 ? 8 : 4, WCH = 64 * EPT, STEP = kWaves * kUnroll, LPG = kGroupTokens / EPT;
+    constexpr int EPT = BF16 ? 8 : 4, WCH = 64 * EPT, STEP = kWaves * kStreamUnroll, LPG = kGroupTokens / EPT;
     constexpr size_t ES = BF16 ? 2 : 4;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int nch = (V + WCH - 1) / WCH, ng = (V + kGroupTokens - 1) / kGroupTokens;
     for (int c0 = w; c0 < nch; c0 += STEP) {
-        uint32_t wv[kUnroll][4];
+        uint32_t wv[kStreamUnroll][4];
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
+        for (int u = 0; u < kStreamUnroll; ++u) {
             const int base = (c0 + u * kWaves) * WCH + lane * EPT;
             if (base + EPT <= V) {
                 const u32x4 q = __builtin_nontemporal_load((const u32x4_any*)(row + (size_t)base * ES));
@@ -256,16 +263,16 @@ __device__ __forceinline__ void stream_group_max(SelShared& sm, const unsigned c
                 }
             }
         }
-        float mx[kUnroll];
+        float mx[kStreamUnroll];
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
+        for (int u = 0; u < kStreamUnroll; ++u) {
             mx[u] = __uint_as_float(elem_bits<BF16>(wv[u], 0));
 #pragma unroll
             for (int i = 1; i < EPT; ++i) mx[u] = fmaxf(mx[u], __uint_as_float(elem_bits<BF16>(wv[u], i)));
         }
-        row16_max_n<kUnroll>(mx);
+        row16_max_n<kStreamUnroll>(mx);
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
+        for (int u = 0; u < kStreamUnroll; ++u) {
             if (LPG == 32) mx[u] = fmaxf(mx[u], __shfl_xor(mx[u], 16));
             const int g = (c0 + u * kWaves) * (WCH / kGroupTokens) + lane / LPG;
             if (lane % LPG == 0 && g < ng) sm.u.gm[g] = mx[u];
@@ -273,16 +280,41 @@ __device__ __forceinline__ void stream_group_max(SelShared& sm, const unsigned c
     }
 }
 
-// The top_k-th largest 16-bit key class of ng <= 64 Q group maxima, by one wave.
+// The top_k-th largest 16-bit key class of ng <= 64 Q group maxima, by one wave.  For
+// top_k <= 64 the top_k-th largest of the lanes' own maxima is a first bound (as many
+// groups reach it); the group maxima that reach it, usually fewer than 128, are
+// compacted through LDS (tmp) and searched two per lane.  With Q = 16 the search over all of
+// them took 6.4 us beside other workgroups' streaming.
 template <int Q>
-__device__ __forceinline__ uint32_t group_threshold(const float* gm, int ng, int top_k) {
+__device__ __forceinline__ uint32_t group_threshold(const float* gm, int ng, int top_k, uint32_t* tmp) {
     const int lane = threadIdx.x & 63;
-    uint32_t kw[Q];
+    uint32_t kw[Q], mine[1] = {0u};
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
         const int g = lane + 64 * q;
         const float m = g < ng ? gm[g] : -INFINITY;
         kw[q] = m >= -3.40282347e38f ? key_f32(__float_as_uint(m)) : 0u;
+        mine[0] = max(mine[0], kw[q]);
+    }
+    if (top_k <= 64) {
+        const uint32_t t0 = wave_kth_class<1, 16>(mine, top_k);
+        if (t0 != 0u) {
+            int cnt = 0;
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+                const uint64_t m = __ballot(kw[q] >= t0);
+                const int pos = cnt + lanes_below(m);
+                if (kw[q] >= t0 && pos < 128) tmp[pos] = kw[q];
+                cnt += (int)__popcll(m);
+            }
+            if (cnt <= 128) {
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+                const uint32_t k2[2] = {lane < cnt ? tmp[lane] : 0u, lane + 64 < cnt ? tmp[lane + 64] : 0u};
+                return wave_kth_class<2, 16>(k2, top_k);
+            }
+        }
     }
     return wave_kth_class<Q, 16>(kw, top_k);
 }
@@ -322,7 +354,8 @@ __device__ __forceinline__ bool select_candidates(SelShared& sm, const unsigned 
     if (ng >= top_k && ng <= 1024) {
         // one wave finds t over all the group maxima; the others wait at one barrier
         if (w == 0) {
-            const uint32_t tw = ng <= 256 ? group_threshold<4>(sm.u.gm, ng, top_k) : group_threshold<16>(sm.u.gm, ng, top_k);
+            uint32_t* tmp = (uint32_t*)sm.tok;  // (free until the candidates are found)
+            const uint32_t tw = ng <= 256 ? group_threshold<4>(sm.u.gm, ng, top_k, tmp) : group_threshold<16>(sm.u.gm, ng, top_k, tmp);
             if (lane == 0) sm.tsel = tw;
         }
         __syncthreads();
@@ -352,6 +385,8 @@ __device__ __forceinline__ bool select_candidates(SelShared& sm, const unsigned 
     // wave w reads groups w*GPW .. of every step of kWaves*GPW list entries
     uint32_t* bk = sm.u.wb.key[w];
     int32_t* bi = sm.u.wb.idx[w];
+    // a logit reaches t (finite ones, when t is 0) exactly if it is at least t's value
+    const float tv = t ? val_f32(t) : -3.40282347e38f;
     int cnt = 0;
     bool over = false;
     for (int e0 = w * GPW; e0 < n_cg; e0 += kWaves * GPW * kUnroll) {
@@ -387,28 +422,34 @@ __device__ __forceinline__ bool select_candidates(SelShared& sm, const unsigned 
                 }
             }
         }
+        // this lane's logits that reach t, as bits (few lanes have any), then their places
+        uint32_t mask = 0u;
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u)
+#pragma unroll
+            for (int i = 0; i < EPT; ++i)
+                mask |= (uint32_t)(__uint_as_float(elem_bits<BF16>(wv[u], i)) >= tv) << (EPT * u + i);
+        static_assert(EPT * kUnroll <= 32, "one mask bit per loaded logit");
+        const uint32_t c = (uint32_t)__popc(mask), incl = wave_incl_sum(c);
+        const int tot = (int)__builtin_amdgcn_readlane((int)incl, 63);
+        if (cnt + tot > kWaveCap) {  // ties at the cut: give up (radix passes)
+            over = true;
+            break;
+        }
+        int pos = cnt + (int)(incl - c);
 #pragma unroll
         for (int u = 0; u < kUnroll; ++u) {
+            const uint32_t mu = (mask >> (EPT * u)) & ((1u << EPT) - 1u);
+            if (mu == 0u) continue;
 #pragma unroll
-            for (int i = 0; i < EPT; ++i) {
-                const uint32_t bits = elem_bits<BF16>(wv[u], i);
-                const float x = __uint_as_float(bits);
-                const bool pass = base[u] >= 0 && x >= -3.40282347e38f && key_f32(bits) >= t && !over;
-                const uint64_t m = __ballot(pass);
-                if (m) {
-                    if (pass) {
-                        const int pos = cnt + lanes_below(m);
-                        bk[pos] = key_f32(bits);
-                        bi[pos] = base[u] + i;
-                    }
-                    cnt += __popcll(m);
+            for (int i = 0; i < EPT; ++i)
+                if ((mu >> i) & 1u) {
+                    bk[pos] = key_f32(elem_bits<BF16>(wv[u], i));
+                    bi[pos] = base[u] + i;
+                    ++pos;
                 }
-                if (cnt > kWaveCap - 64) {  // ties at the cut: give up (radix passes)
-                    over = true;
-                    cnt = 0;
-                }
-            }
         }
+        cnt += tot;
     }
     if (lane == 0) {
         sm.wcount[w] = cnt;
@@ -517,6 +558,7 @@ __global__ __launch_bounds__(kTBlock) void topk_select_kernel(TopkSelectArgs a) 
 
     int it = 0;
     int need;
+    bool sorted = false;
     if (!select_candidates<BF16>(sm, row, a.V, a.top_k)) {
         __syncthreads();  // the candidate buffers are reused by the radix passes
         if (tid == 0 && a.radix_rows) atomicAdd(a.radix_rows, 1u);
@@ -532,51 +574,33 @@ __global__ __launch_bounds__(kTBlock) void topk_select_kernel(TopkSelectArgs a) 
 #pragma unroll
         for (int w = 0; w < kWaves; ++w) tot += sm.wcount[w];
         need = min(a.top_k, tot);
-        constexpr int QW = 4;  // candidates per lane when one wave holds them all
-        if (need > 0 && tot <= 64 * QW) {
-            // one wave: the same bisections over the concatenated buffers, with ballots
-            if (tid < 64) {
-                const int lane = tid;
+        if (need > 0 && tot <= kTBlock) {
+            // one candidate per thread, whose rank among them (key descending, index
+            // ascending: one 64-bit comparison each) is its place in the sorted list
+            uint64_t* comp = (uint64_t*)sm.comp;
+            uint64_t mine = 0u;
+            if (tid < tot) {
                 const int c0 = sm.wcount[0], c1 = c0 + sm.wcount[1], c2 = c1 + sm.wcount[2];
-                uint32_t kk[QW];
-                int32_t ii[QW];
-#pragma unroll
-                for (int q = 0; q < QW; ++q) {
-                    const int j = lane + 64 * q;
-                    const int bw = j < c0 ? 0 : j < c1 ? 1 : j < c2 ? 2 : 3;
-                    const int p = j - (bw == 0 ? 0 : bw == 1 ? c0 : bw == 2 ? c1 : c2);
-                    const bool ok = j < tot;
-                    kk[q] = ok ? sm.u.wb.key[bw][p] : 0u;
-                    ii[q] = ok ? sm.u.wb.idx[bw][p] : 0;
+                const int bw = tid < c0 ? 0 : tid < c1 ? 1 : tid < c2 ? 2 : 3;
+                const int p = tid - (bw == 0 ? 0 : bw == 1 ? c0 : bw == 2 ? c1 : c2);
+                mine = ((uint64_t)sm.u.wb.key[bw][p] << 32) | (uint32_t)~sm.u.wb.idx[bw][p];
+            }
+            comp[tid] = mine;  // (0 past the last: below every candidate)
+            __syncthreads();
+            if (tid < tot) {
+                int rk = 0;
+                const ulonglong2* c2 = (const ulonglong2*)comp;
+#pragma unroll 4
+                for (int i = 0; i < (tot + 1) / 2; ++i) {
+                    const ulonglong2 o = c2[i];
+                    rk += (int)(o.x > mine) + (int)(o.y > mine);
                 }
-                const uint32_t t = wave_kth_class<QW, KeyBits<BF16>::kLow>(kk, need);
-                const uint32_t t_up = t + (1u << KeyBits<BF16>::kLow);
-                const int n_gt = wave_count<QW>([&](int q) { return kk[q] >= t_up; });
-                const int n_ge = wave_count<QW>([&](int q) { return kk[q] >= t; });
-                const int take = need - n_gt;
-                int xmax = 0x7FFFFFFF;
-                if (n_ge - n_gt > take) {
-                    int x = 0;
-                    for (int bit = 18; bit >= 0; --bit) {
-                        const int cand = x | (1 << bit);
-                        if (wave_count<QW>([&](int q) { return kk[q] >= t && kk[q] < t_up && ii[q] < cand; }) < take)
-                            x = cand;
-                    }
-                    xmax = x;
-                }
-                int off = 0;
-#pragma unroll
-                for (int q = 0; q < QW; ++q) {
-                    const bool keep = kk[q] >= t_up || (kk[q] >= t && ii[q] <= xmax);
-                    const uint64_t m = __ballot(keep);
-                    const int pos = off + lanes_below(m);
-                    if (keep && pos < kMaxTopK) {
-                        sm.tok[pos] = ii[q];
-                        sm.val[pos] = val_f32(kk[q]);
-                    }
-                    off += __popcll(m);
+                if (rk < need) {
+                    sm.stok[rk] = (int)~(uint32_t)mine;
+                    sm.sval[rk] = val_f32((uint32_t)(mine >> 32));
                 }
             }
+            sorted = true;
             __syncthreads();
         } else {
 #pragma unroll
@@ -638,7 +662,7 @@ __global__ __launch_bounds__(kTBlock) void topk_select_kernel(TopkSelectArgs a) 
     }
     const int n = need;  // both branches leave exactly need entries
     // sort by (logit descending, index ascending): each entry's rank by counting
-    if (tid < n) {
+    if (!sorted && tid < n) {
         const float xv = sm.val[tid];
         const int tv = sm.tok[tid];
         int rk = 0;
@@ -863,12 +887,40 @@ __device__ int wave_race_one(const TopkRaceArgs& a, const ListHead& h, int rid, 
 // scratch of 64 scores and entries.  Returns false when they are not (or more than 64
 // arrivals reach theta).
 constexpr int kTFin = 64;
+// h: the list, loaded ahead.
+struct ListAll {
+    int n, tok[kMaxTopK / 64];
+    float x[kMaxTopK / 64], xmax;
+};
+__device__ __forceinline__ ListAll list_all(const TopkRaceArgs& a, int rid) {
+    ListAll h;
+    h.n = a.list_len[rid];
+    const int lane = (int)(threadIdx.x & 63);
+#pragma unroll
+    for (int q = 0; q < kMaxTopK / 64; ++q) {
+        const size_t c = (size_t)rid * a.cap + min(lane + 64 * q, a.cap - 1);  // (inside the row's list)
+        h.tok[q] = 64 * q < a.cap ? a.list_tok[c] : -1;
+        h.x[q] = 64 * q < a.cap ? a.list_val[c] : 0.f;
+    }
+    h.xmax = a.list_val[(size_t)rid * a.cap];
+    return h;
+}
+
+__device__ __forceinline__ float wave_min_f32(float x) {
+    x = fminf(x, dpp_row<0xB1>(x));
+    x = fminf(x, dpp_row<0x4E>(x));
+    x = fminf(x, dpp_row<0x141>(x));
+    x = fminf(x, dpp_row<0x140>(x));
+    x = fminf(x, __shfl_xor(x, 16));
+    return fminf(x, __shfl_xor(x, 32));
+}
+
 template <int LAYOUT>
-__device__ bool wave_mpfr32(const TopkRaceArgs& a, RaceShared& sm, int w, int rid, uint32_t members, int s, float T,
-                            uint32_t k0, uint32_t k1) {
+__device__ bool wave_mpfr32(const TopkRaceArgs& a, RaceShared& sm, int w, const ListAll& h, uint32_t members, int s,
+                            float T, uint32_t k0, uint32_t k1) {
     constexpr int Q = kMaxTopK / 64;
     const int lane = threadIdx.x & 63;
-    const int n = a.list_len[rid];
+    const int n = h.n;
     const int nu = __popc(members);
     if (n == 0) {
         if (lane < nu) {
@@ -878,9 +930,7 @@ __device__ bool wave_mpfr32(const TopkRaceArgs& a, RaceShared& sm, int w, int ri
         }
         return true;
     }
-    const int* lt = a.list_tok + (size_t)rid * a.cap;
-    const float* lv = a.list_val + (size_t)rid * a.cap;
-    const float invT = 1.0f / T, xmax = lv[0];
+    const float invT = 1.0f / T, xmax = h.xmax;
     if (!(xmax < INFINITY)) return false;
     float G[Q], xs[Q], sc[Q];
     int tok[Q];
@@ -891,8 +941,8 @@ __device__ bool wave_mpfr32(const TopkRaceArgs& a, RaceShared& sm, int w, int ri
         xs[q] = G[q] = 0.f;
         sc[q] = INFINITY;
         if (c < n) {
-            tok[q] = lt[c];
-            xs[q] = (lv[c] - xmax) * invT;
+            tok[q] = h.tok[q];
+            xs[q] = (h.x[q] - xmax) * invT;
             G[q] = tclock32<LAYOUT>((uint32_t)a.V, 0u, (uint32_t)tok[q], k0, k1);
             sc[q] = ln_f32(G[q]) - xs[q];
         }
@@ -904,10 +954,8 @@ __device__ bool wave_mpfr32(const TopkRaceArgs& a, RaceShared& sm, int w, int ri
 #pragma unroll
         for (int q = 0; q < Q; ++q) t[q] = sc[q];
         for (int r = 0; r < nu; ++r) {
-            float m = fminf(fminf(t[0], t[1]), fminf(t[2], t[3]));
             static_assert(Q == 4, "four entries per lane");
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) m = fminf(m, __shfl_xor(m, o));
+            const float m = wave_min_f32(fminf(fminf(t[0], t[1]), fminf(t[2], t[3])));
             theta = m;
 #pragma unroll
             for (int q = 0; q < Q; ++q)
@@ -1043,9 +1091,19 @@ __device__ void wave_mpfr(const TopkRaceArgs& a, RaceShared& sm, int rid, uint32
     }
 }
 
+// The call's error bits to the sticky word and the caller's status word (one thread).
+// The list kernels set none themselves, so the first workgroup of the call's last
+// launch does this at its start (a launch of its own took 4.4 us and a gap).
+__device__ __forceinline__ void hand_over_status(const TopkRaceArgs& a) {
+    const uint32_t bits = __hip_atomic_exchange(a.ctrl + kCtrlCallErrors, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (bits) __hip_atomic_fetch_or(a.ctrl + kCtrlErrors, bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (a.status) *a.status = bits | (a.status_in ? *a.status_in : 0u);
+}
+
 template <int LAYOUT>
 __global__ __launch_bounds__(512) void topk_race_kernel(TopkRaceArgs a) {
     __shared__ RaceShared sm;
+    if (blockIdx.x == 0 && threadIdx.x == 0) hand_over_status(a);
     const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, w = tid >> 6, nw = (int)(blockDim.x >> 6);
     const int K = a.K, G = a.gamma;
     const int D = a.B * K * G;
@@ -1063,6 +1121,8 @@ __global__ __launch_bounds__(512) void topk_race_kernel(TopkRaceArgs a) {
     const int s_lo = a.target_rows > 0 ? 0 : a.s_begin;
     const int s_hi = a.target_rows > 0 ? G : d_end - 1;
     uint32_t k0, k1;
+    ListHead thead = {};  // a target wave's part of the next list, loaded while a depth runs
+    if (a.target_rows == 1 && w >= dw) thead = list_head(a, D + b * (G + 1) + s_lo, tslots, w - dw);
     for (int s = s_lo; s <= s_hi; ++s) {
         if (s >= a.s_begin && s < d_end && w < dw) {
             for (int k = w; k < K; k += dw) {
@@ -1085,8 +1145,9 @@ __global__ __launch_bounds__(512) void topk_race_kernel(TopkRaceArgs a) {
                         }
                     }
                     if (!rep) continue;
+                    const ListAll h = list_all(a, (b * K + k) * G + s);  // (in flight while the key is folded)
                     list_key(a, sm.pre, t0 + s, &sm.path[k * 33], s, k0, k1, a.m);
-                    if (!wave_mpfr32<LAYOUT>(a, sm, w, (b * K + k) * G + s, members, s, a.T_draft, k0, k1))
+                    if (!wave_mpfr32<LAYOUT>(a, sm, w, h, members, s, a.T_draft, k0, k1))
                         wave_mpfr<LAYOUT>(a, sm, (b * K + k) * G + s, members, s, a.T_draft, k0, k1);
                 }
             }
@@ -1103,7 +1164,9 @@ __global__ __launch_bounds__(512) void topk_race_kernel(TopkRaceArgs a) {
                 list_key(a, sm.pre, t0 + s, sm.chain, s, k0, k1, a.m);
             }
             const int rid = D + b * (G + 1) + s;
-            const Best2 p = wave_race32<LAYOUT>(a, list_head(a, rid, tslots, ti), rid, 0, tslots, a.T_target, k0, k1, ti, twv);
+            const ListHead hs = thead;
+            if (s < G) thead = list_head(a, rid + 1, tslots, ti);
+            const Best2 p = wave_race32<LAYOUT>(a, hs, rid, 0, tslots, a.T_target, k0, k1, ti, twv);
             if (lane == 0) {
                 sm.ts1[ti] = p.s1;
                 sm.ts2[ti] = p.s2;
@@ -1226,6 +1289,7 @@ constexpr int kChainWaves = 4;  // waves sharing each target race; one more fold
 template <int LAYOUT>
 __global__ __launch_bounds__(64 * (kChainWaves + 1)) void topk_chain_kernel(TopkRaceArgs a) {
     __shared__ ChainShared sm;
+    if (a.target_rows == 0 && blockIdx.x == 0 && threadIdx.x == 0) hand_over_status(a);  // (no walk follows)
     const int K = a.K, G = a.gamma;
     const int nd = a.s_count > 0 ? K : 0, R = nd + (a.target_rows == 1 ? 1 : 0);
     // chain-major, the target chains (the longest) first: each kind of chain spreads over
@@ -1343,11 +1407,7 @@ __global__ __launch_bounds__(64 * kWalkWaves) void topk_walk_kernel(TopkRaceArgs
     const int lane = (int)threadIdx.x & 63, wave = (int)threadIdx.x >> 6;
     const int b = (int)blockIdx.x * kWalkWaves + wave;
     const int K = a.K, G = a.gamma;
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        const uint32_t bits = __hip_atomic_exchange(a.ctrl + kCtrlCallErrors, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (bits) __hip_atomic_fetch_or(a.ctrl + kCtrlErrors, bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (a.status) *a.status = bits | (a.status_in ? *a.status_in : 0u);
-    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) hand_over_status(a);
     const bool valid = b < a.B;
     int32_t* v = vals[wave];
     const int nt = G + 1, n = nt + K * G;  // n <= kWalkVals (K and gamma are checked by the caller)
@@ -1421,7 +1481,7 @@ hipError_t launch_topk_race(const TopkRaceArgs& a, int layout, hipStream_t strea
             hipLaunchKernelGGL(topk_walk_kernel, dim3((unsigned)((a.B + kWalkWaves - 1) / kWalkWaves)), dim3(64 * kWalkWaves), 0, stream, a);
             return hipGetLastError();
         }
-        return launch_finish_status(a.ctrl, a.status, stream);
+        return R > 0 ? hipSuccess : launch_finish_status(a.ctrl, a.status, stream);
     }
     // identical drafters (contexts group paths at every depth) or per-path target rows:
     // one workgroup per sequence, at most 8 waves (the TREE clocks need more than 128
@@ -1440,8 +1500,7 @@ hipError_t launch_topk_race(const TopkRaceArgs& a, int layout, hipStream_t strea
         hipLaunchKernelGGL(topk_race_kernel<0>, dim3(a.B), dim3(64 * waves), 0, stream, b);
     else
         hipLaunchKernelGGL(topk_race_kernel<1>, dim3(a.B), dim3(64 * waves), 0, stream, b);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    return launch_finish_status(a.ctrl, a.status, stream);
+    return hipGetLastError();
 }
 
 }  // namespace psd
