@@ -118,13 +118,13 @@ __device__ __forceinline__ float mload(const unsigned char* row, bool bf16, int 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4_f32 __attribute__((ext_vector_type(4), aligned(4)));
 typedef uint32_t u32x4_b16 __attribute__((ext_vector_type(4), aligned(2)));
-template <bool BF16>
+template <bool BF16, bool NT = false>
 __device__ __forceinline__ uint4 mld16(const void* p) {
     u32x4 v;
     if constexpr (BF16)
-        v = *(const u32x4_b16*)p;
+        v = NT ? (u32x4)__builtin_nontemporal_load((const u32x4_b16*)p) : (u32x4)*(const u32x4_b16*)p;
     else
-        v = *(const u32x4_f32*)p;
+        v = NT ? (u32x4)__builtin_nontemporal_load((const u32x4_f32*)p) : (u32x4)*(const u32x4_f32*)p;
     return make_uint4(v.x, v.y, v.z, v.w);
 }
 
@@ -175,13 +175,16 @@ __device__ __forceinline__ void mload8(const unsigned char* row, int V, int base
     mraw_values<BF16>(r, x);
 }
 
+// The streaming pass reads a row once and the sampling comes back for a few hundred tokens
+// of it, so its loads are non-temporal: 2.19 -> 2.03 ms per block at V = 256000, B = 8,
+// K = 16 (rows far larger than the caches), 136.0 -> 135.6 us at V = 128256, B = 1, K = 8.
 template <bool BF16>
 __device__ __forceinline__ void mraw_load(const unsigned char* row, int V, int base, MRaw<BF16>& r) {
     if constexpr (BF16) {
-        r.w[0] = mld16<true>((const uint16_t*)row + min(base, V - 8));
+        r.w[0] = mld16<true, true>((const uint16_t*)row + min(base, V - 8));
     } else {
-        r.w[0] = mld16<false>((const float*)row + min(base, V - 4));
-        r.w[1] = mld16<false>((const float*)row + min(base + 4, V - 4));
+        r.w[0] = mld16<false, true>((const float*)row + min(base, V - 4));
+        r.w[1] = mld16<false, true>((const float*)row + min(base + 4, V - 4));
     }
 }
 // The 8 logits from `base` (-inf past V) out of the raw words; the row's last tokens
