@@ -10,11 +10,11 @@
 // loads, the online log-sum-exp partial (sum of exp2 relative to the segment
 // maximum) and the maximum logit of every 128-token group.  Each value is published
 // as one 64-bit slot tagged with the call's epoch, so nothing waits for stores to
-// drain and nothing is cleared between calls.  The workgroup that holds a row's
-// last segment becomes the row's finisher: it gathers the row's slots and does all
-// key-independent work (block maxima, top groups, LSE), then folds the context key
-// (waiting only for the newest context token), runs the keyed race, publishes the
-// winner and -- for the last row of a sequence -- walks the block.
+// drain and nothing is cleared between calls.  Every third workgroup finishes rows: it
+// gathers a row's slots and does all key-independent work (maxima, seed tokens, LSE, what
+// the race draws first), takes the context key from the race one depth up the path,
+// runs the keyed race, publishes the winner and the next depth's key and -- for the
+// last row of a sequence -- walks the block.
 //
 // The race (TREE clocks): the largest tokens of the row's eighths give achievable
 // scores; a level-by-level descent then expands only nodes whose lower bound
@@ -107,6 +107,7 @@ struct Shared {
     int win_token, win_slot;
     float rowmax;
     uint32_t kappa0, kappa1;
+    int have_key;             // the key was there when the row was folded
     uint32_t next0, next1;  // partial context key of the path's next depth
     int newest;             // winner of the race one depth up the path (it came with the key)
     // where the race's winner goes, ready before the race: the next depth's key words
@@ -194,7 +195,8 @@ __device__ __forceinline__ uint64_t wait_slot(const RaceArgs& a, const uint64_t*
 // one load: the two words of the next depth's key (lanes 0 and 1) and, when asked, its
 // winner (lane 2).  (Polls served by the XCD's own L2, with a path's rows handed out to
 // one XCD, measured the same.)  Returns the lane's word.
-__device__ __forceinline__ uint32_t wait_key(const RaceArgs& a, int prod, uint32_t epoch, bool winner) {
+__device__ __forceinline__ bool wait_key(const RaceArgs& a, int prod, uint32_t epoch, bool winner, bool once,
+                                         uint32_t& word) {
     const int lane = threadIdx.x & 63;
     const int n = winner ? 3 : 2;
     const uint64_t* p = lane < 2 ? (const uint64_t*)(a.ws + a.L.keys) + 2 * (size_t)prod + lane
@@ -202,14 +204,15 @@ __device__ __forceinline__ uint32_t wait_key(const RaceArgs& a, int prod, uint32
     uint64_t w = 0;
     for (uint32_t i = 0;; ++i) {
         if (lane < n) w = ld_dev(p);
-        if (__ballot(lane < n && (uint32_t)(w >> 32) != epoch) == 0u) break;
+        word = (uint32_t)w;
+        if (__ballot(lane < n && (uint32_t)(w >> 32) != epoch) == 0u) return true;
+        if (once) return false;
         if (i >= a.spin_limit) {
             if (lane == 0) set_error(a, kErrSpin);
-            break;
+            return true;
         }
         __builtin_amdgcn_s_sleep(2);
     }
-    return (uint32_t)w;
 }
 
 __device__ __forceinline__ int target_row_id(const RaceArgs& a, int b, int k, int s) {
@@ -1043,8 +1046,47 @@ __device__ __forceinline__ uint32_t pick_word(uint32_t a0, uint32_t a1, uint32_t
     return i == 0 ? a0 : i == 1 ? a1 : i == 2 ? a2 : a3;
 }
 
+// What lane e of pass A draws, all of it known before the context key: the counter and
+// slot, the node's size (and its reciprocal) and first token, and the seed it belongs to.
+// A row whose key is still on its way works it out meanwhile: 43.3 -> 42.3 us per block at
+// V = 1024, K = 2, gamma = 4, B = 1, 97.6 -> 95.2 at V = 32000, K = 4, gamma = 5, B = 16,
+// equal (93.6) at V = 128256, K = 4, gamma = 4, B = 64, whose rows mostly find the key there.
+// (With a plan for lanes that draw nothing, the streamers lose the issue slots: 94.0.)
+struct SeedPlan {
+    uint32_t c0, c2, slot, n, cs, av;  // counter words, slot, node tokens, first token, seed token
+    float rn, xs;                      // 1 / n, scaled seed logit
+    int j, i4;                         // slot index; level-4 node of lanes 6 and 7 (-1: none)
+    bool seed;                         // the seed exists
+};
+__device__ __forceinline__ SeedPlan seed_plan(const RaceArgs& a, const Row& r, const Shared& sm, const float* gm, int e) {
+    const uint32_t V = (uint32_t)a.V;
+    const int n4 = (int)((V + (1u << kShift4) - 1) >> kShift4);
+    const int pair = e >> 3, l = e & 7;
+    static_assert(kInit == 8, "seed index = low 3 bits of the 8-lane group index");
+    const int w = pair & 7;  // seed w, slot j
+    SeedPlan p;
+    p.j = pair >> 3;
+    const int tv = sm.seed_tok[w];
+    p.seed = tv >= 0;
+    p.slot = (uint32_t)(r.slot0 + p.j);
+    p.av = (uint32_t)max(tv, 0);
+    p.xs = tv >= 0 ? scaled(r, gm[tv >> 7]) : -INFINITY;
+    const uint32_t i4 = (uint32_t)(2 * w + (l - 6));
+    const bool l4 = l >= 6 && (int)i4 < n4;
+    p.i4 = l4 ? (int)i4 : -1;
+    p.c0 = l4 ? i4 : path_c0(l, p.av);
+    p.c2 = l4 ? 4u : path_c2(l, p.av);
+    const int sh = l4 ? kShift4 : path_shift(l);
+    const uint32_t node = l4 ? i4 : p.av >> sh;
+    p.cs = (l == 0 || l == 5) ? 0u : node << sh;
+    p.n = l == 0 ? V : l == 5 ? 1u : node_end(sh, node, V) - p.cs;
+    p.rn = __builtin_amdgcn_rcpf((float)p.n);
+    return p;
+}
+
 template <bool BF16, int LAYOUT>
-__device__ __forceinline__ void race(const RaceArgs& a, const Row& r, Shared& sm, const float* gm, uint32_t k0, uint32_t k1) {
+__device__ __forceinline__ void race(const RaceArgs& a, const Row& r, Shared& sm, const float* gm, uint32_t k0, uint32_t k1,
+                                     SeedPlan pl) {
     // (lists, candidates and the best score were reset by the caller)
     const int tid = threadIdx.x;
     const uint32_t V = (uint32_t)a.V;
@@ -1063,29 +1105,21 @@ __device__ __forceinline__ void race(const RaceArgs& a, const Row& r, Shared& sm
     for (int e0 = 0; e0 < nA; e0 += kBlock) {
         const int e = e0 + tid;
         if (e < seed_lanes) {  // whole 8-lane groups: the shuffles stay within active lanes
-            const int pair = e >> 3, l = e & 7;
-            static_assert(kInit == 8, "seed index = low 3 bits of the 8-lane group index");
-            const int w = pair & 7, j = pair >> 3;  // seed w, slot j
-            const int tv = sm.seed_tok[w];
-            const int g = tv >= 0 ? tv >> 7 : -1;
-            const uint32_t slot = (uint32_t)(r.slot0 + j);
-            const uint32_t av = (uint32_t)max(tv, 0);
-            const float xa = g >= 0 ? gm[g] : -INFINITY;
+            const int l = e & 7;
+            if (e0 > 0) pl = seed_plan(a, r, sm, gm, e);
+            const uint32_t slot = pl.slot, av = pl.av;
+            const int j = pl.j;
             if constexpr (LAYOUT == 0) {
                 // lane l turns node l's draw into (minimum increment, position): root
                 // E'/V, level-4..1 node E'/size at a uniform position in it, token E'
+                const uint32_t i4 = (uint32_t)pl.i4;
+                const bool l4 = pl.i4 >= 0;
                 float val = 0.f;
                 uint32_t pos = 0u;
-                const uint32_t i4 = (uint32_t)(2 * w + (l - 6));  // level-4 node of lanes 6 and 7
-                const bool l4 = l >= 6 && (int)i4 < n4;
                 if (l < 6 || l4) {
-                    const Words wd = philox(l4 ? i4 : path_c0(l, av), slot, l4 ? 4u : path_c2(l, av), kDomainTree, k0, k1);
-                    const int sh = l4 ? kShift4 : path_shift(l);
-                    const uint32_t node = l4 ? i4 : av >> sh;
-                    const uint32_t cs = (l == 0 || l == 5) ? 0u : node << sh;
-                    const uint32_t n = l == 0 ? V : l == 5 ? 1u : node_end(sh, node, V) - cs;
-                    val = div_n(exp1_f32(l == 5 ? pick_word(wd.w0, wd.w1, wd.w2, wd.w3, av & 3u) : wd.w0), n);
-                    pos = cs + uniform_position(wd.w1, wd.w2, n);
+                    const Words wd = philox(pl.c0, slot, pl.c2, kDomainTree, k0, k1);
+                    val = exp1_f32(l == 5 ? pick_word(wd.w0, wd.w1, wd.w2, wd.w3, av & 3u) : wd.w0) * pl.rn;
+                    pos = pl.cs + uniform_position(wd.w1, wd.w2, pl.n);
                 }
                 const int base = tid & ~7;
                 float m = __shfl(val, base);
@@ -1110,8 +1144,9 @@ __device__ __forceinline__ void race(const RaceArgs& a, const Row& r, Shared& sm
                 }
                 const float v5 = __shfl(val, base + 5);
                 const float E = (av == p) ? m : m + v5;
-                if (l == 0 && g >= 0) {
-                    const float sc = ln_f32(E) - scaled(r, xa);
+                if (l == 0 && pl.seed) {
+                    const float sc = ln_f32(E) - pl.xs;
+                    const float xa = gm[av >> 7];
                     if (sc < INFINITY) {
                         // (listed only if within the margin of the best so far)
                         atomicMin(&sm.best_key, ordered_key(sc));
@@ -1119,7 +1154,8 @@ __device__ __forceinline__ void race(const RaceArgs& a, const Row& r, Shared& sm
                     }
                 }
             } else {
-                if (l == 0 && g >= 0) {
+                if (l == 0 && pl.seed) {
+                    const float xa = gm[av >> 7];
                     const Words wd = philox(av >> 2, slot, 0u, kDomainFlat, k0, k1);
                     const float sc = ln_f32(exp1_f32(word_at(wd, av & 3u))) - scaled(r, xa);
                     if (sc < INFINITY) {
@@ -1616,14 +1652,32 @@ __device__ __forceinline__ void finish_row(const RaceArgs& a, const Row& r, Shar
             sm.next0 = c0;
             sm.next1 = c1;
         }
+        bool have = true;
         if (prod >= 0) {
-            const uint32_t w = wait_key(a, prod, ep, cons && a.m > 1);
+            uint32_t w;
+            have = wait_key(a, prod, ep, cons && a.m > 1, true, w);
             if (lane == 0) sm.kappa0 = w;
             if (lane == 1) sm.kappa1 = w;
             if (lane == 2) sm.newest = (int)w;
         }
+        if (lane == 0) sm.have_key = have;
     }
     __syncthreads();
+    // what pass A draws, worked out while the key is on its way
+    Row rs = r;
+    rs.shift = sm.rowmax;
+    SeedPlan plan;
+    if (tid < kInit * 8 * rs.nslots) plan = seed_plan(a, rs, sm, gm, tid);
+    if (!sm.have_key) {  // (uniform; written before the barrier above)
+        if (wave == 3) {
+            uint32_t w;
+            wait_key(a, prod, ep, cons && a.m > 1, false, w);
+            if (lane == 0) sm.kappa0 = w;
+            if (lane == 1) sm.kappa1 = w;
+            if (lane == 2) sm.newest = (int)w;
+        }
+        __syncthreads();
+    }
     const uint32_t k0 = sm.kappa0, k1 = sm.kappa1;
     if (sm.rowmax == -INFINITY) {
         if (tid == 0) {
@@ -1632,9 +1686,7 @@ __device__ __forceinline__ void finish_row(const RaceArgs& a, const Row& r, Shar
         }
         __syncthreads();
     } else {
-        Row rs = r;
-        rs.shift = sm.rowmax;
-        race<BF16, LAYOUT>(a, rs, sm, gm, k0, k1);
+        race<BF16, LAYOUT>(a, rs, sm, gm, k0, k1, plan);
     }
     if (tid == 0) {
         const int y = sm.win_token;
