@@ -219,7 +219,8 @@ psd::MpfrArgs mpfr_args(const psd_params* p, const psd_block* b, int32_t s_begin
 // LSE) and the sampling is one launch for every depth when its workgroups fit the device
 // together (tok_slot), else one per depth.  Otherwise each depth has a streaming launch
 // and a sampling launch, so that a depth's rows can stream while the previous depth is
-// sampled: at V=256000, K=16, gamma=4, B=256 2182 us per call against 3036 with one
+// sampled: at V=256000, K=16, gamma=4, B=256 2182 us per call (2031 with the streaming
+// pass's loads made non-temporal since) against 3036 with one
 // launch per depth whose workgroups streamed a row each and then sampled (sized for
 // sampling, they read at 3.9 TB/s).
 psd_status mpfr_prepare(const psd_params* p, const psd_block* b, psd::MpfrArgs& m, bool* by_depth) {

@@ -35,7 +35,8 @@ inline constexpr int ctrl_queue(int q) { return 64 * (q + 1); }
 //   part : payload = float bits of the segment's sum of exp2 (relative to its max)
 //   gmax : payload = float bits of the group's maximum logit
 //   m3   : payload = float bits of a 2048-token block's maximum logit
-//   stop : payload = int32 index of the segment's largest group (lowest index; -1: none)
+//   stop : reserved (no kernel reads or writes it; it keeps the workspace's size, and with
+//          it the block shapes that fit a caller's scratch)
 //   keys : two slots per row, payload = the two words of the context key of the
 //          next depth of the row's path (published by the row's race)
 //
@@ -49,7 +50,7 @@ struct WsLayout {
     size_t part;  // uint64[n_rows][nseg]
     size_t gmax;  // uint64[n_rows][ng]
     size_t m3;    // uint64[n_rows][n3]
-    size_t stop;  // uint64[n_rows][nseg]
+    size_t stop;  // uint64[n_rows][nseg], reserved
     size_t keys;  // uint64[n_rows][2]
     size_t total;
     int n_rows, nseg, ng, n3;

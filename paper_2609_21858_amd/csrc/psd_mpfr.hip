@@ -176,8 +176,9 @@ __device__ __forceinline__ void mload8(const unsigned char* row, int V, int base
 }
 
 // The streaming pass reads a row once and the sampling comes back for a few hundred tokens
-// of it, so its loads are non-temporal: 2.19 -> 2.03 ms per block at V = 256000, B = 8,
-// K = 16 (rows far larger than the caches), 136.0 -> 135.6 us at V = 128256, B = 1, K = 8.
+// of it, so its loads are non-temporal: 2.19 -> 2.03 ms per block at V = 256000, B = 256,
+// K = 16 (rows far larger than the caches), 136.0 -> 135.6 us at V = 128256, B = 64,
+// K = 4.
 template <bool BF16>
 __device__ __forceinline__ void mraw_load(const unsigned char* row, int V, int base, MRaw<BF16>& r) {
     if constexpr (BF16) {
