@@ -195,9 +195,9 @@ psd_status psd_draft(const psd_params *params, const psd_block *block, int32_t s
  * -1 or not a draft of an active path at depth s; else keep the active paths
  * that drafted y_s.  After gamma acceptances emit the bonus y_gamma.
  * Identical drafters (PSD_MODE_MPFR) with draft_logits and target_rows 1: the
- * target chain is raced, and the draft rows are streamed, on two library streams of
- * the current device (created at the first such call and kept until the process
- * ends) beside the sampling launches on `stream`; `stream` waits for both through
+ * target chain is raced, and the draft rows are streamed or sampled, on two library
+ * streams of the current device (created at the first such call and kept until the
+ * process ends) beside the launches on `stream`; `stream` waits for both through
  * events before the walk.
  * Under stream capture the whole call stays on `stream`.  Such calls on one
  * device share those streams (calls from several host threads are serialised
