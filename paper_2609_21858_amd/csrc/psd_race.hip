@@ -86,7 +86,6 @@ struct Shared {
     int seed_tok[kInit];   // seed tokens of the race (-1: none)
     float part[64];        // LSE partial sum of every segment
     Node l3[kL3Cap];
-    uint16_t l3_mask[kL3Cap];  // groups of a listed level-3 node that can still win (bit i: its i-th)
     Node l2[kL2Cap];
     int cand_v[kCandCap];
     int cand_j[kCandCap];
@@ -103,7 +102,12 @@ struct Shared {
     int tick[4];
     int ph_first[kMaxPhases], ph_depth[kMaxPhases], ph_nd[kMaxPhases];  // work-order phases
     uint32_t epoch;
-    float gst[2][128];  // group maxima of the streamed segment (by parity)
+    // A finisher streams only before its first row, so the two share their place: the LDS
+    // of four workgroups fits a CU up to V = 256000 with K = 16 (2.17 ms per block with three).
+    union {
+        float gst[2][128];         // group maxima of the streamed segment (by parity)
+        uint16_t l3_mask[kL3Cap];  // groups of a listed level-3 node that can still win (bit i: its i-th)
+    };
     int win_token, win_slot;
     float rowmax;
     uint32_t kappa0, kappa1;
