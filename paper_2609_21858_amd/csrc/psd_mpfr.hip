@@ -48,7 +48,6 @@ constexpr int kMBlock = 256;
 constexpr int kMaxGroups = 4096;  // 128-token groups of V <= 2^19
 constexpr int kMCand = 1024;      // listed candidate tokens of a context
 constexpr int kSeeds = 16;        // seed tokens of a row, two per workspace word
-constexpr int kSeedArr = 16;      // arrivals drawn per seed, at most
 constexpr float kMMargin = 1e-3f;   // fp32 pruning margin (score units)
 constexpr float kMCutSlack = 1e-3f; // slack of the per-token logit cut (score units)
 constexpr uint32_t kMErrCand = 2u;
@@ -1035,30 +1034,41 @@ __device__ __forceinline__ void mpfr_depth(const MpfrArgs& a, MShared& sm, float
                 nd3.i = (uint32_t)i3;
             }
         }
-        // (one arrival per thread; the first min(nu, 16) arrivals of each seed)
-        const int si = tid & (kSeeds - 1), sj = tid / kSeeds;  // seed, arrival
-        static_assert(kSeeds * kSeedArr == kMBlock, "one seed arrival per thread");
-        const int na = min(nu, kSeedArr);
-        const int sv = sm.seed_tok[si];
+        // (one arrival per thread: the first min(nu, 16) arrivals of each seed or, for more
+        // samples than that, the first nu arrivals of the better seed of every two.  Any
+        // one seed then has nu arrivals, so theta is as good as the best group of the row
+        // allows even where every other seed is a masked token: with 16 arrivals of each, a
+        // context of 32 samples over a row that leaves one stretch of the vocabulary took
+        // its theta from masked seeds and listed the whole row.)
+        const int lg = nu > kMBlock / kSeeds ? 3 : 4;  // log2 of the seeds in use
+        const int nsd = 1 << lg;
+        const int si = tid & (nsd - 1), sj = tid >> lg;  // seed, arrival
+        static_assert(kSeeds == 16 && kMBlock == 256, "16 arrivals of 16 seeds or 32 of 8");
+        const int na = min(nu, kMBlock >> lg);
+        int sid = si;
+        if (lg == 3) {
+            const int g0 = sm.seed_g[2 * si], g1 = sm.seed_g[2 * si + 1];
+            sid = 2 * si + (int)(g1 >= 0 && (g0 < 0 || gm[g1] > gm[g0]));
+        }
+        const int sv = sm.seed_tok[sid];
         const bool on = sj < na && sv >= 0;
         float G = on ? clock_f32<LAYOUT>(V, (uint32_t)sj, (uint32_t)sv, k0, k1) : 0.f;
-#pragma unroll
-        for (int off = kSeeds; off < 64; off <<= 1) {  // the wave's four arrivals of each seed
+        for (int off = nsd; off < 64; off <<= 1) {  // the wave's arrivals of each seed
             const float o = __shfl_up(G, off);
             if (lane >= off) G += o;
         }
-        if (lane >= 64 - kSeeds) sm.esum[wave][si] = G;
+        if (lane >= 64 - nsd) sm.esum[wave][si] = G;
         __syncthreads();
         // ---- theta = the nu-th smallest seed score (by counting): it only has to bound the
         // context's nu-th smallest score from above.  Float32 scores are within the
         // pruning margin of the exact ones (the same assumption as every float32 bound of
         // the race), and theta carries one margin for that on top of its own.  A seed
         // token holds its group's maximum, so its logit is that maximum.
-        const int ns = kSeeds * na;
+        const int ns = nsd * na;
         float s0 = INFINITY;
         if (on) {
             for (int w = 0; w < wave; ++w) G += sm.esum[w][si];
-            s0 = ln_f32(G) - (gm[sm.seed_g[si]] - shift) * a.invT;
+            s0 = ln_f32(G) - (gm[sm.seed_g[sid]] - shift) * a.invT;
         }
         sm.sc[tid] = s0;
         if (tid == 0) sm.theta = INFINITY;  // (fewer than nu finite arrivals)
