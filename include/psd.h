@@ -83,8 +83,9 @@ typedef enum { PSD_F32 = 0, PSD_BF16 = 1 } psd_dtype;
  *      the draft rows are streamed, and the contexts sampled by one launch per depth,
  *      or, when the block's (sequence, path) workgroups fit the device together, by one
  *      launch for every depth (each depth's contexts formed as the earlier drafts
- *      land); with a shared target chain, psd_verify races the chain beside it (see
- *      there). */
+ *      land; it may run beside the streaming launch, and reads a row itself that does
+ *      not come in time); with a shared target chain, psd_verify races the chain beside
+ *      it (see there). */
 typedef enum { PSD_MODE_HET = 0, PSD_MODE_MPFR = 1 } psd_mode;
 
 /* TREE: clocks of a slot built top-down over a fixed token hierarchy (8-token

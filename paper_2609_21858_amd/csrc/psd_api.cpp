@@ -217,16 +217,18 @@ psd::MpfrArgs mpfr_args(const psd_params* p, const psd_block* b, int32_t s_begin
 // When a depth's B K (sequence, path) workgroups cannot fill the device (B K < 1024),
 // every draft row of the call is streamed in one launch (group maxima, maxima, seeds,
 // LSE) and the sampling is one launch for every depth when its workgroups fit the device
-// together (tok_slot), else one per depth.  Otherwise each depth has a streaming launch
+// together (tok_slot), else one per depth; *beside: that launch may run beside the
+// streaming launch.  Otherwise each depth has a streaming launch
 // and a sampling launch, so that a depth's rows can stream while the previous depth is
 // sampled: at V=256000, K=16, gamma=4, B=256 2182 us per call (2031 with the streaming
 // pass's loads made non-temporal since) against 3036 with one
 // launch per depth whose workgroups streamed a row each and then sampled (sized for
 // sampling, they read at 3.9 TB/s).
-psd_status mpfr_prepare(const psd_params* p, const psd_block* b, psd::MpfrArgs& m, bool* by_depth) {
+psd_status mpfr_prepare(const psd_params* p, const psd_block* b, psd::MpfrArgs& m, bool* by_depth, bool* beside) {
     const psd::WsLayout L = psd::ws_layout(b->batch, p->num_drafts, b->gamma, p->vocab, p->dtype == PSD_BF16);
     m.stream_s = m.s_begin;
     m.stream_n = m.s_count;
+    *beside = false;
     *by_depth = (long)b->batch * p->num_drafts >= psd::kMpfrStreamBelow;
     if (*by_depth) {
         m.row_gm = (uint64_t*)((unsigned char*)b->workspace + L.gmax);  // (draft row ids come first)
@@ -238,7 +240,7 @@ psd_status mpfr_prepare(const psd_params* p, const psd_block* b, psd::MpfrArgs& 
     m.row_max = (uint64_t*)((unsigned char*)b->workspace + M.rmax);
     m.row_seed = (uint64_t*)((unsigned char*)b->workspace + M.seed);
     bool fits = false;
-    hipError_t e = psd::mpfr_all_depths_fit(m, p->dtype == PSD_BF16, p->clocks, &fits);
+    hipError_t e = psd::mpfr_all_depths_fit(m, p->dtype == PSD_BF16, p->clocks, &fits, beside);
     if (e != hipSuccess) return hip_fail(e, "MPFR occupancy query");
     m.tok_slot = fits ? (uint64_t*)((unsigned char*)b->workspace + M.slot) : nullptr;
     // half as many streaming workgroups as rows (two rows each, depth-major; at least 512
@@ -271,8 +273,8 @@ psd_status mpfr_sample_depths(const psd_params* p, psd::MpfrArgs m, hipStream_t 
 psd_status run_mpfr_drafts(const psd_params* p, const psd_block* b, int32_t s_begin, int32_t s_count,
                            const void* draft_logits, int32_t* draft_tokens, float* draft_lse, hipStream_t stream) {
     psd::MpfrArgs m = mpfr_args(p, b, s_begin, s_count, draft_logits, draft_tokens, draft_lse);
-    bool by_depth = false;
-    psd_status st = mpfr_prepare(p, b, m, &by_depth);
+    bool by_depth = false, beside = false;
+    psd_status st = mpfr_prepare(p, b, m, &by_depth, &beside);
     if (st != PSD_OK) return st;
     if (!by_depth) {
         if ((st = mpfr_stream_rows(p, m, stream)) != PSD_OK) return st;
@@ -472,8 +474,8 @@ psd_status verify_mpfr_forked(const psd_params* params, const psd_block* block, 
     a.walk_kind = -1;  // no row walks: the walk kernel does, after the drafts
     a.status = ctrl + psd::kCtrlRaceBits;
     psd::MpfrArgs m = mpfr_args(params, block, 0, block->gamma, draft_logits, draft_tokens, draft_lse);
-    bool by_depth = false;
-    psd_status st = mpfr_prepare(params, block, m, &by_depth);
+    bool by_depth = false, beside = false;
+    psd_status st = mpfr_prepare(params, block, m, &by_depth, &beside);
     if (st != PSD_OK) return st;
     hipError_t e;
     psd_status sd;
@@ -508,16 +510,21 @@ psd_status verify_mpfr_forked(const psd_params* params, const psd_block* block, 
             else
                 sd = mpfr_sample(params, m, stream);
         }
-    } else if (m.tok_slot) {
+    } else if (beside) {
         // One sampling launch for every depth, which waits for the streamed rows' tagged
-        // words, beside the streaming launch (which never waits; both launches' workgroups
-        // fit the device together).  The streaming launch has the caller's stream and the
-        // sampling the side stream, behind the fork event, so that the rows start first:
+        // words, beside the streaming launch (which never waits).  The streaming launch has
+        // the caller's stream and the sampling the side stream, behind the fork event, so
+        // that the rows start first:
         // 131.4 us per call at V=128256, K=4, gamma=4, B=64 against 134.4 the other way round.
         sd = mpfr_stream_rows(params, m, stream);
         if (sd == PSD_OK) sd = mpfr_sample(params, m, f.side);
         if (sd == PSD_OK) sd = run_race(params, a, f.race);
     } else {
+        // The sampling after the streaming.  With more samplers than leave the streaming its
+        // places (512 of 768) they would run side by side only as long as the streaming is
+        // dispatched first: at V=128256, K=16, B=48 884 us per call in this form against 1400
+        // (gamma=8, float32), though 294 against 259 where every streaming workgroup found a
+        // place in time (gamma=4, bf16).
         sd = mpfr_stream_rows(params, m, stream);
         if (sd == PSD_OK) sd = run_race(params, a, f.race);
         if (sd == PSD_OK) sd = mpfr_sample_depths(params, m, stream);

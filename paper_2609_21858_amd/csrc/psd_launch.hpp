@@ -216,9 +216,11 @@ hipError_t launch_race(const RaceArgs& a, bool bf16, int layout, hipStream_t str
 // A sampling launch: of every depth when the drafts are handed over in tagged slots
 // (tok_slot set; the caller checked mpfr_all_depths_fit), else of depth a.s.
 hipError_t launch_mpfr_sample(const MpfrArgs& a, bool bf16, int layout, hipStream_t stream);
-// Whether one sampling launch can run every depth of a: more than one depth, and all
-// B K workgroups resident together.  *fits is set; a HIP error of the query is returned.
-hipError_t mpfr_all_depths_fit(const MpfrArgs& a, bool bf16, int layout, bool* fits);
+// Whether one sampling launch can run every depth of a (*fits: more than one depth, and
+// all B K workgroups resident together), and whether it may do so beside the streaming
+// launch (*beside: places are left for that one's workgroups).  A HIP error of the query is
+// returned.
+hipError_t mpfr_all_depths_fit(const MpfrArgs& a, bool bf16, int layout, bool* fits, bool* beside);
 hipError_t launch_mpfr_stream(const MpfrArgs& a, bool bf16, hipStream_t stream);
 hipError_t launch_finish_status(uint32_t* ctrl, uint32_t* status, hipStream_t stream);
 hipError_t launch_detect(const DetectArgs& a, int layout, hipStream_t stream);

@@ -84,6 +84,18 @@ inline WsLayout ws_layout(int B, int K, int gamma, int V, int dtype_bf16) {
     return L;
 }
 
+// Samplers beside the launch that streams their rows.  Every workgroup of either takes at
+// most a third of a CU's registers (their launch bounds) and `lds` bytes of its LDS, and a
+// sampler stays until the rows of its last depth have come.  With at most this many of
+// them, at least a place per CU is left to streaming workgroups, however the launches are
+// dispatched.
+constexpr int kJointPerCu = 3;
+constexpr size_t kLdsPerCu = size_t(160) << 10;
+inline long samplers_beside_streaming(int cus, size_t lds) {
+    const long by_lds = (long)(kLdsPerCu / (lds ? lds : 1));
+    return ((by_lds < kJointPerCu ? by_lds : (long)kJointPerCu) - 1) * cus;
+}
+
 struct RaceArgs {
     const void* draft_logits;   // [B][K][s_count][V] or null
     const void* target_logits;  // [B][gamma+1][V] or [B][K][gamma+1][V] or null

@@ -55,6 +55,9 @@ constexpr int kMWork = 2048;        // compacted (level-3 node, group) items
 constexpr int kMGroupCap = 512;     // listed groups
 constexpr int kMHalfCap = 256;      // listed 4-token halves
 constexpr int kMFinal = 256;        // listed arrivals
+// Polls of a sampler for a streamed word before it reads the row itself (a poll is about a
+// microsecond), and once one row has not come.
+constexpr uint32_t kRowPolls = 1u << 14, kRowPollsLate = 1u << 6;
 
 struct MNode {
     uint32_t i;  // node index at its level
@@ -106,6 +109,7 @@ struct MShared {
     int samples[32];
     int own[32];               // this path's drafts so far
     uint32_t epoch;            // this launch's tag of the handed-over drafts (multi-depth launch)
+    int row_late;              // the depth's row has not come (set by any thread)
 };
 
 __device__ __forceinline__ float mload(const unsigned char* row, bool bf16, int v) {
@@ -625,7 +629,7 @@ __device__ __forceinline__ void record_epoch(const MpfrArgs& a, uint32_t ep) {
 // are waited for, its maximum and seed tokens, and its LSE when the caller wants it.
 // It never waits.
 template <bool BF16, bool LSE>
-__global__ __launch_bounds__(kMBlock) void mpfr_stream_kernel(MpfrArgs a) {
+__global__ __launch_bounds__(kMBlock, kJointPerCu) void mpfr_stream_kernel(MpfrArgs a) {
     __shared__ float red_m[kMBlock / 64], red_s[kMBlock / 64], red_x[kMBlock / 64], rowmax;
     extern __shared__ __align__(16) float gm[];  // one float per group
     __shared__ int seed_g[kSeeds], seed_tok[kSeeds];
@@ -683,20 +687,37 @@ __device__ __forceinline__ int wait_draft(const MpfrArgs& a, size_t rid, uint32_
 }
 
 // Payload of a word the streaming launch wrote.  A launch that runs every depth may
-// run beside the streaming launch: it waits (bounded) for this call's tag.  Launches of
-// one depth follow the streaming launch in stream order and read the payload.
-__device__ __forceinline__ uint32_t row_word(const MpfrArgs& a, const uint64_t* p, uint32_t ep) {
+// run beside the streaming launch: it waits (at most `polls`) for this call's tag, and
+// notes in *late that the word has not come.  Launches of one depth follow the streaming
+// launch in stream order and read the payload.
+__device__ __forceinline__ uint32_t row_word(const MpfrArgs& a, const uint64_t* p, uint32_t ep, uint32_t polls, int* late) {
     if (!a.tok_slot) return (uint32_t)*p;
     uint64_t v = mld_dev(p);
     for (uint32_t i = 0; (uint32_t)(v >> 32) != ep; ++i) {
-        if (i >= a.spin_limit) {
-            __hip_atomic_fetch_or(a.ctrl + kCtrlCallErrors, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (i >= polls) {
+            *late = 1;
             break;
         }
         __builtin_amdgcn_s_sleep(2);
         v = mld_dev(p);
     }
     return (uint32_t)v;
+}
+
+// The row's group maxima (to gm in LDS) by this workgroup itself, 16 lanes per group.
+template <bool BF16>
+__device__ __forceinline__ void read_groups(const unsigned char* row, int V, float* gm) {
+    const int ng = (V + 127) / 128;
+#pragma unroll 1
+    for (int g = (int)threadIdx.x >> 4; g < ng; g += kMBlock / 16) {
+        float x[8];
+        mload8<BF16>(row, V, g * 128 + ((int)threadIdx.x & 15) * 8, x);
+        float mx = x[0];
+#pragma unroll
+        for (int i = 1; i < 8; ++i) mx = fmaxf(mx, x[i]);
+        mx = row16_max(mx);
+        if ((threadIdx.x & 15) == 0) gm[g] = mx;
+    }
 }
 
 // The context's samples from the exact (fp64) scores of its nc listed tokens: nu rounds
@@ -905,10 +926,11 @@ __device__ __forceinline__ bool sorted_samples(const MpfrArgs& a, MShared& sm, i
 // (in), at depth s (out).  first: no earlier depth was run by this workgroup (the
 // context is formed from the caller's drafts at every depth < s).  mine: this workgroup
 // sampled that context (in: at depth s - 1, out: at depth s), so it knows the drafts
-// without waiting for them.  ep: the launch's epoch when it runs every depth.
+// without waiting for them.  ep: the launch's epoch when it runs every depth.  polls: of a
+// wait for a streamed word.
 template <bool BF16, int LAYOUT>
 __device__ __forceinline__ void mpfr_depth(const MpfrArgs& a, MShared& sm, float* gm, int b, int k, int s, uint32_t ep,
-                                           bool first, uint32_t& mask, bool& mine) {
+                                           uint32_t& polls, bool first, uint32_t& mask, bool& mine) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint32_t V = (uint32_t)a.V;
     const int ng = (a.V + 127) / 128, n3 = (ng + 15) / 16;
@@ -977,15 +999,18 @@ __device__ __forceinline__ void mpfr_depth(const MpfrArgs& a, MShared& sm, float
     for (int i = 0; i < 4; ++i) {
         const int g = tid + i * kMBlock;
         if (g < ng)
-            gm[g] = __uint_as_float(a.tok_slot && (uint32_t)(w[i] >> 32) != ep ? row_word(a, a.row_gm + rid * ng + g, ep)
-                                                                               : (uint32_t)w[i]);
+            gm[g] = __uint_as_float(a.tok_slot && (uint32_t)(w[i] >> 32) != ep
+                                        ? row_word(a, a.row_gm + rid * ng + g, ep, polls, &sm.row_late)
+                                        : (uint32_t)w[i]);
     }
-    for (int g = tid + 4 * kMBlock; g < ng; g += kMBlock) gm[g] = __uint_as_float(row_word(a, a.row_gm + rid * ng + g, ep));
+    for (int g = tid + 4 * kMBlock; g < ng; g += kMBlock)
+        gm[g] = __uint_as_float(row_word(a, a.row_gm + rid * ng + g, ep, polls, &sm.row_late));
     if (tid < ((ng + 15) & ~15) - ng) gm[ng + tid] = -INFINITY;
     if (a.row_max) {
-        if (tid == 0) sm.rowmax = __uint_as_float(row_word(a, a.row_max + rid, ep));
+        if (tid == 0) sm.rowmax = __uint_as_float(row_word(a, a.row_max + rid, ep, polls, &sm.row_late));
         if (tid < kSeeds) {
-            const uint32_t h = (row_word(a, a.row_seed + rid * (kSeeds / 2) + (tid >> 1), ep) >> (16 * (tid & 1))) & 0xFFFFu;
+            const uint32_t h =
+                (row_word(a, a.row_seed + rid * (kSeeds / 2) + (tid >> 1), ep, polls, &sm.row_late) >> (16 * (tid & 1))) & 0xFFFFu;
             const int tk = h == 0xFFFFu ? -1 : min(seed_base(tid, ng) + (int)h, a.V - 1);
             sm.seed_tok[tid] = tk;
             sm.seed_g[tid] = tk >= 0 ? tk / 128 : -1;
@@ -996,7 +1021,17 @@ __device__ __forceinline__ void mpfr_depth(const MpfrArgs& a, MShared& sm, float
         sm.n_lg = sm.n_half[0] = sm.n_half[1] = sm.n_cand = sm.n_fin = 0;
     }
     __syncthreads();
-    if (!a.row_max) {
+    // A row that has not come is read here: the streaming workgroup that has it may not have
+    // been dispatched (the samplers and other launches may hold the places it needs), so a
+    // sampler never depends on one.
+    const bool late = sm.row_late != 0;
+    if (!a.row_max || late) {  // (uniform)
+        if (late) {
+            read_groups<BF16>(row, a.V, gm);
+            polls = min(polls, kRowPollsLate);
+            __syncthreads();
+            if (tid == 0) sm.row_late = 0;  // (read by every thread before the barrier)
+        }
         seed_groups(gm, ng, sm.seed_g);
         float mx = -INFINITY;
         if (wave == 0) {
@@ -1177,11 +1212,13 @@ __device__ __forceinline__ void mpfr_depth(const MpfrArgs& a, MShared& sm, float
 
 // One workgroup per (sequence, path).  Without tok_slot: depth a.s only.  With it:
 // every depth of the call in turn, each depth's contexts formed from the drafts of the
-// earlier depths as they land; waits are only for workgroups of the same launch, so
-// the launcher uses this form only when all of them can be resident together.  The
-// last workgroup to leave resets the exit count and records the launch's epoch.
+// earlier depths as they land.  A workgroup waits for the drafts of its context's lowest
+// path alone, whose workgroup has a lower index (path-major), and for streamed rows only
+// for a while (row_word): the running workgroup of lowest index depends on none that
+// might not be dispatched.  The last workgroup to leave resets the exit count and records
+// the launch's epoch.
 template <bool BF16, int LAYOUT>
-__global__ __launch_bounds__(kMBlock, 3) void mpfr_draft_kernel(MpfrArgs a) {
+__global__ __launch_bounds__(kMBlock, kJointPerCu) void mpfr_draft_kernel(MpfrArgs a) {
     __shared__ MShared sm;
     extern __shared__ __align__(16) float gm[];  // the row's group maxima (dynamic: one per group)
     // Path-major: consecutive workgroups go to the 8 XCDs in turn, and contexts are sampled
@@ -1190,15 +1227,17 @@ __global__ __launch_bounds__(kMBlock, 3) void mpfr_draft_kernel(MpfrArgs a) {
     const int b = (int)blockIdx.x % a.B, k = (int)blockIdx.x / a.B;
     uint32_t mask = a.K >= 32 ? 0xFFFFFFFFu : (1u << a.K) - 1u;
     bool mine = false;
+    uint32_t polls = min(a.spin_limit, kRowPolls);
+    if (threadIdx.x == 0) sm.row_late = 0;
     if (!a.tok_slot) {
-        mpfr_depth<BF16, LAYOUT>(a, sm, gm, b, k, a.s, 0u, true, mask, mine);
+        mpfr_depth<BF16, LAYOUT>(a, sm, gm, b, k, a.s, 0u, polls, true, mask, mine);
         return;
     }
     if (threadIdx.x == 0) sm.epoch = next_epoch(a);
     __syncthreads();
     const uint32_t ep = sm.epoch;
     for (int s = a.s_begin; s < a.s_begin + a.s_count; ++s) {
-        mpfr_depth<BF16, LAYOUT>(a, sm, gm, b, k, s, ep, s == a.s_begin, mask, mine);
+        mpfr_depth<BF16, LAYOUT>(a, sm, gm, b, k, s, ep, polls, s == a.s_begin, mask, mine);
         __syncthreads();
     }
     if (threadIdx.x == 0) record_epoch(a, ep);
@@ -1220,8 +1259,8 @@ namespace {
 size_t mpfr_smem(const MpfrArgs& a) { return (size_t)(((a.V + 127) / 128 + 15) & ~15) * sizeof(float); }
 
 template <bool BF16, int LAYOUT>
-hipError_t mpfr_fit(const MpfrArgs& a, bool* fits) {
-    *fits = false;
+hipError_t mpfr_fit(const MpfrArgs& a, bool* fits, bool* beside) {
+    *fits = *beside = false;
     if (a.s_count < 2) return hipSuccess;
     int per_cu = 0, dev = 0, cus = 0;
     hipError_t e;
@@ -1231,9 +1270,10 @@ hipError_t mpfr_fit(const MpfrArgs& a, bool* fits) {
     if ((e = hipGetDevice(&dev)) != hipSuccess) return e;
     if ((e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess) return e;
     *fits = (long)per_cu * cus >= (long)a.B * a.K;
+    // (a streaming workgroup's LDS is below a sampler's)
+    *beside = *fits && (long)a.B * a.K <= samplers_beside_streaming(cus, sizeof(MShared) + mpfr_smem(a));
     return hipSuccess;
 }
-
 // tok_slot set (the caller checked mpfr_all_depths_fit): every depth; otherwise depth a.s.
 template <bool BF16, int LAYOUT>
 hipError_t mpfr_sample(const MpfrArgs& a, hipStream_t stream) {
@@ -1244,9 +1284,9 @@ hipError_t mpfr_sample(const MpfrArgs& a, hipStream_t stream) {
 
 }  // namespace
 
-hipError_t mpfr_all_depths_fit(const MpfrArgs& a, bool bf16, int layout, bool* fits) {
-    if (bf16) return layout == 0 ? mpfr_fit<true, 0>(a, fits) : mpfr_fit<true, 1>(a, fits);
-    return layout == 0 ? mpfr_fit<false, 0>(a, fits) : mpfr_fit<false, 1>(a, fits);
+hipError_t mpfr_all_depths_fit(const MpfrArgs& a, bool bf16, int layout, bool* fits, bool* beside) {
+    if (bf16) return layout == 0 ? mpfr_fit<true, 0>(a, fits, beside) : mpfr_fit<true, 1>(a, fits, beside);
+    return layout == 0 ? mpfr_fit<false, 0>(a, fits, beside) : mpfr_fit<false, 1>(a, fits, beside);
 }
 
 hipError_t launch_mpfr_sample(const MpfrArgs& a, bool bf16, int layout, hipStream_t stream) {
