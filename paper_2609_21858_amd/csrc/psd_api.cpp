@@ -448,8 +448,8 @@ namespace {
 // until the walk, so the fused kernel races it (without the walk) on the side
 // stream while the drafts are sampled on the caller's stream (the draft rows are
 // streamed on whichever stream lets the sampling start soonest); the walk kernel
-// follows both.  The race kernel's error bits go to a control word that the walk
-// kernel adds to the call's status.
+// follows both, and ends the call's epoch.  The race kernel's error bits go to a control
+// word that the walk kernel adds to the call's status.
 psd_status verify_mpfr_forked(const psd_params* params, const psd_block* block, const void* target_logits,
                               const void* draft_logits, int32_t* draft_tokens, int32_t* out_tokens,
                               int32_t* out_len, float* target_lse, float* draft_lse, int32_t* target_tokens,
@@ -473,6 +473,7 @@ psd_status verify_mpfr_forked(const psd_params* params, const psd_block* block, 
     build_depths(a, block->gamma + 1);
     a.walk_kind = -1;  // no row walks: the walk kernel does, after the drafts
     a.status = ctrl + psd::kCtrlRaceBits;
+    a.keep_epoch = 1;  // (streaming workgroups may still start: the walk kernel records it)
     psd::MpfrArgs m = mpfr_args(params, block, 0, block->gamma, draft_logits, draft_tokens, draft_lse);
     bool by_depth = false, beside = false;
     psd_status st = mpfr_prepare(params, block, m, &by_depth, &beside);
@@ -547,6 +548,7 @@ psd_status verify_mpfr_forked(const psd_params* params, const psd_block* block, 
     w.ctrl = ctrl;
     w.status = block->status;
     w.status_in = ctrl + psd::kCtrlRaceBits;
+    w.advance_epoch = 1;
     if ((e = psd::launch_walk(w, stream)) != hipSuccess) return hip_fail(e, "walk kernel launch");
     return PSD_OK;
 }

@@ -10,10 +10,6 @@ namespace psd {
 // Control word that carries the race kernel's share of a call's error bits to a
 // later walk kernel of the same call (a word the race kernel uses for nothing else).
 constexpr int kCtrlRaceBits = 7;
-// Epoch of the last identical-drafter launch that ran every depth, and its workgroups
-// that have left (words of their own: the race kernel may run beside it).
-constexpr int kCtrlMpfrEpoch = 8;
-constexpr int kCtrlMpfrExited = 9;
 
 struct DetectArgs {
     const int32_t* tokens;  // [n_seq][row_stride], positions [0, seq_len) of each row scored
@@ -59,7 +55,7 @@ struct MpfrArgs {
     int s_begin, s_count, s;    // depth of this launch: s_begin <= s < s_begin + s_count
     float T, invT;
     // Written by the streaming launches and read by the sampling launches (draft row ids).
-    // With tok_slot each word is (epoch << 32) | payload: a sampling launch that runs every
+    // With tok_slot each word is (the call's epoch << 32) | payload: a sampling launch that runs every
     // depth may run beside the streaming launch and waits for the tags.  Otherwise the
     // streams order the launches and the tag is 0.  row_max and row_seed may be null: the
     // sampling launches then find both from the group maxima.
@@ -172,6 +168,7 @@ struct TopkRaceArgs {
     uint32_t* status;        // nullable: the call's error bits for the caller
     const uint32_t* status_in;  // nullable: bits already taken from the call by an earlier
                                 // kernel of the same call, added to *status
+    int advance_epoch;       // the walk is the last kernel of a call whose words are tagged
 };
 
 // Position-indexed toy language model: target rows [B][gamma+1][V] at positions
@@ -222,6 +219,8 @@ hipError_t launch_mpfr_sample(const MpfrArgs& a, bool bf16, int layout, hipStrea
 // returned.
 hipError_t mpfr_all_depths_fit(const MpfrArgs& a, bool bf16, int layout, bool* fits, bool* beside);
 hipError_t launch_mpfr_stream(const MpfrArgs& a, bool bf16, hipStream_t stream);
+// The call's error bits to the sticky word and the caller's status word, and the end of
+// the call's epoch, for calls that end with neither a race kernel nor a walk.
 hipError_t launch_finish_status(uint32_t* ctrl, uint32_t* status, hipStream_t stream);
 hipError_t launch_detect(const DetectArgs& a, int layout, hipStream_t stream);
 hipError_t launch_pvalue(int n, const double* score, const int32_t* count, double* out_log_p,

@@ -30,7 +30,10 @@ inline constexpr int ctrl_queue(int q) { return 64 * (q + 1); }
 // Every slot a call publishes is (epoch << 32) | 32-bit payload, with the call's
 // epoch (1 .. 2^32-1) in the same bits for every slot kind, so readers detect fresh
 // data by its tag, stale data of another call shape never matches, and nothing is
-// cleared between calls:
+// cleared between calls.  Every kernel of a call takes its epoch from kCtrlEpoch, and only
+// the call's last kernel, once all others have ended, records it there: a workgroup that
+// is dispatched late still has its own call's epoch, and no two calls on a workspace
+// share one.
 //   tok  : payload = int32 token
 //   part : payload = float bits of the segment's sum of exp2 (relative to its max)
 //   gmax : payload = float bits of the group's maximum logit
@@ -130,6 +133,7 @@ struct RaceArgs {
     uint32_t* status;     // nullable: this call's error bits, written by its last workgroup
     uint32_t spin_limit;  // polls of a bounded wait before it gives up (psd_set_spin_limit)
     int max_grid;         // most workgroups of the launch (0: as many as fit the device)
+    int keep_epoch;       // a later kernel of the call records its epoch (else the last workgroup does)
 };
 
 }  // namespace psd

@@ -108,7 +108,7 @@ struct MShared {
     uint32_t kappa0, kappa1;
     int samples[32];
     int own[32];               // this path's drafts so far
-    uint32_t epoch;            // this launch's tag of the handed-over drafts (multi-depth launch)
+    uint32_t epoch;            // the call's tag of the handed-over drafts (multi-depth launch)
     int row_late;              // the depth's row has not come (set by any thread)
 };
 
@@ -608,20 +608,8 @@ __device__ __forceinline__ uint32_t mld_dev_u32(const uint32_t* p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// The call's epoch for its tagged words: one more than the last recorded (1 .. 2^32-1).
-__device__ __forceinline__ uint32_t next_epoch(const MpfrArgs& a) {
-    const uint32_t last = mld_dev_u32(a.ctrl + kCtrlMpfrEpoch);
-    return last == 0xFFFFFFFFu ? 1u : last + 1u;
-}
-
-// The last workgroup of a launch to leave resets the exit count and records the epoch.
-__device__ __forceinline__ void record_epoch(const MpfrArgs& a, uint32_t ep) {
-    const uint32_t old = __hip_atomic_fetch_add(a.ctrl + kCtrlMpfrExited, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (old == gridDim.x - 1) {
-        __hip_atomic_store(a.ctrl + kCtrlMpfrExited, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(a.ctrl + kCtrlMpfrEpoch, ep, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-}
+// The call's epoch for its tagged words.
+__device__ __forceinline__ uint32_t call_epoch(const MpfrArgs& a) { return epoch_after(mld_dev_u32(a.ctrl + kCtrlEpoch)); }
 
 // The streaming launch over the draft rows of depths [stream_s, stream_s + stream_n),
 // depth-major (the first depth's rows are handed out first), one row per workgroup or
@@ -637,7 +625,7 @@ __global__ __launch_bounds__(kMBlock, kJointPerCu) void mpfr_stream_kernel(MpfrA
     const int n = a.B * a.K;
     const int ng = (a.V + 127) / 128;
     const size_t esize = BF16 ? 2 : 4;
-    if (threadIdx.x == 0) ep_s = a.tok_slot ? next_epoch(a) : 0u;  // (tag 0: ordered by the streams, no reader waits)
+    if (threadIdx.x == 0) ep_s = a.tok_slot ? call_epoch(a) : 0u;  // (tag 0: ordered by the streams, no reader waits)
     // rows blockIdx.x, blockIdx.x + gridDim.x, ...: with fewer workgroups than rows, the
     // first depths' rows land first
     for (int r = (int)blockIdx.x; r < n * a.stream_n; r += (int)gridDim.x) {
@@ -926,7 +914,7 @@ __device__ __forceinline__ bool sorted_samples(const MpfrArgs& a, MShared& sm, i
 // (in), at depth s (out).  first: no earlier depth was run by this workgroup (the
 // context is formed from the caller's drafts at every depth < s).  mine: this workgroup
 // sampled that context (in: at depth s - 1, out: at depth s), so it knows the drafts
-// without waiting for them.  ep: the launch's epoch when it runs every depth.  polls: of a
+// without waiting for them.  ep: the call's epoch when the launch runs every depth.  polls: of a
 // wait for a streamed word.
 template <bool BF16, int LAYOUT>
 __device__ __forceinline__ void mpfr_depth(const MpfrArgs& a, MShared& sm, float* gm, int b, int k, int s, uint32_t ep,
@@ -1215,8 +1203,7 @@ __device__ __forceinline__ void mpfr_depth(const MpfrArgs& a, MShared& sm, float
 // earlier depths as they land.  A workgroup waits for the drafts of its context's lowest
 // path alone, whose workgroup has a lower index (path-major), and for streamed rows only
 // for a while (row_word): the running workgroup of lowest index depends on none that
-// might not be dispatched.  The last workgroup to leave resets the exit count and records
-// the launch's epoch.
+// might not be dispatched.
 template <bool BF16, int LAYOUT>
 __global__ __launch_bounds__(kMBlock, kJointPerCu) void mpfr_draft_kernel(MpfrArgs a) {
     __shared__ MShared sm;
@@ -1233,22 +1220,22 @@ __global__ __launch_bounds__(kMBlock, kJointPerCu) void mpfr_draft_kernel(MpfrAr
         mpfr_depth<BF16, LAYOUT>(a, sm, gm, b, k, a.s, 0u, polls, true, mask, mine);
         return;
     }
-    if (threadIdx.x == 0) sm.epoch = next_epoch(a);
+    if (threadIdx.x == 0) sm.epoch = call_epoch(a);
     __syncthreads();
     const uint32_t ep = sm.epoch;
     for (int s = a.s_begin; s < a.s_begin + a.s_count; ++s) {
         mpfr_depth<BF16, LAYOUT>(a, sm, gm, b, k, s, ep, polls, s == a.s_begin, mask, mine);
         __syncthreads();
     }
-    if (threadIdx.x == 0) record_epoch(a, ep);
 }
 
-// The call's error bits to the sticky word and the caller's status word (for calls
-// that end without a fused race kernel, whose last workgroup does this).
+// The call's error bits to the sticky word and the caller's status word, and its epoch
+// (for calls that end without a fused race kernel, whose last workgroup does this).
 __global__ void finish_status_kernel(uint32_t* ctrl, uint32_t* status) {
     const uint32_t bits = __hip_atomic_exchange(ctrl + kCtrlCallErrors, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (bits) __hip_atomic_fetch_or(ctrl + kCtrlErrors, bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (status) *status = bits;
+    ctrl[kCtrlEpoch] = epoch_after(ctrl[kCtrlEpoch]);
 }
 
 }  // namespace

@@ -1794,8 +1794,7 @@ __global__ __launch_bounds__(kBlock, 4) void race_kernel(RaceArgs a) {
     const int q = (int)(blockIdx.x % (unsigned)nq);
     if (tid == 0) {
         sm.err_local = 0u;
-        const uint32_t last = ld_dev(ctrl + kCtrlEpoch);
-        sm.epoch = last == 0xFFFFFFFFu ? 1u : last + 1u;  // 1 .. 2^32-1
+        sm.epoch = epoch_after(ld_dev(ctrl + kCtrlEpoch));
         sm.tick[0] = finisher ? take_row(a, q, nq) : take_item(a, q, nq);
     }
     for (int i = tid; i < a.n_phase; i += kBlock) {
@@ -1860,7 +1859,7 @@ __global__ __launch_bounds__(kBlock, 4) void race_kernel(RaceArgs a) {
         }
     }
     // The last workgroup to leave resets the queues, hands over the call's error bits
-    // and advances the epoch.  A workgroup that recorded errors fences (release)
+    // and (unless a later kernel of the call does) records the epoch.  A workgroup that recorded errors fences (release)
     // before it counts its exit, and the last one fences (acquire) after it: its
     // read of the call's bits then sees every error of the call.  The exit count
     // itself stays relaxed (a release per workgroup writes back its L2: ~19 us).
@@ -1876,7 +1875,7 @@ __global__ __launch_bounds__(kBlock, 4) void race_kernel(RaceArgs a) {
             if (a.status) *a.status = bits;
             for (int i = 0; i < 2 * kMaxQueues; ++i) st_dev(ctrl + ctrl_queue(i), 0u);
             st_dev(ctrl + kCtrlExited, 0u);
-            st_dev(ctrl + kCtrlEpoch, sm.epoch);
+            if (!a.keep_epoch) st_dev(ctrl + kCtrlEpoch, sm.epoch);
         }
     }
 }

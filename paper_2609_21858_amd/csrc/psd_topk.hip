@@ -1091,13 +1091,15 @@ __device__ void wave_mpfr(const TopkRaceArgs& a, RaceShared& sm, int rid, uint32
     }
 }
 
-// The call's error bits to the sticky word and the caller's status word (one thread).
+// The call's error bits to the sticky word and the caller's status word, and its epoch
+// where its words are tagged (one thread).
 // The list kernels set none themselves, so the first workgroup of the call's last
 // launch does this at its start (a launch of its own took 4.4 us and a gap).
 __device__ __forceinline__ void hand_over_status(const TopkRaceArgs& a) {
     const uint32_t bits = __hip_atomic_exchange(a.ctrl + kCtrlCallErrors, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (bits) __hip_atomic_fetch_or(a.ctrl + kCtrlErrors, bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (a.status) *a.status = bits | (a.status_in ? *a.status_in : 0u);
+    if (a.advance_epoch) a.ctrl[kCtrlEpoch] = epoch_after(a.ctrl[kCtrlEpoch]);
 }
 
 template <int LAYOUT>

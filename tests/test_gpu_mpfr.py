@@ -296,7 +296,7 @@ def test_mpfr_epoch_across_sampling_forms(psd):
     """Two block shapes share one workspace: B K = 1000, more workgroups than fit the
     device together at this kernel's occupancy (768 on MI355X) but still under the
     streaming launch's limit, so one sampling launch per depth follows a streaming
-    launch that records the call's epoch; and B K = 128,
+    launch; and B K = 128,
     where one sampling launch runs every depth beside the streaming launch and waits
     for its tagged words.  The shapes' tagged words sit at different offsets, so a stale
     tag would show up as a wrong draft.  Alternating the two, every call equals the same
@@ -327,9 +327,8 @@ def test_mpfr_epoch_across_sampling_forms(psd):
 
 def test_modes_alternate_on_one_workspace(psd):
     """Distinct-drafter and identical-drafter calls of one block alternate on one
-    workspace (sized for the larger): the race kernel's epoch and the identical-drafter
-    launches' epoch advance independently, and every call equals the same call on a
-    fresh workspace."""
+    workspace (sized for the larger): every call equals the same call on a fresh
+    workspace."""
     w = workloads.WORKLOADS[2]
     blk = workloads.make_block(w, 17, device=DEV)
     ph = psd.make_params(w.key, w.V, w.K, w.m, w.T_target, w.T_draft, dtype=w.torch_dtype)
