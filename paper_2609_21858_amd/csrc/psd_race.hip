@@ -973,8 +973,10 @@ __device__ __forceinline__ void eval_list(const RaceArgs& a, const Row& r, Share
         }
         __syncthreads();
     }
-    // (no candidate is listed before the next barrier, so every thread reads the same count)
+    // (no candidate is listed before the next barrier, and the compaction, which writes the
+    // count, starts when every thread has read it: all take the same branch)
     if (sm.n_cand > kCandCap / 2) {
+        __syncthreads();
         if (threadIdx.x == 0) compact_candidates(sm);
         __syncthreads();
     }
