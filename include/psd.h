@@ -132,7 +132,7 @@ typedef struct {
                                      with that call's 32-bit epoch, and the call's last workgroup resets
                                      the work queues and advances the epoch, so nothing needs clearing
                                      between calls, even of different shapes.  Clear it again after
-                                     4294967295 calls, after a launch that did not run to completion, or
+                                     4294443007 calls, after a launch that did not run to completion, or
                                      to reset the error bits.  One call at a time per workspace. */
     size_t workspace_bytes;
     uint32_t *status;             /* device, nullable: one word that the call's last workgroup sets to the

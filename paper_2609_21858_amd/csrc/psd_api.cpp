@@ -304,10 +304,8 @@ psd_status run_topk(const psd_params* p, const psd_block* b, int32_t s_begin, in
     s.top_k = p->top_k;
     s.top_p = p->top_p;
     s.cap = p->top_k;
-    s.list_tok = (int32_t*)(ws + T.tok);
-    s.list_val = (float*)(ws + T.val);
-    s.list_len = (int32_t*)(ws + T.len);
-    s.list_lse = (float*)(ws + T.lse);
+    s.list = (uint64_t*)(ws + T.list);
+    s.list_len = (uint32_t*)(ws + T.len);
     s.radix_rows = (uint32_t*)(ws + L.ctrl) + psd::kCtrlTopkRadix;
     int ns = 0;
     if (draft_logits && s_count > 0) {
@@ -340,8 +338,7 @@ psd_status run_topk(const psd_params* p, const psd_block* b, int32_t s_begin, in
     r.out_tokens = out_tokens;
     r.out_len = out_len;
     r.target_tokens = target_tokens;
-    r.list_tok = s.list_tok;
-    r.list_val = s.list_val;
+    r.list = s.list;
     r.list_len = s.list_len;
     r.cap = p->top_k;
     r.key = p->key;
@@ -356,7 +353,7 @@ psd_status run_topk(const psd_params* p, const psd_block* b, int32_t s_begin, in
     r.mpfr = p->mode == PSD_MODE_MPFR;
     r.T_target = p->temp_target;
     r.T_draft = p->temp_draft;
-    r.chain = (int32_t*)(ws + T.chain);
+    r.chain = (uint64_t*)(ws + L.tok) + (size_t)B * K * G;
     r.ctrl = (uint32_t*)(ws + L.ctrl);
     r.status = b->status;
     if ((e = psd::launch_topk_race(r, p->clocks, stream)) != hipSuccess) return hip_fail(e, "top-k race launch");
@@ -457,16 +454,14 @@ psd_status verify_mpfr_forked(const psd_params* params, const psd_block* block, 
     unsigned char* ws = (unsigned char*)block->workspace;
     const psd::WsLayout L = psd::ws_layout(block->batch, params->num_drafts, block->gamma, params->vocab,
                                            params->dtype == PSD_BF16);
-    const psd::MpfrLayout M = psd::mpfr_layout(L, block->batch, params->num_drafts, block->gamma);
     uint32_t* ctrl = (uint32_t*)(ws + L.ctrl);
-    int32_t* y = target_tokens ? target_tokens : (int32_t*)(ws + M.ytok);
     psd::RaceArgs a = base_args(params, block);
     a.target_logits = target_logits;
     a.draft_tokens = draft_tokens;
     a.out_tokens = out_tokens;
     a.out_len = out_len;
     a.target_lse = target_lse;
-    a.target_tokens = y;
+    a.target_tokens = target_tokens;
     a.s_begin = 0;
     a.s_count = 0;
     a.target_rows = 1;
@@ -541,7 +536,7 @@ psd_status verify_mpfr_forked(const psd_params* params, const psd_block* block, 
     w.draft_tokens = draft_tokens;
     w.out_tokens = out_tokens;
     w.out_len = out_len;
-    w.chain = y;
+    w.chain = (uint64_t*)(ws + L.tok) + (size_t)block->batch * params->num_drafts * block->gamma;
     w.K = params->num_drafts;
     w.B = block->batch;
     w.gamma = block->gamma;

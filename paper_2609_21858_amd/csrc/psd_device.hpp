@@ -10,6 +10,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "psd_layout.hpp"
+
 namespace psd {
 
 // ---------------------------------------------------------------- constants
@@ -33,8 +35,8 @@ constexpr int kGroupTokens = 128;
 // ln = -16.6355323.  Rounded down (a valid lower bound for every flat clock).
 constexpr float kLnClockFloor = -16.6356f;
 
-// The epoch of a call on a workspace whose last recorded one is `last` (1 .. 2^32-1).
-__device__ __forceinline__ uint32_t epoch_after(uint32_t last) { return last == 0xFFFFFFFFu ? 1u : last + 1u; }
+// The epoch of a call on a workspace whose last recorded one is `last` (1 .. kEpochEnd - 1).
+__device__ __forceinline__ uint32_t epoch_after(uint32_t last) { return last >= kEpochEnd - 1u ? 1u : last + 1u; }
 
 // ---------------------------------------------------------------- Philox
 

@@ -71,10 +71,9 @@ struct MpfrArgs {
 };
 
 // Identical drafters: the draft rows' group maxima and maxima, streamed once per call
-// ahead of the depth-by-depth sampling, after the race kernel's workspace, then the
-// shared target chain's tokens for a walk kernel that runs after the drafts.
+// ahead of the depth-by-depth sampling, after the race kernel's workspace.
 struct MpfrLayout {
-    size_t gm, rmax, seed, slot, ytok, total;
+    size_t gm, rmax, seed, slot, total;
 };
 // Identical-drafter calls with fewer than this many (sequence, path) workgroups per
 // depth stream every draft row in one launch, whose words have a region of their own;
@@ -89,32 +88,27 @@ inline MpfrLayout mpfr_layout(const WsLayout& L, int B, int K, int gamma) {
     M.rmax = align256(M.gm + rows * (size_t)L.ng * 8);
     M.seed = align256(M.rmax + rows * 8);
     M.slot = align256(M.seed + rows * 8 * 8);  // 8 seeds per row
-    M.ytok = align256(M.slot + rows * 8);      // one tagged draft per row
-    M.total = align256(M.ytok + (size_t)B * (gamma + 1) * 4);  // shared-chain targets [B][gamma+1]
+    // one tagged draft per row, then [B][gamma+1] words that nothing uses (they keep the
+    // workspace's size)
+    M.total = align256(align256(M.slot + rows * 8) + (size_t)B * (gamma + 1) * 4);
     return M;
 }
 
 // Truncation before the race (top-k, then top-p): per row a kept list of at most
-// top_k (token, logit) pairs, sorted, its length and LSE, after the race kernel's
-// workspace (same row identifiers).
+// top_k (token, logit) pairs, sorted, and its length, after the race kernel's
+// workspace (same row identifiers).  No word of them can pass for a tagged slot:
+//   list : uint64 (~token << 32) | logit bits
+//   len  : uint32 ~length
 constexpr int kMaxTopK = 256;
 struct TopkLayout {
-    size_t tok, val, len, lse, chain, total;  // offsets from the workspace base; total = end
+    size_t list, len, total;  // offsets from the workspace base; total = end
 };
 inline TopkLayout topk_layout(const WsLayout& L, int top_k) {
     TopkLayout T;
-    size_t o = L.total;
-    T.tok = o;
-    o = align256(o + (size_t)L.n_rows * top_k * 4);
-    T.val = o;
-    o = align256(o + (size_t)L.n_rows * top_k * 4);
-    T.len = o;
-    o = align256(o + (size_t)L.n_rows * 4);
-    T.lse = o;
-    o = align256(o + (size_t)L.n_rows * 4);
-    T.chain = o;  // shared target chain tokens [B][gamma + 1] (n_rows >= B (gamma + 1))
-    o = align256(o + (size_t)L.n_rows * 4);
-    T.total = o;
+    T.list = L.total;
+    T.len = T.list + 2 * align256((size_t)L.n_rows * top_k * 4);
+    // (two words per row after the lengths, which nothing uses, keep the workspace's size)
+    T.total = T.len + 3 * align256((size_t)L.n_rows * 4);
     return T;
 }
 
@@ -137,10 +131,8 @@ struct TopkSelectArgs {
     int top_k;
     float top_p;
     int cap;
-    int32_t* list_tok;
-    float* list_val;
-    int32_t* list_len;
-    float* list_lse;
+    uint64_t* list;      // [row id][cap]
+    uint32_t* list_len;  // [row id]
     uint32_t* radix_rows;  // nullable: counts rows whose one-pass selection could not be
                            // proven exact and were selected again by radix passes
 };
@@ -152,9 +144,8 @@ struct TopkRaceArgs {
     int32_t* out_tokens;     // [B][gamma+1] (target_rows > 0)
     int32_t* out_len;        // [B]
     int32_t* target_tokens;  // nullable
-    const int32_t* list_tok;
-    const float* list_val;
-    const int32_t* list_len;
+    const uint64_t* list;
+    const uint32_t* list_len;
     int cap;
     uint64_t key;
     int V, K, m, B, gamma;
@@ -163,7 +154,8 @@ struct TopkRaceArgs {
     int mpfr;
     float T_target, T_draft;
     int target_waves;        // waves sharing each shared-chain target race (set by the launcher)
-    int32_t* chain;          // workspace [B][gamma + 1]: shared-chain targets for the walk kernel
+    uint64_t* chain;         // the token slots [B][gamma + 1] of the shared target rows: their
+                             // payloads are the targets the walk kernel reads
     uint32_t* ctrl;          // workspace control words (the call's error bits)
     uint32_t* status;        // nullable: the call's error bits for the caller
     const uint32_t* status_in;  // nullable: bits already taken from the call by an earlier
@@ -205,8 +197,8 @@ hipError_t launch_toy_rows(const ToyArgs& a, bool bf16, hipStream_t stream);
 hipError_t launch_advance(const AdvanceArgs& a, hipStream_t stream);
 hipError_t launch_topk_select(const TopkSelectArgs& a, bool bf16, hipStream_t stream);
 hipError_t launch_topk_race(const TopkRaceArgs& a, int layout, hipStream_t stream);
-// The walk alone (one thread per sequence) over shared-chain targets a.chain
-// [B][gamma+1] and the drafts, then the call's error bits (with *a.status_in).
+// The walk alone (one thread per sequence) over the shared-chain targets a.chain
+// and the drafts, then the call's error bits (with *a.status_in).
 hipError_t launch_walk(const TopkRaceArgs& a, hipStream_t stream);
 
 hipError_t launch_race(const RaceArgs& a, bool bf16, int layout, hipStream_t stream);

@@ -28,7 +28,7 @@ constexpr int kMaxQueues = 8;      // work queues (one per XCD) of each kind, co
 inline constexpr int ctrl_queue(int q) { return 64 * (q + 1); }
 
 // Every slot a call publishes is (epoch << 32) | 32-bit payload, with the call's
-// epoch (1 .. 2^32-1) in the same bits for every slot kind, so readers detect fresh
+// epoch (1 .. kEpochEnd - 1) in the same bits for every slot kind, so readers detect fresh
 // data by its tag, stale data of another call shape never matches, and nothing is
 // cleared between calls.  Every kernel of a call takes its epoch from kCtrlEpoch, and only
 // the call's last kernel, once all others have ended, records it there: a workgroup that
@@ -43,6 +43,12 @@ inline constexpr int ctrl_queue(int q) { return 64 * (q + 1); }
 //   keys : two slots per row, payload = the two words of the context key of the
 //          next depth of the row's path (published by the row's race)
 //
+// Words that no reader waits for carry no epoch, and may lie where a call of another shape
+// has slots.  Those of the streams' order have tag 0; in the kept lists of truncated calls,
+// every 32-bit word that can be a slot's high half is the complement of a token or a length,
+// at least kEpochEnd: neither is the tag of any call.
+constexpr uint32_t kEpochEnd = 0xFFF80000u;  // ~(2^19 - 1), the complement of the largest token
+
 // Row identifiers (independent of the call):
 //   draft (b, k, s)            : (b*K + k)*gamma + s
 //   target shared (b, s)       : D + b*(gamma+1) + s                 D = B*K*gamma

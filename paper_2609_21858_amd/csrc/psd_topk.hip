@@ -654,8 +654,7 @@ __global__ __launch_bounds__(kTBlock) void topk_select_kernel(TopkSelectArgs a) 
     }
     if (need == 0) {
         if (tid == 0) {
-            a.list_len[rid] = 0;
-            a.list_lse[rid] = -INFINITY;
+            a.list_len[rid] = ~0u;
             if (G.lse_out) G.lse_out[lse_at] = -INFINITY;
         }
         return;
@@ -685,16 +684,11 @@ __global__ __launch_bounds__(kTBlock) void topk_select_kernel(TopkSelectArgs a) 
     __syncthreads();
     if (tid == 0) {
         const float lse = (float)(z0 + log(sm.dsel));
-        a.list_len[rid] = keep;
-        a.list_lse[rid] = lse;
+        a.list_len[rid] = ~(uint32_t)keep;
         if (G.lse_out) G.lse_out[lse_at] = lse;
     }
-    int32_t* out_tok = a.list_tok + (size_t)rid * a.cap;
-    float* out_val = a.list_val + (size_t)rid * a.cap;
-    if (tid < keep) {
-        out_tok[tid] = sm.stok[tid];
-        out_val[tid] = sm.sval[tid];
-    }
+    if (tid < keep)
+        a.list[(size_t)rid * a.cap + tid] = ((uint64_t)~(uint32_t)sm.stok[tid] << 32) | __float_as_uint(sm.sval[tid]);
 }
 
 // ---------------------------------------------------------------- races over the lists
@@ -798,6 +792,11 @@ __device__ __forceinline__ void best2_wave(Best2& b) {
 // Whether the smallest score is certain (an empty set, or one of infinite scores, is).
 __device__ __forceinline__ bool best2_clear(const Best2& b) { return !(b.s2 - b.s1 <= kTMargin); }
 
+// A kept list's length, and the token and logit of an entry (psd_launch.hpp, TopkLayout).
+__device__ __forceinline__ int list_length(const TopkRaceArgs& a, int rid) { return (int)~a.list_len[rid]; }
+__device__ __forceinline__ int entry_token(uint64_t e) { return (int)~(uint32_t)(e >> 32); }
+__device__ __forceinline__ float entry_logit(uint64_t e) { return __uint_as_float((uint32_t)e); }
+
 // The race of one row's list over slots [slot0, slot0 + nslots) -- argmin of
 // ln E_j[v] - l_v / T (exact, fp64) -- over the (token, slot) entries of 64-entry units
 // part, part + nparts, ... by one wave.  Returns the wave's winning token (-1 when it
@@ -806,15 +805,15 @@ template <int LAYOUT>
 __device__ int wave_race(const TopkRaceArgs& a, int rid, int slot0, int nslots, float T, uint32_t k0, uint32_t k1,
                          int part = 0, int nparts = 1, double* out_s = nullptr, int* out_j = nullptr) {
     const int lane = threadIdx.x & 63;
-    const int n = a.list_len[rid];
-    const int* lt = a.list_tok + (size_t)rid * a.cap;
-    const float* lv = a.list_val + (size_t)rid * a.cap;
+    const int n = list_length(a, rid);
+    const uint64_t* list = a.list + (size_t)rid * a.cap;
     double bs = INFINITY;
     int bv = 0x7FFFFFFF, bj = 0x7FFFFFFF, bc = -1;
     for (int e = part * 64 + lane; e < n * nslots; e += 64 * nparts) {
         const int c = e / nslots, j = slot0 + e % nslots;
-        const int v = lt[c];
-        const double s = log(tclock<LAYOUT>((uint32_t)a.V, (uint32_t)j, (uint32_t)v, k0, k1)) - (double)lv[c] / (double)T;
+        const uint64_t le = list[c];
+        const int v = entry_token(le);
+        const double s = log(tclock<LAYOUT>((uint32_t)a.V, (uint32_t)j, (uint32_t)v, k0, k1)) - (double)entry_logit(le) / (double)T;
         if (tlex(s, v, j, bs, bv, bj)) {
             bs = s;
             bv = v;
@@ -841,8 +840,9 @@ struct ListHead {
 
 __device__ __forceinline__ ListHead list_head(const TopkRaceArgs& a, int rid, int nslots, int part) {
     const int c = min((part * 64 + (int)(threadIdx.x & 63)) / nslots, a.cap - 1);
-    return ListHead{a.list_len[rid], a.list_tok[(size_t)rid * a.cap + c], a.list_val[(size_t)rid * a.cap + c],
-                    a.list_val[(size_t)rid * a.cap]};
+    const uint64_t* list = a.list + (size_t)rid * a.cap;
+    const uint64_t e = list[c];
+    return ListHead{list_length(a, rid), entry_token(e), entry_logit(e), entry_logit(list[0])};
 }
 
 // The float32 scores of the row's (token, slot) entries of 64-entry units part, part +
@@ -853,8 +853,7 @@ __device__ Best2 wave_race32(const TopkRaceArgs& a, const ListHead& h, int rid, 
                              uint32_t k0, uint32_t k1, int part, int nparts) {
     const int lane = threadIdx.x & 63;
     const int n = h.n;
-    const int* lt = a.list_tok + (size_t)rid * a.cap;
-    const float* lv = a.list_val + (size_t)rid * a.cap;
+    const uint64_t* list = a.list + (size_t)rid * a.cap;
     const float invT = 1.0f / T;
     // (token, slot) packed as token * 32 + slot (tokens < 2^19, slots < 32)
     // (a +inf logit has no float32 score here: never certain, so the exact race decides)
@@ -862,8 +861,9 @@ __device__ Best2 wave_race32(const TopkRaceArgs& a, const ListHead& h, int rid, 
     Best2 b{INFINITY, INFINITY, -1};
     for (int e = part * 64 + lane, first = 1; e < n * nslots; e += 64 * nparts, first = 0) {
         const int c = e / nslots, j = slot0 + e % nslots;
-        const int v = first ? h.v : lt[c];
-        const float x = first ? h.x : lv[c];
+        const uint64_t le = first ? 0u : list[c];
+        const int v = first ? h.v : entry_token(le);
+        const float x = first ? h.x : entry_logit(le);
         best2_add(b, ln_f32(tclock32<LAYOUT>((uint32_t)a.V, (uint32_t)j, (uint32_t)v, k0, k1)) - (x - h.xmax) * invT,
                   (v << 5) | j);
     }
@@ -894,15 +894,16 @@ struct ListAll {
 };
 __device__ __forceinline__ ListAll list_all(const TopkRaceArgs& a, int rid) {
     ListAll h;
-    h.n = a.list_len[rid];
+    h.n = list_length(a, rid);
+    const uint64_t* list = a.list + (size_t)rid * a.cap;
     const int lane = (int)(threadIdx.x & 63);
 #pragma unroll
     for (int q = 0; q < kMaxTopK / 64; ++q) {
-        const size_t c = (size_t)rid * a.cap + min(lane + 64 * q, a.cap - 1);  // (inside the row's list)
-        h.tok[q] = 64 * q < a.cap ? a.list_tok[c] : -1;
-        h.x[q] = 64 * q < a.cap ? a.list_val[c] : 0.f;
+        const uint64_t e = 64 * q < a.cap ? list[min(lane + 64 * q, a.cap - 1)] : 0u;  // (inside the row's list)
+        h.tok[q] = entry_token(e);
+        h.x[q] = entry_logit(e);
     }
-    h.xmax = a.list_val[(size_t)rid * a.cap];
+    h.xmax = entry_logit(list[0]);
     return h;
 }
 
@@ -1025,10 +1026,9 @@ __device__ void wave_mpfr(const TopkRaceArgs& a, RaceShared& sm, int rid, uint32
                           uint32_t k0, uint32_t k1) {
     constexpr int Q = kMaxTopK / 64;
     const int lane = threadIdx.x & 63;
-    const int n = a.list_len[rid];
+    const int n = list_length(a, rid);
     const int nu = __popc(members);
-    const int* lt = a.list_tok + (size_t)rid * a.cap;
-    const float* lv = a.list_val + (size_t)rid * a.cap;
+    const uint64_t* list = a.list + (size_t)rid * a.cap;
     double Gs[Q], sc[Q], lT[Q];
     int tok[Q], jj[Q];
 #pragma unroll
@@ -1036,8 +1036,9 @@ __device__ void wave_mpfr(const TopkRaceArgs& a, RaceShared& sm, int rid, uint32
         const int c = lane + 64 * q;
         jj[q] = 0;
         if (c < n) {
-            tok[q] = lt[c];
-            lT[q] = (double)lv[c] / (double)T;
+            const uint64_t e = list[c];
+            tok[q] = entry_token(e);
+            lT[q] = (double)entry_logit(e) / (double)T;
             Gs[q] = tclock<LAYOUT>((uint32_t)a.V, 0u, (uint32_t)tok[q], k0, k1);
             sc[q] = log(Gs[q]) - lT[q];
         } else {
@@ -1392,7 +1393,7 @@ __global__ __launch_bounds__(64 * (kChainWaves + 1)) void topk_chain_kernel(Topk
         }
     }
     for (int s = tid; s <= G; s += blockDim.x) {
-        a.chain[(size_t)b * (G + 1) + s] = sm.path[s];
+        a.chain[(size_t)b * (G + 1) + s] = (uint32_t)sm.path[s];  // (tag 0: the walk is a later launch)
         if (a.target_tokens) a.target_tokens[(size_t)b * (G + 1) + s] = sm.path[s];
     }
 }
@@ -1414,9 +1415,9 @@ __global__ __launch_bounds__(64 * kWalkWaves) void topk_walk_kernel(TopkRaceArgs
     int32_t* v = vals[wave];
     const int nt = G + 1, n = nt + K * G;  // n <= kWalkVals (K and gamma are checked by the caller)
     if (valid) {
-        const int32_t* y = a.chain + (size_t)b * nt;
+        const uint64_t* y = a.chain + (size_t)b * nt;
         const int32_t* d = a.draft_tokens + (size_t)b * K * G;
-        for (int e = lane; e < n; e += 64) v[e] = e < nt ? y[e] : d[e - nt];
+        for (int e = lane; e < n; e += 64) v[e] = e < nt ? (int32_t)(uint32_t)y[e] : d[e - nt];
     }
     __syncthreads();
     if (!valid || lane != 0) return;

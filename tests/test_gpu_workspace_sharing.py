@@ -112,3 +112,37 @@ def test_one_epoch_for_every_word_of_a_call(psd):
     # (at depth 0 the first path's row serves every path)
     streamed = [r for r in range(rows) if r % 4 != 0 or (r // 4) % 4 == 0]
     assert (tags[streamed] == 3).all()
+
+
+@pytest.mark.parametrize("mode", ["het", "mpfr"])
+@pytest.mark.parametrize("rows,top_k", [("shared", 0), ("paths", 0), ("shared", 7), ("paths", 40)])
+@pytest.mark.parametrize("K", [1, 4])
+def test_no_word_has_the_tag_of_another_call(psd, mode, rows, top_k, K):
+    """After one call on a zeroed workspace, every word that another shape may read as a
+    slot has tag 0, that call's own epoch, or a high half that is no epoch (the complement
+    of a token or a length)."""
+    c = Call(psd, mode, 6, top_k, rows, seed=3, V=5000, K=K, gamma=3)
+    ws = torch.zeros(c.bytes, dtype=torch.uint8, device=DEV)
+    b = c.blk
+    if K == 4:
+        c.check(ws, 0)
+    else:  # (the targets not asked for: the walk takes them from the workspace)
+        out = psd.verify(c.params, ws, b["prefix_tokens"], b["start_pos"], b["target_logits"], b["draft_logits"],
+                         target_rows=c.tr)
+        assert torch.equal(out["out_tokens"].cpu(), c.want["out_tokens"])
+    tags = ws[8192:c.bytes // 8 * 8].view(torch.int32).view(-1, 2)[:, 1].cpu().long() & 0xFFFFFFFF
+    epoch = int(ws[4 * EPOCH_WORD:4 * EPOCH_WORD + 4].view(torch.int32)[0])
+    other = tags[(tags != 0) & (tags != epoch) & (tags < 0xFFF80000)]
+    assert other.numel() == 0, other[:8].tolist()
+
+
+@pytest.mark.parametrize("mode,top_k", [("het", 0), ("mpfr", 0)])
+def test_last_epochs(psd, mode, top_k):
+    """The epochs before the last one and after it wrap to 1, never to a kept list's words."""
+    c = Call(psd, mode, 2, top_k, seed=4, V=3000, K=2, gamma=2)
+    ws = torch.zeros(c.bytes, dtype=torch.uint8, device=DEV)
+    word = ws[4 * EPOCH_WORD:4 * EPOCH_WORD + 4].view(torch.int32)
+    word.fill_(0xFFF80000 - 2 - (1 << 32))
+    for want in (0xFFF80000 - 1, 1, 2):
+        c.check(ws, want)
+        assert int(word[0]) & 0xFFFFFFFF == want
