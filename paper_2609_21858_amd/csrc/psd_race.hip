@@ -955,6 +955,9 @@ __device__ __forceinline__ void eval_list(const RaceArgs& a, const Row& r, Share
     for (int first = 0; first < n;) {
         const int cnt = min(n - first, step);
         list_halves<BF16>(a, r, sm, gm, first, cnt, par);
+        // (between the barriers after the last candidate was listed and before the next is;
+        // thread 0 alone reads the count, so no other's path depends on it)
+        if (threadIdx.x == 0) compact_candidates(sm);
         __syncthreads();
         const int nh = (int)sm.n_ev[par];
         if (threadIdx.x == 0) {
@@ -971,13 +974,6 @@ __device__ __forceinline__ void eval_list(const RaceArgs& a, const Row& r, Share
             if (again) step = max(8, cnt >> 1);
             again = true;
         }
-        __syncthreads();
-    }
-    // (no candidate is listed before the next barrier, and the compaction, which writes the
-    // count, starts when every thread has read it: all take the same branch)
-    if (sm.n_cand > kCandCap / 2) {
-        __syncthreads();
-        if (threadIdx.x == 0) compact_candidates(sm);
         __syncthreads();
     }
 }
