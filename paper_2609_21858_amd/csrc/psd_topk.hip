@@ -832,17 +832,18 @@ __device__ int wave_race(const TopkRaceArgs& a, int rid, int slot0, int nslots, 
 // A lane's first (token, slot) entry of a list race, loaded ahead: the list's length
 // and the token and logit of the lane's entry (its index clamped into the row's list,
 // so the loads never wait for the length and never leave the list), and the list's
-// largest logit.
+// largest logit.  Length and entry stay as stored until they are used: undoing the
+// complement where they are loaded would wait for the loads there.
 struct ListHead {
-    int n, v;
-    float x, xmax;
+    uint32_t len;
+    uint64_t e;
+    float xmax;
 };
 
 __device__ __forceinline__ ListHead list_head(const TopkRaceArgs& a, int rid, int nslots, int part) {
     const int c = min((part * 64 + (int)(threadIdx.x & 63)) / nslots, a.cap - 1);
     const uint64_t* list = a.list + (size_t)rid * a.cap;
-    const uint64_t e = list[c];
-    return ListHead{list_length(a, rid), entry_token(e), entry_logit(e), entry_logit(list[0])};
+    return ListHead{a.list_len[rid], list[c], entry_logit(list[0])};
 }
 
 // The float32 scores of the row's (token, slot) entries of 64-entry units part, part +
@@ -852,21 +853,24 @@ template <int LAYOUT>
 __device__ Best2 wave_race32(const TopkRaceArgs& a, const ListHead& h, int rid, int slot0, int nslots, float T,
                              uint32_t k0, uint32_t k1, int part, int nparts) {
     const int lane = threadIdx.x & 63;
-    const int n = h.n;
+    const int n = (int)~h.len;
     const uint64_t* list = a.list + (size_t)rid * a.cap;
     const float invT = 1.0f / T;
     // (token, slot) packed as token * 32 + slot (tokens < 2^19, slots < 32)
     // (a +inf logit has no float32 score here: never certain, so the exact race decides)
     if (n > 0 && !(h.xmax < INFINITY)) return Best2{0.f, 0.f, -1};
     Best2 b{INFINITY, INFINITY, -1};
-    for (int e = part * 64 + lane, first = 1; e < n * nslots; e += 64 * nparts, first = 0) {
-        const int c = e / nslots, j = slot0 + e % nslots;
-        const uint64_t le = first ? 0u : list[c];
-        const int v = first ? h.v : entry_token(le);
-        const float x = first ? h.x : entry_logit(le);
-        best2_add(b, ln_f32(tclock32<LAYOUT>((uint32_t)a.V, (uint32_t)j, (uint32_t)v, k0, k1)) - (x - h.xmax) * invT,
+    auto add = [&](int e, uint64_t le) {
+        const int v = entry_token(le), j = slot0 + e % nslots;
+        best2_add(b, ln_f32(tclock32<LAYOUT>((uint32_t)a.V, (uint32_t)j, (uint32_t)v, k0, k1)) -
+                         (entry_logit(le) - h.xmax) * invT,
                   (v << 5) | j);
-    }
+    };
+    // (the first entry apart: a wait for a loaded one would also wait for the next race's
+    // list, which is in flight)
+    int e = part * 64 + lane;
+    if (e < n * nslots) add(e, h.e);
+    for (e += 64 * nparts; e < n * nslots; e += 64 * nparts) add(e, list[e / nslots]);
     best2_wave(b);
     return b;
 }
@@ -889,20 +893,18 @@ __device__ int wave_race_one(const TopkRaceArgs& a, const ListHead& h, int rid, 
 constexpr int kTFin = 64;
 // h: the list, loaded ahead.
 struct ListAll {
-    int n, tok[kMaxTopK / 64];
-    float x[kMaxTopK / 64], xmax;
+    uint32_t len;
+    uint64_t e[kMaxTopK / 64];
+    float xmax;
 };
 __device__ __forceinline__ ListAll list_all(const TopkRaceArgs& a, int rid) {
     ListAll h;
-    h.n = list_length(a, rid);
+    h.len = a.list_len[rid];
     const uint64_t* list = a.list + (size_t)rid * a.cap;
     const int lane = (int)(threadIdx.x & 63);
 #pragma unroll
-    for (int q = 0; q < kMaxTopK / 64; ++q) {
-        const uint64_t e = 64 * q < a.cap ? list[min(lane + 64 * q, a.cap - 1)] : 0u;  // (inside the row's list)
-        h.tok[q] = entry_token(e);
-        h.x[q] = entry_logit(e);
-    }
+    for (int q = 0; q < kMaxTopK / 64; ++q)
+        h.e[q] = 64 * q < a.cap ? list[min(lane + 64 * q, a.cap - 1)] : 0u;  // (inside the row's list)
     h.xmax = entry_logit(list[0]);
     return h;
 }
@@ -921,7 +923,7 @@ __device__ bool wave_mpfr32(const TopkRaceArgs& a, RaceShared& sm, int w, const 
                             float T, uint32_t k0, uint32_t k1) {
     constexpr int Q = kMaxTopK / 64;
     const int lane = threadIdx.x & 63;
-    const int n = h.n;
+    const int n = (int)~h.len;
     const int nu = __popc(members);
     if (n == 0) {
         if (lane < nu) {
@@ -942,8 +944,8 @@ __device__ bool wave_mpfr32(const TopkRaceArgs& a, RaceShared& sm, int w, const 
         xs[q] = G[q] = 0.f;
         sc[q] = INFINITY;
         if (c < n) {
-            tok[q] = h.tok[q];
-            xs[q] = (h.x[q] - xmax) * invT;
+            tok[q] = entry_token(h.e[q]);
+            xs[q] = (entry_logit(h.e[q]) - xmax) * invT;
             G[q] = tclock32<LAYOUT>((uint32_t)a.V, 0u, (uint32_t)tok[q], k0, k1);
             sc[q] = ln_f32(G[q]) - xs[q];
         }
