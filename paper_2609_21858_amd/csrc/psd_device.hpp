@@ -298,8 +298,16 @@ __device__ __forceinline__ uint32_t wave_incl_sum(uint32_t v) {
 // 2^kRefSlack and their sum far below the float range, and the sum's relative precision
 // does not depend on the reference.  (Raising it to every new maximum costs an
 // exponential and four more instructions per 8 values.)
-constexpr float kNegBig = -1e30f;   // finite stand-in for the reference of no value (no inf - inf)
+// Terms are exp2(fma(x, c2, -m)), whose argument carries the rounding of the reference m to
+// float32: at most 32 up to 2^30 in size, which keeps every term and sum finite.  No
+// reference is below -2^30 (values below it add 0), and a row whose maximum is beyond 2^30
+// in size is summed again relative to that maximum.
+constexpr float kFarScaled = 0x1p30f;
+constexpr float kNegBig = -kFarScaled;  // reference of no value (finite: no inf - inf)
 constexpr float kRefSlack = 60.f;
+__device__ __forceinline__ bool far_row(float rowmax, float c2) {
+    return fabsf(rowmax) < INFINITY && fabsf(rowmax) * c2 > kFarScaled;
+}
 
 struct ExpSum {
     float m, s;

@@ -456,6 +456,31 @@ __device__ __forceinline__ void mlist_tree(const MpfrArgs& a, MShared& sm, const
     if (tot == 0) __syncthreads();
 }
 
+// The LSE of a far row (far_row), which is read again for the sum of
+// exp((l - row maximum) / T).  red is LDS scratch of kMBlock / 64 entries.  Every thread
+// calls it, after a barrier; it ends with one.
+template <bool BF16>
+__device__ __forceinline__ void far_row_lse(const unsigned char* row, int V, float invT, float rowmax, float* lse_out,
+                                            float* red) {
+    const int tid = threadIdx.x;
+    const float c2 = invT * 1.4426950408889634f;
+    float s = 0.f;
+#pragma unroll 1
+    for (int base = 8 * tid; base < V; base += 8 * kMBlock) {
+        float x[8];
+        mload8<BF16>(row, V, base, x);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) s += __builtin_amdgcn_exp2f((x[i] - rowmax) * c2);
+    }
+    s = row16_sum(s);
+    s += __shfl_xor(s, 16);
+    s += __shfl_xor(s, 32);
+    if ((tid & 63) == 0) red[tid >> 6] = s;
+    __syncthreads();
+    if (tid == 0) *lse_out = rowmax * invT + ln_f32(((red[0] + red[1]) + red[2]) + red[3]);
+    __syncthreads();
+}
+
 // Stream one row: the maximum of every 128-token group (to gm in LDS) and the row maximum
 // (returned to every thread), and with LSE the log-sum-exp at T (to *lse_out).  red_* are
 // LDS scratch of kMBlock / 64 entries.  The pass is bound by vector instructions as much
@@ -540,7 +565,12 @@ __device__ __forceinline__ float mstream_row(const unsigned char* row, int V, fl
         if constexpr (LSE) *lse_out = xm == -INFINITY ? -INFINITY : (m + __builtin_amdgcn_logf(sacc)) * 0.69314718055994531f;
     }
     __syncthreads();
-    return *rowmax;
+    const float xm = *rowmax;
+    if constexpr (LSE) {
+        static_assert(kMBlock / 64 == 4, "four waves' sums");
+        if (far_row(xm, c2)) far_row_lse<BF16>(row, V, invT, xm, lse_out, red_s);  // (uniform)
+    }
+    return xm;
 }
 
 // Seed groups of a row: the largest group of each sixteenth of the row (lowest index on

@@ -353,6 +353,25 @@ __device__ __forceinline__ void lse_merge_finite(float& m, float& s, float om, f
     m = mn;
 }
 
+// The LSE of a far row (far_row) by one wave, which reads the row again for the sum of
+// exp((l - row maximum) / T).
+template <bool BF16>
+__device__ __forceinline__ float far_row_lse(const unsigned char* row, int V, float invT, float rowmax) {
+    const float c2 = invT * 1.4426950408889634f;
+    float s = 0.f;
+#pragma unroll 1
+    for (int base = 8 * (threadIdx.x & 63); base < V; base += 8 * 64) {
+        float x[8];
+        load8<BF16>(row, V, base, x);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) s += __builtin_amdgcn_exp2f((x[i] - rowmax) * c2);
+    }
+    s = row16_sum(s);
+    s += __shfl_xor(s, 16);
+    s += __shfl_xor(s, 32);
+    return rowmax * invT + ln_f32(s);
+}
+
 // One 32 KiB segment: the maximum logit of every 128-token group (16 lanes hold a
 // group) and the segment's sum of exp2(l * log2e / T - M), M = log2e / T * (segment
 // maximum).  Unless the workgroup is about to finish a row (which can wait on other
@@ -1601,8 +1620,9 @@ __device__ __forceinline__ void finish_row(const RaceArgs& a, const Row& r, Shar
         for (int t = lane; t < n3; t += 64) rm = fmaxf(rm, sm.m3[t]);
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) rm = fmaxf(rm, __shfl_xor(rm, off));
+        float lse = mi == -INFINITY ? -INFINITY : (mi + __builtin_amdgcn_logf(si)) * 0.69314718055994531f;
+        if (far_row(rm, c2) && (r.kind == 0 ? a.draft_lse : a.target_lse)) lse = far_row_lse<BF16>(r.ptr, a.V, r.invT, rm);
         if (lane == 0) {
-            const float lse = mi == -INFINITY ? -INFINITY : (mi + __builtin_amdgcn_logf(si)) * 0.69314718055994531f;
             if (r.kind == 0) {
                 if (a.draft_lse) a.draft_lse[((size_t)r.b * a.K + r.k) * a.gamma + r.s] = lse;
             } else if (a.target_lse) {
