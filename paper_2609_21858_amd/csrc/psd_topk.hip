@@ -344,7 +344,7 @@ __device__ __forceinline__ bool select_candidates(SelShared& sm, const unsigned 
     for (int q = 0; q < QG; ++q) {
         const int g = tid + kTBlock * q;
         const float m = g < ng ? sm.u.gm[g] : -INFINITY;
-        fin[q] = m >= -3.40282347e38f;  // a finite (or +inf) logit in the group; not NaN
+        fin[q] = m >= -3.40282347e38f;  // a finite (or +inf) logit in the group
         kg[q] = fin[q] ? key_f32(__float_as_uint(m)) : 0u;
     }
     int it = 0;
@@ -673,8 +673,9 @@ __global__ __launch_bounds__(kTBlock) void topk_select_kernel(TopkSelectArgs a) 
     // top-p on the sorted list: the shortest prefix whose normalised mass at T reaches
     // top_p; then the LSE of the kept set (fp64)
     const double T = (double)G.T;
+    // (a logit equal to the largest has term 1, +inf included)
     const double z0 = (double)sm.sval[0] / T;
-    const double e = tid < n ? exp((double)sm.sval[tid] / T - z0) : 0.0;
+    const double e = tid >= n ? 0.0 : sm.sval[tid] == sm.sval[0] ? 1.0 : exp((double)sm.sval[tid] / T - z0);
     double tot;
     const double inc = block_incl_sum_f64(sm, e, tot);
     int keep = n;
@@ -789,8 +790,9 @@ __device__ __forceinline__ void best2_wave(Best2& b) {
     for (int o = 1; o < 64; o <<= 1)
         best2_merge(b, __shfl_xor(b.s1, o), __shfl_xor(b.s2, o), __shfl_xor(b.vj, o));
 }
-// Whether the smallest score is certain (an empty set, or one of infinite scores, is).
-__device__ __forceinline__ bool best2_clear(const Best2& b) { return !(b.s2 - b.s1 <= kTMargin); }
+// Whether the smallest score is certain (that of an empty set is).  (No inf - inf: this file
+// is compiled with no NaNs.)
+__device__ __forceinline__ bool best2_clear(const Best2& b) { return b.s1 == INFINITY || b.s2 > b.s1 + kTMargin; }
 
 // A kept list's length, and the token and logit of an entry (psd_launch.hpp, TopkLayout).
 __device__ __forceinline__ int list_length(const TopkRaceArgs& a, int rid) { return (int)~a.list_len[rid]; }
@@ -857,8 +859,9 @@ __device__ Best2 wave_race32(const TopkRaceArgs& a, const ListHead& h, int rid, 
     const uint64_t* list = a.list + (size_t)rid * a.cap;
     const float invT = 1.0f / T;
     // (token, slot) packed as token * 32 + slot (tokens < 2^19, slots < 32)
-    // (a +inf logit has no float32 score here: never certain, so the exact race decides)
-    if (n > 0 && !(h.xmax < INFINITY)) return Best2{0.f, 0.f, -1};
+    // (a +inf logit, or a temperature whose reciprocal is not finite, has no float32 score
+    // here: never certain, so the exact race decides)
+    if (n > 0 && !(h.xmax < INFINITY && invT < INFINITY)) return Best2{0.f, 0.f, -1};
     Best2 b{INFINITY, INFINITY, -1};
     auto add = [&](int e, uint64_t le) {
         const int v = entry_token(le), j = slot0 + e % nslots;
@@ -934,7 +937,7 @@ __device__ bool wave_mpfr32(const TopkRaceArgs& a, RaceShared& sm, int w, const 
         return true;
     }
     const float invT = 1.0f / T, xmax = h.xmax;
-    if (!(xmax < INFINITY)) return false;
+    if (!(xmax < INFINITY && invT < INFINITY)) return false;
     float G[Q], xs[Q], sc[Q];
     int tok[Q];
 #pragma unroll
