@@ -57,5 +57,15 @@ def build(verbose: bool = False) -> str:
     return LIB
 
 
+def build_test_helper(src: str) -> str:
+    """Compile one HIP source of the tests to lib<name>.so in the _build folder beside it."""
+    out = os.path.join(os.path.dirname(src), "_build", "lib" + os.path.splitext(os.path.basename(src))[0] + ".so")
+    os.makedirs(os.path.dirname(out), exist_ok=True)
+    r = subprocess.run([hipcc()] + FLAGS + ["-shared", src, "-o", out], capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"hipcc failed for {src}:\n{r.stdout}\n{r.stderr}")
+    return out
+
+
 if __name__ == "__main__":
     build(verbose=True)

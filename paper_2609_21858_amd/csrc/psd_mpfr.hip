@@ -874,9 +874,9 @@ __device__ __forceinline__ void exact_samples(const MpfrArgs& a, MShared& sm, in
 // arrivals), the list is sorted by counting, and the first nu are the samples if each
 // is further from its successor than both scores can err.  -ln U in fp32 is within 1.7e-7
 // relative of the exact one for every one of the 2^23 uniforms (measured over all of
-// them), so sums of clocks are within 1e-6 relative; the logarithm adds 1.7e-6 and the
-// scaled logit 2.4e-7 of its size: 2e-5 + 1e-6 |scaled logit| is assumed, several times
-// their sum.  Returns false when the order is not decided (exact_samples then does it).
+// them), so sums of clocks are within 1e-6 relative; the logarithm adds at most 4e-6 (3.7e-6
+// measured over [2^-44, 2^8)) and the scaled logit 2.4e-7 of its size:
+// 2e-5 + 1e-6 |scaled logit| is assumed, four times their sum.  Returns false when the order is not decided (exact_samples then does it).
 // Every thread calls it.
 template <int LAYOUT>
 __device__ __forceinline__ bool sorted_samples(const MpfrArgs& a, MShared& sm, int nc, int nu, float shift, uint32_t k0,
