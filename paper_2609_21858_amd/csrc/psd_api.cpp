@@ -490,7 +490,9 @@ psd_status verify_mpfr_forked(const psd_params* params, const psd_block* block, 
     // workgroups than it would take alone, which leaves room for the others': per call
     // at V=128256, K=4, gamma=4, B=64 (V=256000, K=16, B=256) 384 take 136 (2190) us,
     // 256 146 (2230), 512 141 (2200), 1024 152 (2330) (with the draft rows streamed on a side
-    // stream).
+    // stream).  These two are the only shapes measured; the number limits the
+    // launch's share of the device (384 of 1024 places: 258 streaming workgroups, 126 that
+    // finish rows), whatever the numbers of draft and target rows.
     a.max_grid = 384;
     if (by_depth) {
         // Each depth's rows on the side stream, its sampling on the caller's once they are

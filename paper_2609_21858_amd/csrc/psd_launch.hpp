@@ -61,7 +61,8 @@ struct MpfrArgs {
     // sampling launches then find both from the group maxima.
     uint64_t* row_gm;           // [B*K*gamma][groups] group maxima of the draft rows (float bits)
     uint64_t* row_max;          // [B*K*gamma] their maxima (float bits)
-    uint64_t* row_seed;         // [B*K*gamma][8] their seed tokens (-1: none)
+    uint64_t* row_seed;         // [B*K*gamma][8] their 16 seed tokens, two per payload: each one's
+                                // offset from its sixteenth of the row (0xFFFF: none)
     uint64_t* tok_slot;         // nullable [B*K*gamma]: the drafts of a launch that runs every
                                 // depth, as (epoch << 32) | token, for the later depths' waits
     uint32_t spin_limit;        // polls of a bounded wait before it gives up
@@ -87,7 +88,7 @@ inline MpfrLayout mpfr_layout(const WsLayout& L, int B, int K, int gamma) {
     M.gm = L.total;
     M.rmax = align256(M.gm + rows * (size_t)L.ng * 8);
     M.seed = align256(M.rmax + rows * 8);
-    M.slot = align256(M.seed + rows * 8 * 8);  // 8 seeds per row
+    M.slot = align256(M.seed + rows * 8 * 8);  // 8 words of seeds per row
     // one tagged draft per row, then [B][gamma+1] words that nothing uses (they keep the
     // workspace's size)
     M.total = align256(align256(M.slot + rows * 8) + (size_t)B * (gamma + 1) * 4);

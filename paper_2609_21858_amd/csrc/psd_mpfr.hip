@@ -267,8 +267,8 @@ __device__ __forceinline__ uint32_t wave_reserve(uint32_t* count, uint32_t n) {
 // Listed halves of the groups [first, first + cnt) of the list, four entries per 16-lane
 // row at a time.
 template <bool BF16>
-__device__ __forceinline__ void mlist_halves(const MpfrArgs& a, MShared& sm, const unsigned char* row, const float* gm,
-                                             float shift, int first, int cnt, int par) {
+__device__ __forceinline__ void mlist_halves(const MpfrArgs& a, MShared& sm, const unsigned char* row, float shift,
+                                             int first, int cnt, int par) {
     constexpr int U = 4;
     const int tid = threadIdx.x, c = tid & 15, r16 = tid >> 4;
     const float theta = sm.theta;
@@ -363,8 +363,8 @@ __device__ __forceinline__ void mscore_halves(const MpfrArgs& a, MShared& sm, fl
 // Evaluate and empty the group list (after a barrier; ends with one).  par: parity of
 // the half count in use, the other one being 0.
 template <bool BF16>
-__device__ __forceinline__ void mflush_groups(const MpfrArgs& a, MShared& sm, const unsigned char* row, const float* gm,
-                                              float shift, uint32_t k0, uint32_t k1, int& par) {
+__device__ __forceinline__ void mflush_groups(const MpfrArgs& a, MShared& sm, const unsigned char* row, float shift,
+                                              uint32_t k0, uint32_t k1, int& par) {
     const int n = sm.n_lg;
     if (n == 0) {
         __syncthreads();
@@ -373,7 +373,7 @@ __device__ __forceinline__ void mflush_groups(const MpfrArgs& a, MShared& sm, co
     int step = 64;
     for (int first = 0; first < n;) {
         const int cnt = min(n - first, step);
-        mlist_halves<BF16>(a, sm, row, gm, shift, first, cnt, par);
+        mlist_halves<BF16>(a, sm, row, shift, first, cnt, par);
         __syncthreads();
         const int nh = sm.n_half[par];
         if (threadIdx.x == 0) {
@@ -449,7 +449,7 @@ __device__ __forceinline__ void mlist_tree(const MpfrArgs& a, MShared& sm, const
         __syncthreads();
         wb += kMBlock;
         if (wb >= tot || sm.n_lg > kMGroupCap - kMBlock)
-            mflush_groups<BF16>(a, sm, row, gm, shift, k0, k1, par);
+            mflush_groups<BF16>(a, sm, row, shift, k0, k1, par);
         else
             __syncthreads();
     }

@@ -10,7 +10,8 @@
 // loads, the online log-sum-exp partial (sum of exp2 relative to the segment
 // maximum) and the maximum logit of every 128-token group.  Each value is published
 // as one 64-bit slot tagged with the call's epoch, so nothing waits for stores to
-// drain and nothing is cleared between calls.  Every third workgroup finishes rows: it
+// drain and nothing is cleared between calls.  Of every nine consecutive workgroups the
+// last three finish rows, the others only stream: a finishing workgroup
 // gathers a row's slots and does all key-independent work (maxima, seed tokens, LSE, what
 // the race draws first), takes the context key from the race one depth up the path,
 // runs the keyed race, publishes the winner and the next depth's key and -- for the
@@ -57,8 +58,9 @@ constexpr int kRolePeriod = 9;             // workgroup roles: of every kRolePer
 constexpr int kRoleFinish = 3;             // kRoleFinish finish rows and the others stream
 constexpr int kHalfCap = 256;              // 4-token halves listed by one evaluation pass
 constexpr int kPassGroups = 16 * kRowEntries;  // group entries of one evaluation pass
-constexpr int kEvalGroups = 128;           // group entries of one evaluation pass (tree clocks; 64: 100 vs 96 us at
-                                           // V = 32000, K = 4, 1383 vs 1395 at V = 151936, K = 8)
+constexpr int kEvalGroups = 128;           // group entries of one evaluation pass (tree clocks; with 64 the V = 32000,
+                                           // K = 4 block, a chain of races, takes 4 % longer, 100 vs 96 us, and the
+                                           // V = 151936, K = 8 one, bound by streaming, 0.9 % less, 1383 vs 1395)
 constexpr int kBuckets = 32;               // bound buckets of the group list's evaluation order
 constexpr float kMargin = 1e-3f;           // float32 pruning / candidate margin (score units)
 constexpr float kCutSlack = 1e-3f;         // slack of the per-token logit cut (score units)
@@ -81,7 +83,6 @@ struct Half {
 
 struct Shared {
     float m3[256];
-    float m4[16];
     int init_v[kInit];     // seed groups of the race (-1: none)
     int seed_tok[kInit];   // seed tokens of the race (-1: none)
     float part[64];        // LSE partial sum of every segment
@@ -119,7 +120,6 @@ struct Shared {
     uint64_t* pub_key;
     uint64_t* pub_tok;
     int32_t* pub_out;
-    int win[32];            // context tokens (own window, next depth's window)
     int key_min, key_max;   // (token, slot) range of the candidates near the best
     uint32_t err_local;       // error bits this workgroup recorded (it then publishes them with a release)
     uint16_t work[kWorkCap];  // compacted work items (level-3 list index * 16 + group)
@@ -1070,7 +1070,8 @@ __device__ __forceinline__ uint32_t pick_word(uint32_t a0, uint32_t a1, uint32_t
 // What lane e of pass A draws, all of it known before the context key: the counter and
 // slot, the node's size (and its reciprocal) and first token, and the seed it belongs to.
 // A row whose key is still on its way works it out meanwhile: 43.3 -> 42.3 us per block at
-// V = 1024, K = 2, gamma = 4, B = 1, 97.6 -> 95.2 at V = 32000, K = 4, gamma = 5, B = 16,
+// V = 1024, K = 2, gamma = 4, B = 1, 97.6 -> 95.2 at V = 32000, K = 4, gamma = 5, B = 16 (two
+// builds in turn; that block takes 94 to 104 us from one process to another),
 // equal (93.6) at V = 128256, K = 4, gamma = 4, B = 64, whose rows mostly find the key there.
 // (With a plan for lanes that draw nothing, the streamers lose the issue slots: 94.0.)
 struct SeedPlan {
@@ -1117,13 +1118,10 @@ __device__ __forceinline__ void race(const RaceArgs& a, const Row& r, Shared& sm
     // Pass A: the seed tokens (each the largest logit of its group) in every slot --
     // tree clocks: 8 lanes per (token, slot), lane l < 6 drawing path node l -- and,
     // for tree clocks, the minimum of every (slot, level-4 node): lanes 6 and 7 of the
-    // seed lanes of slot j take its first 2 kInit level-4 nodes (with the root drawn
-    // by lane 0), lanes past the seed lanes the rest, one item per lane.
-    const int nseed = kInit;
-    const int seed_lanes = nseed * ns * 8;
-    const int n4x = max(0, n4 - 2 * nseed);  // level-4 nodes per slot past the seed lanes
-    const int nA = seed_lanes + (LAYOUT == 0 ? ns * n4x : 0);
-    for (int e0 = 0; e0 < nA; e0 += kBlock) {
+    // seed lanes of slot j take its level-4 nodes (with the root drawn by lane 0).
+    static_assert((1 << (kShift5 - kShift4)) <= 2 * kInit, "two lanes per seed hold every level-4 node");
+    const int seed_lanes = kInit * ns * 8;
+    for (int e0 = 0; e0 < seed_lanes; e0 += kBlock) {
         const int e = e0 + tid;
         if (e < seed_lanes) {  // whole 8-lane groups: the shuffles stay within active lanes
             const int l = e & 7;
@@ -1185,20 +1183,6 @@ __device__ __forceinline__ void race(const RaceArgs& a, const Row& r, Shared& sm
                     }
                 }
             }
-        } else if (LAYOUT == 0 && e < nA) {
-            // level-4 node i4 of slot j past the seed lanes: root and node draws
-            // issued together
-            const int it = e - seed_lanes, j = it / n4x;
-            const uint32_t i4 = (uint32_t)(2 * nseed + it % n4x);
-            const uint32_t slot = (uint32_t)(r.slot0 + j);
-            const Words wr = philox(0u, slot, 5u, kDomainTree, k0, k1);
-            const Words w4 = philox(i4, slot, 4u, kDomainTree, k0, k1);
-            const float rm = div_n(exp1_f32(wr.w0), V);
-            const uint32_t rp = uniform_position(wr.w1, wr.w2, V);
-            const uint32_t cs = i4 << kShift4, n = node_end(kShift4, i4, V) - cs;
-            const bool hold = rp >= cs && rp < cs + n;
-            level4_list(gm, ng)[j * n4 + (int)i4] = Node{(slot << 20) | i4, hold ? rm : rm + div_n(exp1_f32(w4.w0), n),
-                             hold ? rp : cs + uniform_position(w4.w1, w4.w2, n)};
         }
     }
     __syncthreads();
@@ -1484,7 +1468,7 @@ __device__ __forceinline__ void finish_row(const RaceArgs& a, const Row& r, Shar
         __builtin_amdgcn_s_setprio(1);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int ng = a.L.ng;
-    const int n3 = (ng + 15) / 16, n4 = (n3 + 15) / 16;
+    const int n3 = (ng + 15) / 16;
     const uint32_t ep = sm.epoch;
     const float c2 = r.invT * 1.4426950408889634f;
 
@@ -1544,8 +1528,7 @@ __device__ __forceinline__ void finish_row(const RaceArgs& a, const Row& r, Shar
     }
     __syncthreads();
 
-    // ---- key-independent work: the race's seed tokens, level-4 maxima, LSE, row
-    // maximum.  Seed groups: the largest group of each eighth of the row (lowest index
+    // ---- key-independent work: the race's seed tokens, LSE, row maximum.  Seed groups: the largest group of each eighth of the row (lowest index
     // on ties; -1 where the eighth has no finite logit), 32 lanes per eighth.  A row of
     // any size gets up to 8 seeds this way: with one seed per 32 KiB segment a
     // 32000-token bf16 row had two, and its 4-slot races listed 111 (slot, group)
@@ -1574,8 +1557,8 @@ __device__ __forceinline__ void finish_row(const RaceArgs& a, const Row& r, Shar
     }
     __syncthreads();
     // Waves 0-1: the seed tokens, 16 lanes per seed group with 8 tokens each (the
-    // group's lowest token holding its maximum); wave 2: level-4 maxima, LSE, row
-    // maximum; wave 3: the context keys.  The four run side by side.
+    // group's lowest token holding its maximum); wave 2: LSE, row maximum; wave 3: the
+    // context keys.  The four run side by side.
     if (wave < 2) {
         static_assert(kInit * 16 == 128, "one 16-lane row per seed group in waves 0-1");
         const int i = tid >> 4, sub = tid & 15;
@@ -1594,11 +1577,6 @@ __device__ __forceinline__ void finish_row(const RaceArgs& a, const Row& r, Shar
         for (int off = 8; off > 0; off >>= 1) tk = min(tk, __shfl_xor(tk, off));
         if (sub == 0) sm.seed_tok[i] = g >= 0 && tk != 0x7FFFFFFF ? tk : -1;
     } else if (wave == 2) {
-        if (lane < n4) {
-            float mx = -INFINITY;
-            for (int t = 16 * lane; t < min(n3, 16 * lane + 16); ++t) mx = fmaxf(mx, sm.m3[t]);
-            sm.m4[lane] = mx;
-        }
         // LSE: segment i's maximum is the maximum of its groups (the same float product
         // the segment used), merged with the segments' sums in float32.
         constexpr int per = (BF16 ? kSegTokensBf16 : kSegTokensF32) / 2048;  // level-3 blocks per segment

@@ -8,13 +8,14 @@
 //    keeps only the maximum of every 128-token group; the top_k-th largest group
 //    maximum bounds the row's top_k-th largest logit from below, so only the groups
 //    whose maximum reaches it are read again and their logits that reach it are the
-//    candidates (wave buffers in LDS: ballot and lane prefix, no atomics).  Block-wide
-//    bisections over the candidates' keys and then their indices pick the k largest
-//    (order-preserving keys, ties to the lowest index).  Rows whose ties at the cut
-//    overflow the buffers are selected by exact radix passes instead.  Then the kept
-//    list is sorted by (logit descending, index ascending), its top-p prefix and the
-//    log-sum-exp of the kept set at the row's temperature are formed in fp64;
-//  * the races over the lists, exact fp64 clocks of every (token, slot) -- distinct
+//    candidates (wave buffers in LDS: wave prefix sums, no atomics).  Up to 256 of them
+//    are ranked by counting, which leaves the k largest sorted (order-preserving keys,
+//    ties to the lowest index); more are cut by block-wide bisections over their keys and
+//    then their indices, and sorted.  Rows whose ties at the cut overflow the buffers are
+//    selected by exact radix passes instead.  The top-p prefix and the log-sum-exp of the
+//    kept set at the row's temperature are formed in fp64;
+//  * the races over the lists: float32 clocks of every (token, slot), and fp64 ones where
+//    the float32 scores do not decide -- distinct
 //    drafters race slot k / all K slots, identical drafters draw each context's nu
 //    samples from the cumulative clocks and race the targets on slot 0 -- then the
 //    walk.  Distinct drafters (drafting, or with the shared target chain):
